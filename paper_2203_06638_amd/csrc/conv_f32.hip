@@ -372,117 +372,247 @@ static hipError_t launch_lds(const float* src, const float* B, const float* bias
     return hipGetLastError();
 }
 
-// Spatially tiled variant (stride-1 data gradients and any forward pass with
-// Cs % 16 == 0 whose tile shape fits): a workgroup computes OH full output
-// rows of one image (TP = OH * Wo pixels) for BN output channels.  For each
-// group of 16 source channels it loads the input rows the tile reads, halo
-// and padding included (IH x IW pixels), and the filter slice (BN x R*S x
-// 16) into LDS once, then runs every tap from LDS: the 3x3 halo is fetched
-// from memory once instead of once per tap.  The data gradient of a stride-1
-// conv is a forward conv of dY with the filter flipped and padding R-1-pad.
-// IW_inv = ceil(2^32 / IW): pix / IW == umulhi(pix, IW_inv) for the pixel
-// counts of an LDS tile (pix * IW < 2^32).
-struct TileGeom { int OH, IH, IW, pad_eff, tiles_per_img; unsigned IW_inv; };
+// ------------------------------------------------------------------------
+// spatial tiles: boxes of pixel slots over the stacked images
+// ------------------------------------------------------------------------
 
+// The images' output rows are stacked (row R = n * Hper + h).  A box is OH
+// stacked rows x OW columns in OH x OWs slots (OWs >= OW); nc boxes side by
+// side cover a row, and a box may reach over the end of an image, so any
+// image size fills its slots.  Its input rows are rows of the padded stack,
+// Hp rows an image, of which output row R reads S(R), S(R) + 1, ...,
+// S(R) = n * Hp + h * step.
+struct BoxGeom {
+    int OH, OW, OWs, nc;        // box; boxes per row
+    int rows;                   // Nb * Hper
+    int Hper, Wo;               // output rows and columns of one image
+    int Hp, step;               // padded rows of one image, rows between output rows
+    int IH, IW;                 // staged rows and columns
+    int pad_eff;                // input row of padded row hh: hh - pad_eff
+    unsigned OWs_inv, IW_inv, Hper_inv, Hp_inv, nc_inv;
+};
+
+// n / d == box_div(n, box_inv(d)) for n * d < 2^32 (checked on the host)
+static unsigned box_inv(int d) { return d == 1 ? 0u : (unsigned)((0x100000000ull + d - 1) / d); }
+__device__ __forceinline__ int box_div(int n, unsigned inv) { return inv ? (int)__umulhi((unsigned)n, inv) : n; }
+
+// S(R)
+__device__ __forceinline__ int box_prow(const BoxGeom& t, int R) {
+    const int n = box_div(R, t.Hper_inv);
+    return n * t.Hp + (R - n * t.Hper) * t.step;
+}
+
+// Tensors are read through buffer descriptors: a load at kNoLoad lies past
+// every one and returns zero, so the zero padding costs no branch, and (unlike
+// a pointer chosen at run time, a flat address) the loads count apart from the
+// LDS accesses and stay in flight across a barrier and the MFMAs.
+constexpr unsigned kNoLoad = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const float* p, long n) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)(n * 4), 0x00020000);
+}
+__device__ __forceinline__ f4 buf_load4(__amdgpu_buffer_rsrc_t r, unsigned off, int soff) {
+    return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
+}
+// the workgroup's LDS accesses done, loads from memory left in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Fills the geometry of boxes of `slots` slots, nc to a row, over Nb images of
+// Hper x Wo outputs, each reading `ext` padded rows and columns, `step` apart;
+// box columns are rounded up to a multiple of cq slots.  False when a box
+// stages more than max_batches * 64 input pixels or an index leaves box_div's
+// range.
+static bool box_fill(BoxGeom& t, int Nb, int Hper, int Wo, int ext, int step, int pad_eff, int slots, int nc, int cq,
+                     int max_batches) {
+    const long rows = (long)Nb * Hper;
+    if (nc > Wo || rows >= (1L << 30)) return false;
+    t.OW = (Wo + nc - 1) / nc;
+    t.OWs = (t.OW + cq - 1) / cq * cq;
+    if (t.OWs > slots) return false;
+    t.nc = (Wo + t.OW - 1) / t.OW;
+    t.OH = (int)std::min<long>(slots / t.OWs, rows);
+    t.rows = (int)rows;
+    t.Hper = Hper;
+    t.Wo = Wo;
+    t.step = step;
+    t.Hp = (Hper - 1) * step + ext;
+    t.pad_eff = pad_eff;
+    // over the ends of as many images as OH rows can reach over
+    const int ends = Hper % t.OH == 0 ? 0 : (t.OH + Hper - 2) / Hper;
+    t.IH = (t.OH - 1) * step + ext + ends * std::max(0, ext - step);
+    t.IW = (t.OWs - 1) * step + ext;
+    if ((t.IH * (long)t.IW + 63) / 64 > max_batches) return false;
+    const double tiles = (double)((rows + t.OH - 1) / t.OH) * t.nc;
+    if (((double)Nb * t.Hp + t.IH) * t.Hp >= 4294967296.0 || (double)rows * Hper >= 4294967296.0 ||
+        tiles >= 1073741824.0 || tiles * t.nc >= 4294967296.0)
+        return false;
+    t.OWs_inv = box_inv(t.OWs);
+    t.IW_inv = box_inv(t.IW);
+    t.Hper_inv = box_inv(Hper);
+    t.Hp_inv = box_inv(t.Hp);
+    t.nc_inv = box_inv(t.nc);
+    return true;
+}
+static int box_tiles(const BoxGeom& t) { return (t.rows + t.OH - 1) / t.OH * t.nc; }
+
+// The number of boxes per row: among those within 4% of the fewest boxes, the
+// one that stages the fewest batches of 64 input pixels, then the fewest
+// boxes.  (At 28 columns and 64 slots 16 x 4 boxes fill all slots, 2 x 28 only
+// 56; square boxes stage the smallest halo.)
+static bool box_pick(BoxGeom& out, int Nb, int Hper, int Wo, int ext, int step, int pad_eff, int slots, int cq,
+                     int max_batches) {
+    long fewest = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        long best = 0;
+        for (int nc = 1; nc <= 32; ++nc) {
+            BoxGeom t;
+            if (!box_fill(t, Nb, Hper, Wo, ext, step, pad_eff, slots, nc, cq, max_batches)) continue;
+            const long n = box_tiles(t);
+            if (pass == 0) {
+                if (!fewest || n < fewest) fewest = n;
+                continue;
+            }
+            if (n * 25 > fewest * 26) continue;
+            const long score = (long)((t.IH * t.IW + 63) / 64) * (1L << 31) + n;
+            if (!best || score < best) {
+                best = score;
+                out = t;
+            }
+        }
+        if (!fewest) return false;
+    }
+    return true;
+}
+
+// Bytes of a tensor of n floats addressable with the kernels' 32-bit offsets
+static bool buf_fits(double n) { return 4.0 * n < 2147483648.0; }
+
+// Spatially tiled convolution (3x3 and 1x1 passes with Cs % 4 == 0: forward
+// with any stride, stride-1 data gradients; the data gradient of a stride-1
+// conv is a forward conv of dY with the filter flipped and padding KS-1-pad).
+// A workgroup takes one box of TM * 64 pixel slots and TN * 16 output
+// channels.  Per 16 source channels the box's input rows, halo and padding
+// included, and the filter slice go into LDS once and every tap runs from
+// there; the next channel group's loads are in flight during this group's
+// MFMAs.  At ResNet-20's sizes a pass is one round of workgroups, bound by the
+// latency of its phases (loads, MFMAs, epilogue), so small boxes with several
+// workgroups to a compute unit, whose phases overlap, are the fastest: 128
+// slots where they still give 512 workgroups, else 64 (measured over 38
+// passes within 2% of the best of 64/128/256 slots x 16/32 channels).
+// 1x1 passes are bound by staging and take 32 channels where that still gives
+// 512 workgroups.  Against tiles of whole rows (which took only widths that
+// divide 64, 128 or 256, staged through flat loads that the compiler drained
+// before the MFMAs): ResNet-20's stages 11.7 / 10.5 / 10.9 -> 10.9 / 9.5 / 9.4
+// us forward; against the GEMM kernel that other widths ran on: 100 x 28x28x16
+// 16.9 -> 8.9 us, 16 x 56x56x64 62 -> 43 us, 16 x 28x28x128 69 -> 43 us.
+//
 // INBN (forward passes): the source is the input of a training-mode batch
 // norm followed by a ReLU; each staged source value becomes
 // relu(fma(x, scale[c], shift[c])) (padding stays zero), with the per-channel
 // coefficients derived in the prologue from the batch sums (or read from aux;
 // bnacc.h).  The normalised tensor is never stored.
-// Variants with at most two row blocks per wave and no epilogue statistics
-// or folded input fit 128 registers without spilling: they are held to that,
-// for four waves per SIMD instead of three.
-// 16 bytes of device memory at p, through a global-address-space pointer (a
-// pointer chosen at run time between buffers would otherwise be a flat
-// address, whose loads also count with the LDS accesses)
-__device__ __forceinline__ f4 ld_global4(const float* p) {
-    return *(const __attribute__((address_space(1))) f4*)p;
-}
+constexpr int kTileBatches = 6;   // staged input quads per thread and channel group, at most
 
-template <int MODE, int KS, int WM, int TM, int TN, bool STATS, bool INBN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((TM <= 2 && !INBN && !STATS) ? 4 : 1, 8)))
-void conv_tile_f32(const float* __restrict__ src, const float* __restrict__ B,
-                                                     const float* __restrict__ bias, float* __restrict__ Y,
-                                                     ConvGeom g, TileGeom t, int accumulate, BnSums sums, BnFwd inbn,
-                                                     BnBwdSum bs) {
-    constexpr int WN = 4 / WM;
-    constexpr int TP = WM * TM * 16, BN = WN * TN * 16;
-    constexpr int LDW = 20;
-    constexpr int RS = KS * KS;
-    constexpr int NU = 8;                         // float4 loads in flight per thread
+template <int MODE, int KS, int TM, int TN, bool STATS, bool INBN>
+__global__ __launch_bounds__(256) void conv_tile_f32(const float* __restrict__ src, const float* __restrict__ B,
+                                                    const float* __restrict__ bias, float* __restrict__ Y, ConvGeom g,
+                                                    BoxGeom t, int accumulate, BnSums sums, BnFwd inbn, BnBwdSum bs) {
+    constexpr int BN = TN * 16, RS = KS * KS, LDW = 20;
+    constexpr int NW = (BN * RS * 4 + 255) / 256;     // weight quads per thread and channel group
     extern __shared__ float lds[];
-    float* Xs = lds;                              // [IH*IW][LDW]
-    float* Ws = lds + t.IH * t.IW * LDW;          // [BN*RS][LDW]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WM, wn = wave / WM;
-    const int gi = lane >> 4, li = lane & 15;
-    const int img = blockIdx.x / t.tiles_per_img;
-    const int oh0 = (blockIdx.x - img * t.tiles_per_img) * t.OH;
+    const int gi = lane >> 4, li = lane & 15, q = tid & 3;
+    const int tr = box_div((int)blockIdx.x, t.nc_inv), tc = (int)blockIdx.x - tr * t.nc;
+    const int R0 = tr * t.OH, w0 = tc * t.OW;
+    const int ohv = min(t.OH, t.rows - R0), owv = min(t.OW, t.Wo - w0);
     const int n0 = blockIdx.y * BN;
-    const int st = g.stride;
-    const int h_org = oh0 * st - t.pad_eff, w_org = -t.pad_eff;
-    const int npix = t.OH * g.Wo;
+    const int P0 = box_prow(t, R0);
+    const int nx = t.IH * t.IW * 4, nxu = (nx + 255) >> 8;   // staged input quads, batches of them
+    float* Xs = lds;                                  // [IH * IW][LDW]
+    float* Ws = lds + t.IH * t.IW * LDW;              // [BN * RS][LDW]
 
     __shared__ float in_co[INBN ? 2 * kFoldMaxC : 1];   // scale | shift of the source channels
-    if (INBN) {
-        bn_fwd_coeffs(inbn, g.Cs, in_co, in_co + kFoldMaxC);
-        __syncthreads();
-    }
-    // relu(fma(v, scale, shift)) of source quad c..c+3 (INBN)
-    auto fold = [&](f4 v, int c) {
-        if (INBN) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = fmaxf(__builtin_fmaf(v[k], in_co[c + k], in_co[kFoldMaxC + c + k]), 0.f);
-        }
-        return v;
-    };
+    if (INBN) bn_fwd_coeffs(inbn, g.Cs, in_co, in_co + kFoldMaxC);
 
-    // LDS offset of the input pixel each of this lane's output rows reads at tap (0,0)
+    // byte offsets of this thread's quads at channel group 0
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(src, (long)g.Nb * g.Hs * g.Ws * g.Cs);
+    const __amdgpu_buffer_rsrc_t wr = buf_rsrc(B, (long)g.Ncols * RS * g.Cs);
+    unsigned xo[kTileBatches], wo[NW];
+#pragma unroll
+    for (int u = 0; u < kTileBatches; ++u) {
+        xo[u] = kNoLoad;
+        if (u < nxu) {
+            const int pix = (tid + u * 256) >> 2;
+            const int ih = box_div(pix, t.IW_inv), iw = pix - ih * t.IW;
+            const int pr = P0 + ih;
+            const int n = box_div(pr, t.Hp_inv), hh = pr - n * t.Hp;
+            // a 1x1 pass stages only the pixels it reads
+            const int h = (KS == 1 ? hh * g.stride : hh) - t.pad_eff;
+            const int w = (KS == 1 ? (w0 + iw) * g.stride : w0 * g.stride + iw) - t.pad_eff;
+            if (ih < t.IH && n < g.Nb && h >= 0 && h < g.Hs && w >= 0 && w < g.Ws)
+                xo[u] = (unsigned)(((n * g.Hs + h) * g.Ws + w) * g.Cs + q * 4) * 4u;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+        const int rest = (tid + u * 256) >> 2;
+        const int nl = rest / RS, tap = rest - nl * RS;
+        const int stap = MODE == CONV_FWD ? tap : RS - 1 - tap;
+        wo[u] = (nl < BN && n0 + nl < g.Ncols) ? (unsigned)(((n0 + nl) * RS + stap) * g.Cs + q * 4) * 4u : kNoLoad;
+    }
+    f4 xv[kTileBatches], wv[NW];
+    auto load = [&](int c0) {
+        const unsigned bad = c0 + q * 4 < g.Cs ? 0u : kNoLoad;
+#pragma unroll
+        for (int u = 0; u < kTileBatches; ++u)
+            if (u < nxu) xv[u] = buf_load4(xr, xo[u] | bad, c0 * 4);
+#pragma unroll
+        for (int u = 0; u < NW; ++u) wv[u] = buf_load4(wr, wo[u] | bad, c0 * 4);
+    };
+    load(0);
+
+    // LDS offset of the input pixel each of this lane's slots reads at tap
+    // (0, 0); slots outside the box's pixels read the first one's
     int abase[TM];
 #pragma unroll
     for (int x = 0; x < TM; ++x) {
-        int p = (wm * TM + x) * 16 + li;
-        p = p < npix ? p : npix - 1;
-        const int oh = p / g.Wo, ow = p - (p / g.Wo) * g.Wo;
-        abase[x] = (oh * st * t.IW + ow * st) * LDW + gi * 4;
+        const int p = (wave * TM + x) * 16 + li;
+        const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+        const bool ok = oh < ohv && ow < owv;
+        const int prow = ok ? box_prow(t, R0 + oh) - P0 : 0;
+        abase[x] = (prow * t.IW + (ok ? ow * (KS == 1 ? 1 : g.stride) : 0)) * LDW + gi * 4;
     }
-
     f4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    if (INBN) __syncthreads();
 
-    // loader: element e = tid + 256 u has quad q = tid & 3 in both parts.
-    // When a channel group fits one batch (ntot <= NU*256), the addresses
-    // are decoded once and the next group's loads -- the same addresses 16
-    // channels on -- are issued before this group's MFMAs.
-    const int q = tid & 3;
-    const int nx = t.IH * t.IW * 4, ntot = nx + BN * RS * 4;
-    const int ngroups = g.Cs >> 4;
-    // decode: the element's source quad sp (nullptr: none -- zero padding, a
-    // column past the output) and its LDS offset d (-1: past the tiles)
-    auto decode = [&](int e, const float*& sp, int& d) {
-        sp = nullptr;
-        d = -1;
-        if (e < nx) {
-            const int pix = e >> 2;
-            const int ih = (int)__umulhi((unsigned)pix, t.IW_inv);
-            const int iw = pix - ih * t.IW;
-            const int h = h_org + ih, w = w_org + iw;
-            if (h >= 0 && h < g.Hs && w >= 0 && w < g.Ws)
-                sp = src + ((long)(img * g.Hs + h) * g.Ws + w) * g.Cs + q * 4;
-            d = pix * LDW + q * 4;
-        } else if (e < ntot) {
-            const int rest = (e - nx) >> 2;
-            const int tap = rest % RS, nl = rest / RS;
-            const int n = n0 + nl;
-            const int stap = MODE == CONV_FWD ? tap : RS - 1 - tap;
-            if (n < g.Ncols) sp = B + ((long)n * RS + stap) * g.Cs + q * 4;
-            d = t.IH * t.IW * LDW + rest * LDW + q * 4;
+    const int sdst = (tid >> 2) * LDW + q * 4;
+    for (int c0 = 0; c0 < g.Cs; c0 += 16) {
+        if (INBN) {
+            // relu(fma(x, scale, shift)); the zero padding stays zero
+            f4 sc = f4{0.f, 0.f, 0.f, 0.f}, sh = sc;
+            if (c0 + q * 4 < g.Cs) {
+                sc = *(const f4*)(in_co + c0 + q * 4);
+                sh = *(const f4*)(in_co + kFoldMaxC + c0 + q * 4);
+            }
+#pragma unroll
+            for (int u = 0; u < kTileBatches; ++u)
+                if (u < nxu) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        xv[u][k] = xo[u] == kNoLoad ? 0.f : fmaxf(__builtin_fmaf(xv[u][k], sc[k], sh[k]), 0.f);
+                }
         }
-    };
-    auto compute = [&]() {
+#pragma unroll
+        for (int u = 0; u < kTileBatches; ++u)
+            if (u < nxu && tid + u * 256 < nx) *(f4*)(Xs + sdst + u * 64 * LDW) = xv[u];
+#pragma unroll
+        for (int u = 0; u < NW; ++u)
+            if (tid + u * 256 < BN * RS * 4) *(f4*)(Ws + sdst + u * 64 * LDW) = wv[u];
+        lds_barrier();
+        if (c0 + 16 < g.Cs) load(c0 + 16);            // in flight during this group's MFMAs
 #pragma unroll
         for (int tap = 0; tap < RS; ++tap) {
             const int toff = ((tap / KS) * t.IW + tap % KS) * LDW;
@@ -490,8 +620,7 @@ void conv_tile_f32(const float* __restrict__ src, const float* __restrict__ B,
 #pragma unroll
             for (int x = 0; x < TM; ++x) a[x] = *(const f4*)(Xs + abase[x] + toff);
 #pragma unroll
-            for (int y = 0; y < TN; ++y)
-                b[y] = *(const f4*)(Ws + (((wn * TN + y) * 16 + li) * RS + tap) * LDW + gi * 4);
+            for (int y = 0; y < TN; ++y) b[y] = *(const f4*)(Ws + ((y * 16 + li) * RS + tap) * LDW + gi * 4);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -499,71 +628,13 @@ void conv_tile_f32(const float* __restrict__ src, const float* __restrict__ B,
 #pragma unroll
                     for (int y = 0; y < TN; ++y) acc[x][y] = mfma16x16x4(a[x][j], b[y][j], acc[x][y]);
         }
-    };
-    if (ntot <= NU * 256) {
-        const float* sp[NU];
-        int d[NU];
-        f4 v[NU];
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            decode(tid + u * 256, sp[u], d[u]);
-            v[u] = sp[u] ? *(const f4*)sp[u] : f4{0.f, 0.f, 0.f, 0.f};
-        }
-        for (int cgp = 0; cgp < ngroups; ++cgp) {
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-                if (d[u] >= 0)
-                    *(f4*)(lds + d[u]) = (INBN && sp[u] && tid + u * 256 < nx) ? fold(v[u], cgp * 16 + q * 4) : v[u];
-            __syncthreads();
-            if (cgp + 1 < ngroups) {
-                const int c1 = (cgp + 1) * 16;
-#pragma unroll
-                for (int u = 0; u < NU; ++u) v[u] = sp[u] ? *(const f4*)(sp[u] + c1) : f4{0.f, 0.f, 0.f, 0.f};
-            }
-            compute();
-            __syncthreads();
-        }
-    } else {
-        for (int cgp = 0; cgp < ngroups; ++cgp) {
-            const int c0 = cgp * 16;
-            for (int base = tid; base < ntot; base += NU * 256) {
-                // all of the batch's loads first (elements without a source
-                // load the source's first quad, a valid address, and are
-                // zeroed afterwards): with a conditional load and the fold
-                // right behind each, they would go out one at a time
-                f4 v[NU];
-                int d[NU];
-                bool z[NU];
-#pragma unroll
-                for (int u = 0; u < NU; ++u) {
-                    const float* sp;
-                    decode(base + u * 256, sp, d[u]);
-                    z[u] = !sp;
-                    v[u] = ld_global4((sp ? sp : src + q * 4) + c0);
-                }
-#pragma unroll
-                for (int u = 0; u < NU; ++u) {
-                    if (z[u]) v[u] = f4{0.f, 0.f, 0.f, 0.f};
-                    else if (INBN && base + u * 256 < nx) v[u] = fold(v[u], c0 + q * 4);
-                }
-#pragma unroll
-                for (int u = 0; u < NU; ++u)
-                    if (d[u] >= 0) *(f4*)(lds + d[u]) = v[u];
-            }
-            __syncthreads();
-            compute();
-            __syncthreads();
-        }
+        lds_barrier();
     }
 
-    const long m0 = (long)blockIdx.x * TP;      // tiles are consecutive runs of the NHWC rows
-    const int pix_base = wm * TM * 16;
-    const int n_base = n0 + wn * TN * 16;
-    f4 bs0 = f4{0.f, 0.f, 0.f, 0.f}, bs1 = bs0;   // data gradient with STATS: sum gm, sum gm*xhat
     if (bias) {
 #pragma unroll
         for (int y = 0; y < TN; ++y) {
-            const int n = n_base + y * 16 + li;
+            const int n = n0 + y * 16 + li;
             const float bb = n < g.Ncols ? bias[n] : 0.f;
 #pragma unroll
             for (int x = 0; x < TM; ++x)
@@ -571,9 +642,9 @@ void conv_tile_f32(const float* __restrict__ src, const float* __restrict__ B,
                 for (int i = 0; i < 4; ++i) acc[x][y][i] += bb;
         }
     }
-    // the wave's TM*16 x TN*16 output block, transposed through LDS (the
-    // X/W tiles are dead) so that every lane stores whole float4 channel
-    // quads of one pixel
+    // the wave's TM*16 x TN*16 output block, transposed through LDS so that
+    // every lane stores whole float4 channel quads of one pixel
+    f4 bs0 = f4{0.f, 0.f, 0.f, 0.f}, bs1 = bs0;   // data gradient with STATS: sum gm, sum gm*xhat
     {
         constexpr int OP = TN * 16 + 4;           // LDS pitch of a pixel row
         float* Ot = lds + wave * (TM * 16 * OP);
@@ -585,32 +656,28 @@ void conv_tile_f32(const float* __restrict__ src, const float* __restrict__ B,
                 for (int i = 0; i < 4; ++i) Ot[(x * 16 + gi * 4 + i) * OP + y * 16 + li] = acc[x][y][i];
         __builtin_amdgcn_wave_barrier();          // a wave's LDS accesses execute in order
         constexpr int QPP = TN * 4;               // float4 quads per pixel of the block
-        // data gradient with STATS: this lane's channel quad is fixed (64 %
-        // QPP == 0); its BN's mean, rstd, scale and shift
+        const int qd = lane % QPP, n = n0 + qd * 4;   // (64 % QPP == 0: a lane keeps one channel quad)
         f4 bmu{}, brs{}, bsc{}, bsh{};
-        if (MODE == CONV_DGRAD && STATS) {
-            const int n = n_base + (lane % QPP) * 4;
-            if (n < g.Ncols) {
-                bmu = *(const f4*)(bs.aux + n);
-                brs = *(const f4*)(bs.aux + g.Ncols + n);
-                bsc = *(const f4*)(bs.aux + 2 * g.Ncols + n);
-                bsh = *(const f4*)(bs.aux + 3 * g.Ncols + n);
-            }
+        if (MODE == CONV_DGRAD && STATS && n < g.Ncols) {
+            bmu = *(const f4*)(bs.aux + n);
+            brs = *(const f4*)(bs.aux + g.Ncols + n);
+            bsc = *(const f4*)(bs.aux + 2 * g.Ncols + n);
+            bsh = *(const f4*)(bs.aux + 3 * g.Ncols + n);
         }
 #pragma unroll
         for (int k = 0; k < TM * 16 * QPP / 64; ++k) {
-            const int e = k * 64 + lane;
-            const int p = e / QPP, qd = e - (e / QPP) * QPP;
-            const int n = n_base + qd * 4;
-            if (n < g.Ncols) {
-                const f4 v = *(const f4*)(Ot + p * OP + qd * 4);
-                f4* o = (f4*)(Y + (m0 + pix_base + p) * g.Ncols + n);
+            const int pl = (k * 64 + lane) / QPP;
+            const int p = wave * TM * 16 + pl;
+            const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+            if (oh < ohv && ow < owv && n < g.Ncols) {
+                const long e = ((long)(R0 + oh) * t.Wo + w0 + ow) * g.Ncols + n;
+                const f4 v = *(const f4*)(Ot + pl * OP + qd * 4);
+                f4* o = (f4*)(Y + e);
                 const f4 tot = accumulate == kStoreAdd ? *o + v : (accumulate == kStoreRelu ? relu4(v) : v);
                 *o = tot;
                 if (MODE == CONV_DGRAD && STATS) {
                     // gm = the stored gradient where the forward's ReLU passed
                     // (its output y > 0, or fma(x, scale, shift) > 0), xhat of the BN input
-                    const long e = (m0 + pix_base + p) * g.Ncols + n;
                     const f4 x = *(const f4*)(bs.x1 + e);
                     const f4 yv = bs.y ? *(const f4*)(bs.y + e) : f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -625,10 +692,8 @@ void conv_tile_f32(const float* __restrict__ src, const float* __restrict__ B,
         }
     }
     if constexpr (MODE == CONV_DGRAD && STATS) {
-        // lanes of one channel quad (lane mod QPP) summed by a fixed xor tree,
-        // then the WM waves of this channel block in order
+        // lanes of one channel quad summed by a fixed xor tree, then the four waves in order
         constexpr int QPP = TN * 4;
-        static_assert(64 % QPP == 0, "a lane keeps one channel quad");
 #pragma unroll
         for (int o = QPP; o < 64; o <<= 1) {
 #pragma unroll
@@ -643,111 +708,98 @@ void conv_tile_f32(const float* __restrict__ src, const float* __restrict__ B,
             bred[wave][1][lane] = bs1;
         }
         __syncthreads();
-        if (threadIdx.x < WN * QPP) {
-            const int wnb = threadIdx.x / QPP, qd = threadIdx.x - wnb * QPP;
-            f4 t0 = bred[wnb * WM][0][qd], t1 = bred[wnb * WM][1][qd];
-            for (int w = 1; w < WM; ++w) {
-                t0 += bred[wnb * WM + w][0][qd];
-                t1 += bred[wnb * WM + w][1][qd];
-            }
-            const int nb = n0 + wnb * TN * 16 + qd * 4;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = nb + j;
-                if (c >= g.Ncols) continue;
-                if (sums.acc) {
-                    acc_add(sums.acc, 0, (int)blockIdx.x, g.Ncols, c, (double)t0[j]);
-                    acc_add(sums.acc, 1, (int)blockIdx.x, g.Ncols, c, (double)t1[j]);
-                } else {
-                    sums.p0[(long)blockIdx.x * g.Ncols + c] = t0[j];
-                    sums.p1[(long)blockIdx.x * g.Ncols + c] = t1[j];
-                }
+        if (tid < 2 * BN) {
+            const int k = tid / BN, cl = tid - k * BN, c = n0 + cl;
+            float s = bred[0][k][cl >> 2][cl & 3];
+            for (int w = 1; w < 4; ++w) s += bred[w][k][cl >> 2][cl & 3];
+            if (c < g.Ncols) {
+                if (sums.acc) acc_add(sums.acc, k, (int)blockIdx.x, g.Ncols, c, (double)s);
+                else (k ? sums.p1 : sums.p0)[(long)blockIdx.x * g.Ncols + c] = s;
             }
         }
     }
     if constexpr (MODE == CONV_FWD && STATS) {
-        // (every pixel of a tile lies inside the tensor)
-        __shared__ float red[WM][3][BN];
-        tile_moments<TM, TN, WM, BN, true>(
-            acc, wm, wn, [](int, int) { return true; }, red,
-            [&](int t, float n, float mu, float m2) {
-                if (n0 + t < g.Ncols) tile_moments_store(sums, (int)blockIdx.x, g.Ncols, n0 + t, n, mu, m2);
-            });
+        __shared__ float red[4][3][BN];
+        const auto store = [&](int c, float n, float mu, float m2) {
+            if (n0 + c < g.Ncols) tile_moments_store(sums, (int)blockIdx.x, g.Ncols, n0 + c, n, mu, m2);
+        };
+        if (ohv * owv == TM * 64) {
+            tile_moments<TM, TN, 4, BN, true>(acc, wave, 0, [](int, int) { return true; }, red, store);
+        } else {
+            // slots of this lane's accumulator rows that hold a pixel
+            unsigned ok = 0;
+#pragma unroll
+            for (int x = 0; x < TM; ++x)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int p = (wave * TM + x) * 16 + gi * 4 + i;
+                    const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+                    if (oh < ohv && ow < owv) ok |= 1u << (x * 4 + i);
+                }
+            tile_moments<TM, TN, 4, BN, false>(
+                acc, wave, 0, [&](int x, int i) { return ((ok >> (x * 4 + i)) & 1) != 0; }, red, store);
+        }
     }
 }
 
-// Picks (WM, TM, TN) and the tile rows OH for the spatial kernel, or returns
-// false when no shape fits (the GEMM-style kernels take those passes).
-struct TileCfg { int wm, tm, tn; TileGeom t; size_t lds; };
+struct TileCfg { int tm, tn, tiles; BoxGeom t; size_t lds; };
+
+// Box and channel tile of a pass, or false when the spatial kernel does not
+// take it (the GEMM-style kernels do).
 static bool pick_tile(int mode, const ConvGeom& g, TileCfg& out) {
-    if (g.Cs % 16 != 0 || g.Ncols % 4 != 0) return false;
-    if (!((g.R == 3 && g.S == 3) || (g.R == 1 && g.S == 1))) return false;
+    if (g.Cs % 4 || g.Cs < 16 || g.Ncols % 4 || g.R != g.S || (g.R != 1 && g.R != 3)) return false;
     if (mode == CONV_DGRAD && g.stride != 1) return false;
-    static const int cands[][3] = {
-        // wm, tm, tn  (tile pixels = wm*tm*16, output channels = (4/wm)*tn*16)
-        {4, 4, 1}, {4, 2, 1}, {2, 4, 1}, {2, 2, 1}, {1, 4, 1}, {2, 2, 2}, {1, 4, 2}, {4, 1, 1}, {2, 1, 1}, {1, 2, 1},
-        {1, 1, 1}};
-    const long M = (long)g.Nb * g.Ho * g.Wo;
-    // first choice: four waves along the pixels, 16 output channels, and a
-    // tile of 8 output rows (4 for strided passes) -- measured fastest at
-    // ResNet-20's shapes (32x32, 16x16 and 8x8 outputs)
-    int pref[3] = {0, 0, 0};
-    const int prow = g.stride == 1 ? 8 : 4;
-    if ((prow * g.Wo) % 64 == 0) {
-        const int tm = prow * g.Wo / 64;
-        if (tm == 1 || tm == 2 || tm == 4) pref[0] = 4, pref[1] = tm, pref[2] = 1;
+    if (!buf_fits((double)g.Nb * g.Hs * g.Ws * g.Cs) || !buf_fits((double)g.Ncols * g.R * g.R * g.Cs)) return false;
+    static const int shapes[][2] = {{2, 2}, {2, 1}, {1, 1}};
+    bool found = false;
+    for (auto& sh : shapes) {
+        const int tm = sh[0], tn = sh[1], bn = tn * 16;
+        if (tn == 2 && (g.R != 1 || g.Ncols % 32)) continue;
+        TileCfg c;
+        if (!box_pick(c.t, g.Nb, g.Ho, g.Wo, g.R, g.R == 1 ? 1 : g.stride, mode == CONV_FWD ? g.pad : g.R - 1 - g.pad,
+                      tm * 64, 1, kTileBatches))
+            continue;
+        c.tm = tm;
+        c.tn = tn;
+        c.tiles = box_tiles(c.t);
+        // the staged tiles; the epilogue's transpose reuses the space
+        c.lds = sizeof(float) * std::max<size_t>(20 * ((size_t)c.t.IH * c.t.IW + (size_t)bn * g.R * g.R),
+                                                 (size_t)4 * tm * 16 * (bn + 4));
+        found = true;
+        out = c;
+        if ((long)c.tiles * ((g.Ncols + bn - 1) / bn) >= 512) break;
     }
-    for (int ci = -1; ci < (int)(sizeof(cands) / sizeof(cands[0])); ++ci) {
-        const int* c = ci < 0 ? pref : cands[ci];
-        if (!c[0]) continue;
-        const int wm = c[0], tm = c[1], tn = c[2];
-        const int tp = wm * tm * 16, bn = (4 / wm) * tn * 16;
-        if (bn > 16 && g.Ncols <= bn / 2) continue;             // output width too small for this tile
-        if (g.Ncols > 16 && bn == 16 && g.Ncols % 32 == 0 && wm != 4) continue;
-        if (tp % g.Wo) continue;
-        const int oh = tp / g.Wo;
-        if (oh < 1 || g.Ho % oh) continue;
-        const int pad_eff = mode == CONV_FWD ? g.pad : g.R - 1 - g.pad;
-        const int ih = (oh - 1) * g.stride + g.R, iw = (g.Wo - 1) * g.stride + g.S;
-        // staged X and W tiles; the epilogue's transpose reuses the space
-        const size_t lds = sizeof(float) * std::max<size_t>(20 * ((size_t)ih * iw + (size_t)bn * g.R * g.S),
-                                                            (size_t)4 * tm * 16 * (tn * 16 + 4));
-        if (lds > 60 * 1024) continue;   // leaves room for the static statistics arrays
-        const long tiles = M / tp;
-        if (tiles * ((g.Ncols + bn - 1) / bn) < 128) continue;
-        const unsigned inv = (unsigned)((0x100000000ull + iw - 1) / iw);
-        out = {wm, tm, tn, {oh, ih, iw, pad_eff, g.Ho / oh, inv}, lds};
-        return true;
-    }
-    return false;
+    return found;
 }
 
-template <int MODE, int KS, int WM, int TM, int TN>
+template <int MODE, int KS, int TM, int TN>
 static hipError_t launch_tile(const float* src, const float* B, const float* bias, float* Y, const ConvGeom& g,
                               const TileCfg& c, int acc, const BnSums* stats, const BnFwd* inbn,
                               const BnBwdSum* bsv, hipStream_t st) {
-    constexpr int BN = (4 / WM) * TN * 16;
-    dim3 grid((unsigned)(g.Nb * c.t.tiles_per_img), (unsigned)((g.Ncols + BN - 1) / BN));
+    dim3 grid((unsigned)c.tiles, (unsigned)((g.Ncols + TN * 16 - 1) / (TN * 16)));
     const BnSums sm = stats ? *stats : BnSums{};
     const BnFwd ib = inbn ? *inbn : BnFwd{};
     const BnBwdSum bsum = bsv ? *bsv : BnBwdSum{};
     // a data gradient's statistics are the sums of a BN backward (bsv)
     if (MODE == CONV_DGRAD && stats && (!bsv || (acc && !bsv->y))) return hipErrorInvalidValue;
-    if (inbn) {
-        if (MODE != CONV_FWD || g.Cs > kFoldMaxC) return hipErrorInvalidValue;
-        if (stats)
-            launch((conv_tile_f32<MODE, KS, WM, TM, TN, true, true>), grid, dim3(256), c.lds, st, src, B, bias, Y, g,
-                   c.t, (int)acc, sm, ib, bsum);
-        else
-            launch((conv_tile_f32<MODE, KS, WM, TM, TN, false, true>), grid, dim3(256), c.lds, st, src, B, bias, Y, g,
-                   c.t, (int)acc, sm, ib, bsum);
-    } else if (stats) {
-        launch((conv_tile_f32<MODE, KS, WM, TM, TN, true, false>), grid, dim3(256), c.lds, st, src, B, bias, Y, g,
-               c.t, (int)acc, sm, ib, bsum);
-    } else {
-        launch((conv_tile_f32<MODE, KS, WM, TM, TN, false, false>), grid, dim3(256), c.lds, st, src, B, bias, Y, g,
-               c.t, (int)acc, sm, ib, bsum);
+    if (inbn && (MODE != CONV_FWD || g.Cs > kFoldMaxC)) return hipErrorInvalidValue;
+    if constexpr (MODE == CONV_FWD) {
+        if (inbn) {
+            if (stats)
+                launch((conv_tile_f32<MODE, KS, TM, TN, true, true>), grid, dim3(256), c.lds, st, src, B, bias, Y, g,
+                       c.t, acc, sm, ib, bsum);
+            else
+                launch((conv_tile_f32<MODE, KS, TM, TN, false, true>), grid, dim3(256), c.lds, st, src, B, bias, Y, g,
+                       c.t, acc, sm, ib, bsum);
+            return hipGetLastError();
+        }
     }
+    if (stats)
+        launch((conv_tile_f32<MODE, KS, TM, TN, true, false>), grid, dim3(256), c.lds, st, src, B, bias, Y, g, c.t,
+               acc, sm, ib, bsum);
+    else
+        launch((conv_tile_f32<MODE, KS, TM, TN, false, false>), grid, dim3(256), c.lds, st, src, B, bias, Y, g, c.t,
+               acc, sm, ib, bsum);
     return hipGetLastError();
 }
 
@@ -755,15 +807,13 @@ template <int MODE>
 static hipError_t dispatch_tile(const float* src, const float* B, const float* bias, float* Y, const ConvGeom& g,
                                 const TileCfg& c, int acc, const BnSums* stats, const BnFwd* inbn,
                                 const BnBwdSum* bsv, hipStream_t st) {
-#define TILE(WM_, TM_, TN_)                                                                                        \
-    if (c.wm == WM_ && c.tm == TM_ && c.tn == TN_) {                                                               \
-        if (g.R == 3) return launch_tile<MODE, 3, WM_, TM_, TN_>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st); \
-        return launch_tile<MODE, 1, WM_, TM_, TN_>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);               \
+    if (g.R == 3) {
+        if (c.tm == 2) return launch_tile<MODE, 3, 2, 1>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);
+        return launch_tile<MODE, 3, 1, 1>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);
     }
-    TILE(4, 4, 1) TILE(4, 2, 1) TILE(2, 4, 1) TILE(2, 2, 1) TILE(1, 4, 1) TILE(2, 2, 2) TILE(1, 4, 2)
-    TILE(4, 1, 1) TILE(2, 1, 1) TILE(1, 2, 1) TILE(1, 1, 1)
-#undef TILE
-    return hipErrorInvalidValue;
+    if (c.tn == 2) return launch_tile<MODE, 1, 2, 2>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);
+    if (c.tm == 2) return launch_tile<MODE, 1, 2, 1>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);
+    return launch_tile<MODE, 1, 1, 1>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);
 }
 
 // Data gradient of a stride-2 conv, split by output parity.  dX pixel
@@ -771,70 +821,86 @@ static hipError_t dispatch_tile(const float* src, const float* B, const float* b
 // even, from dY[i + (a + pad - r)/2][j + (b + pad - s)/2]: per parity class
 // (a, b) this is a dense stride-1 correlation over dY with a subset of the
 // taps (3x3, pad 1: 1, 2, 2 and 4 taps; 1x1, pad 0: one tap, class (0, 0)).
-// A workgroup takes OH class rows of one image for all four classes (a dX
-// tile of 2 OH rows), so every workgroup runs all R*S taps once and the dY
-// rows it reads are staged in LDS once per 16 dY channels; no MFMA is spent
-// on taps that fall between strides.  The finished tile is transposed
-// through LDS and stored as float4 channel quads.
-struct S2Geom { int OH, IH, IW, Hc, Wc, tiles_per_img, dr0, ds0; unsigned IW_inv; };
-
-template <int KS, int PAD, int WM, int TM, int TN>
+// A workgroup takes a box of class pixels (i, j) for all four classes, so
+// every workgroup runs all taps once, the dY rows it reads are staged in LDS
+// once per 16 dY channels, and no MFMA is spent on taps that fall between
+// strides; odd grids leave out the last class row or column at the store.
+// (The GEMM kernel that odd and non-power-of-two grids ran on spends four
+// MFMAs where one counts: 16 x 28x28x128 -> 56x56x64 took 127 us, 100 x
+// 14x14x32 -> 28x28x16 42 us.)
+template <int KS, int PAD, int TM>
 __global__ __launch_bounds__(256) void conv_dgrad_s2_f32(const float* __restrict__ dY, const float* __restrict__ B,
-                                                         float* __restrict__ dX, ConvGeom g, S2Geom t,
+                                                         float* __restrict__ dX, ConvGeom g, BoxGeom t,
                                                          int accumulate) {
-    constexpr int WN = 4 / WM;
-    constexpr int TP = WM * TM * 16, BN = WN * TN * 16;
-    constexpr int LDW = 20;
-    constexpr int RS = KS * KS;
-    constexpr int NU = 8;
+    constexpr int TP = TM * 64, LDW = 20, RS = KS * KS;
+    constexpr int NW = (16 * RS * 4 + 255) / 256;
     extern __shared__ float lds[];
-    float* Xs = lds;                              // [IH*IW][LDW] dY rows
-    float* Ws = lds + t.IH * t.IW * LDW;          // [BN][RS][LDW]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WM, wn = wave / WM;
-    const int gi = lane >> 4, li = lane & 15;
-    const int img = blockIdx.x / t.tiles_per_img;
-    const int i0 = (blockIdx.x - img * t.tiles_per_img) * t.OH;
-    const int n0 = blockIdx.y * BN;
-    const int h_org = i0 + t.dr0, w_org = t.ds0;
+    const int gi = lane >> 4, li = lane & 15, q = tid & 3;
+    const int tr = box_div((int)blockIdx.x, t.nc_inv), tc = (int)blockIdx.x - tr * t.nc;
+    const int R0 = tr * t.OH, w0 = tc * t.OW;
+    const int ohv = min(t.OH, t.rows - R0), owv = min(t.OW, t.Wo - w0);
+    const int n0 = blockIdx.y * 16;
+    const int P0 = box_prow(t, R0);
+    const int nx = t.IH * t.IW * 4, nxu = (nx + 255) >> 8;
+    float* Xs = lds;                              // [IH * IW][LDW] dY rows
+    float* Ws = lds + t.IH * t.IW * LDW;          // [16][RS][LDW]
 
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(dY, (long)g.Nb * g.Hs * g.Ws * g.Cs);
+    const __amdgpu_buffer_rsrc_t wr = buf_rsrc(B, (long)g.Ncols * RS * g.Cs);
+    unsigned xo[kTileBatches], wo[NW];
+#pragma unroll
+    for (int u = 0; u < kTileBatches; ++u) {
+        xo[u] = kNoLoad;
+        if (u < nxu) {
+            const int pix = (tid + u * 256) >> 2;
+            const int ih = box_div(pix, t.IW_inv), iw = pix - ih * t.IW;
+            const int pr = P0 + ih;
+            const int n = box_div(pr, t.Hp_inv), h = pr - n * t.Hp, w = w0 + iw;
+            if (ih < t.IH && n < g.Nb && h < g.Hs && w < g.Ws)
+                xo[u] = (unsigned)(((n * g.Hs + h) * g.Ws + w) * g.Cs + q * 4) * 4u;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+        const int rest = (tid + u * 256) >> 2;    // (channel, tap)
+        wo[u] = (rest < 16 * RS && n0 + rest / RS < g.Ncols) ? (unsigned)((n0 * RS + rest) * g.Cs + q * 4) * 4u
+                                                            : kNoLoad;
+    }
+    f4 xv[kTileBatches], wv[NW];
+    auto load = [&](int c0) {
+        const unsigned bad = c0 + q * 4 < g.Cs ? 0u : kNoLoad;
+#pragma unroll
+        for (int u = 0; u < kTileBatches; ++u)
+            if (u < nxu) xv[u] = buf_load4(xr, xo[u] | bad, c0 * 4);
+#pragma unroll
+        for (int u = 0; u < NW; ++u) wv[u] = buf_load4(wr, wo[u] | bad, c0 * 4);
+    };
+    load(0);
     int abase[TM];
 #pragma unroll
     for (int x = 0; x < TM; ++x) {
-        const int p = (wm * TM + x) * 16 + li;
-        const int oh = p / t.Wc, ow = p - (p / t.Wc) * t.Wc;
-        abase[x] = (oh * t.IW + ow) * LDW + gi * 4;
+        const int p = (wave * TM + x) * 16 + li;
+        const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+        const bool ok = oh < ohv && ow < owv;
+        abase[x] = ((ok ? box_prow(t, R0 + oh) - P0 : 0) * t.IW + (ok ? ow : 0)) * LDW + gi * 4;
     }
-    f4 acc[4][TM][TN];
+    f4 acc[4][TM];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[c][i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < TM; ++i) acc[c][i] = f4{0.f, 0.f, 0.f, 0.f};
 
-    const int q = tid & 3;
-    const int nx = t.IH * t.IW * 4, ntot = nx + BN * RS * 4;
-    auto decode = [&](int e, const float*& sp, int& d) {
-        sp = nullptr;
-        d = -1;
-        if (e < nx) {
-            const int pix = e >> 2;
-            const int ih = (int)__umulhi((unsigned)pix, t.IW_inv);
-            const int iw = pix - ih * t.IW;
-            const int h = h_org + ih, w = w_org + iw;
-            if (h >= 0 && h < g.Hs && w >= 0 && w < g.Ws)
-                sp = dY + ((long)(img * g.Hs + h) * g.Ws + w) * g.Cs + q * 4;
-            d = pix * LDW + q * 4;
-        } else if (e < ntot) {
-            const int rest = (e - nx) >> 2;
-            const int tap = rest % RS, nl = rest / RS;
-            const int n = n0 + nl;
-            if (n < g.Ncols) sp = B + ((long)n * RS + tap) * g.Cs + q * 4;
-            d = t.IH * t.IW * LDW + rest * LDW + q * 4;
-        }
-    };
-    auto compute = [&]() {
+    const int sdst = (tid >> 2) * LDW + q * 4;
+    for (int c0 = 0; c0 < g.Cs; c0 += 16) {
+#pragma unroll
+        for (int u = 0; u < kTileBatches; ++u)
+            if (u < nxu && tid + u * 256 < nx) *(f4*)(Xs + sdst + u * 64 * LDW) = xv[u];
+#pragma unroll
+        for (int u = 0; u < NW; ++u)
+            if (tid + u * 256 < 16 * RS * 4) *(f4*)(Ws + sdst + u * 64 * LDW) = wv[u];
+        lds_barrier();
+        if (c0 + 16 < g.Cs) load(c0 + 16);
 #pragma unroll
         for (int cls = 0; cls < 4; ++cls) {
             const int ca = cls >> 1, cb = cls & 1;
@@ -844,156 +910,82 @@ __global__ __launch_bounds__(256) void conv_dgrad_s2_f32(const float* __restrict
                 for (int sx = 0; sx < KS; ++sx) {
                     if (((ca + PAD - r) & 1) || ((cb + PAD - sx) & 1)) continue;
                     // source row i + (a + pad - r)/2, column j + (b + pad - s)/2
-                    const int dr = (ca + PAD - r) / 2 - t.dr0, ds = (cb + PAD - sx) / 2 - t.ds0;
-                    const int toff = (dr * t.IW + ds) * LDW;
-                    const int tap = r * KS + sx;
-                    f4 av[TM], bv[TN];
+                    const int toff = ((ca + PAD - r) / 2 * t.IW + (cb + PAD - sx) / 2) * LDW;
+                    const f4 bv = *(const f4*)(Ws + (li * RS + r * KS + sx) * LDW + gi * 4);
+                    f4 av[TM];
 #pragma unroll
                     for (int x = 0; x < TM; ++x) av[x] = *(const f4*)(Xs + abase[x] + toff);
 #pragma unroll
-                    for (int y = 0; y < TN; ++y)
-                        bv[y] = *(const f4*)(Ws + (((wn * TN + y) * 16 + li) * RS + tap) * LDW + gi * 4);
-#pragma unroll
                     for (int j = 0; j < 4; ++j)
 #pragma unroll
-                        for (int x = 0; x < TM; ++x)
-#pragma unroll
-                            for (int y = 0; y < TN; ++y)
-                                acc[cls][x][y] = mfma16x16x4(av[x][j], bv[y][j], acc[cls][x][y]);
+                        for (int x = 0; x < TM; ++x) acc[cls][x] = mfma16x16x4(av[x][j], bv[j], acc[cls][x]);
                 }
         }
-    };
-    const int ngroups = g.Cs >> 4;
-    if (ntot <= NU * 256) {
-        const float* sp[NU];
-        int d[NU];
-        f4 v[NU];
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            decode(tid + u * 256, sp[u], d[u]);
-            v[u] = sp[u] ? *(const f4*)sp[u] : f4{0.f, 0.f, 0.f, 0.f};
-        }
-        for (int cgp = 0; cgp < ngroups; ++cgp) {
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-                if (d[u] >= 0) *(f4*)(lds + d[u]) = v[u];
-            __syncthreads();
-            if (cgp + 1 < ngroups) {
-                const int c1 = (cgp + 1) * 16;
-#pragma unroll
-                for (int u = 0; u < NU; ++u) v[u] = sp[u] ? *(const f4*)(sp[u] + c1) : f4{0.f, 0.f, 0.f, 0.f};
-            }
-            compute();
-            __syncthreads();
-        }
-    } else {
-        for (int cgp = 0; cgp < ngroups; ++cgp) {
-            const int c0 = cgp * 16;
-            for (int base = tid; base < ntot; base += NU * 256) {
-                f4 v[NU];
-                int d[NU];
-#pragma unroll
-                for (int u = 0; u < NU; ++u) {
-                    const float* sp;
-                    decode(base + u * 256, sp, d[u]);
-                    v[u] = sp ? *(const f4*)(sp + c0) : f4{0.f, 0.f, 0.f, 0.f};
-                }
-#pragma unroll
-                for (int u = 0; u < NU; ++u)
-                    if (d[u] >= 0) *(f4*)(lds + d[u]) = v[u];
-            }
-            __syncthreads();
-            compute();
-            __syncthreads();
-        }
+        lds_barrier();
     }
 
-    // the dX tile (2 OH rows x 2 Wc columns x BN channels) in LDS, pixel-major
-    constexpr int OP = BN + 4;
-    const int tw = 2 * t.Wc;
+    // the four classes' pixels in LDS, then stored as float4 channel quads in
+    // the order of dX's columns
+    constexpr int OP = 20;
 #pragma unroll
     for (int cls = 0; cls < 4; ++cls)
 #pragma unroll
         for (int x = 0; x < TM; ++x)
 #pragma unroll
-            for (int y = 0; y < TN; ++y)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int p = (wm * TM + x) * 16 + gi * 4 + i;
-                    const int oh = p / t.Wc, ow = p - (p / t.Wc) * t.Wc;
-                    const int tp = (2 * oh + (cls >> 1)) * tw + 2 * ow + (cls & 1);
-                    lds[tp * OP + (wn * TN + y) * 16 + li] = acc[cls][x][y][i];
-                }
+            for (int i = 0; i < 4; ++i)
+                lds[(cls * TP + (wave * TM + x) * 16 + gi * 4 + i) * OP + li] = acc[cls][x][i];
     __syncthreads();
-    constexpr int QPP = BN / 4;
-    for (int e = tid; e < 4 * TP * QPP; e += 256) {
-        const int tp = e / QPP, qd = e - (e / QPP) * QPP;
-        const int n = n0 + qd * 4;
-        if (n >= g.Ncols) continue;
-        const int hr = tp / tw, wc = tp - (tp / tw) * tw;
-        const f4 v = *(const f4*)(lds + tp * OP + qd * 4);
-        f4* o = (f4*)(dX + ((long)(img * g.Ho + 2 * i0 + hr) * g.Wo + wc) * g.Ncols + n);
+    const int n = n0 + q * 4;
+    if (n >= g.Ncols) return;
+#pragma unroll 4
+    for (int e = tid >> 2; e < 4 * TP; e += 64) {
+        const int b = e & 1, p = (e >> 1) & (TP - 1), a = e / (2 * TP);
+        const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+        if (oh >= ohv || ow >= owv) continue;
+        const int im = box_div(R0 + oh, t.Hper_inv);
+        const int hr = 2 * (R0 + oh - im * t.Hper) + a, wc = 2 * (w0 + ow) + b;
+        if (hr >= g.Ho || wc >= g.Wo) continue;
+        const f4 v = *(const f4*)(lds + ((2 * a + b) * TP + p) * OP + q * 4);
+        f4* o = (f4*)(dX + ((long)(im * g.Ho + hr) * g.Wo + wc) * g.Ncols + n);
         *o = accumulate == kStoreAdd ? *o + v : (accumulate == kStoreRelu ? relu4(v) : v);
     }
 }
 
-// Tile shape of the parity-split stride-2 data gradient, or false when it
-// does not apply.
-struct S2Cfg { int wm, tm, tn; S2Geom t; size_t lds; };
+// Box of the parity-split stride-2 data gradient, or false when it does not
+// apply.
+struct S2Cfg { int tm, tiles; BoxGeom t; size_t lds; };
 static bool pick_s2(const ConvGeom& g, S2Cfg& out) {
-    if (g.stride != 2 || g.Cs % 16 || g.Ncols % 4 || (g.Ho & 1) || (g.Wo & 1)) return false;
+    if (g.stride != 2 || g.Cs % 4 || g.Ncols % 4) return false;
     if (!((g.R == 3 && g.S == 3 && g.pad == 1) || (g.R == 1 && g.S == 1 && g.pad == 0))) return false;
-    const int Hc = g.Ho / 2, Wc = g.Wo / 2;
-    // source offsets (a + pad - r)/2 over every class and tap
-    int dr0 = 1 << 20, dr1 = -(1 << 20);
-    for (int a = 0; a < 2; ++a)
-        for (int r = 0; r < g.R; ++r)
-            if (((a + g.pad - r) & 1) == 0) {
-                dr0 = std::min(dr0, (a + g.pad - r) / 2);
-                dr1 = std::max(dr1, (a + g.pad - r) / 2);
-            }
-    static const int cands[][3] = {{4, 4, 1}, {4, 2, 1}, {4, 1, 1}, {2, 2, 1}, {2, 1, 1}, {1, 1, 1}};
-    for (int pass = 0; pass < 2; ++pass)
-        for (auto& c : cands) {
-            const int wm = c[0], tm = c[1], tn = c[2];
-            const int tp = wm * tm * 16, bn = (4 / wm) * tn * 16;
-            if (bn > 16 && g.Ncols <= bn / 2) continue;
-            if (tp % Wc) continue;
-            const int oh = tp / Wc;
-            if (oh < 1 || Hc % oh) continue;
-            const long wgs = (long)g.Nb * (Hc / oh) * ((g.Ncols + bn - 1) / bn);
-            if (pass == 0 && wgs < 256) continue;     // first look for shapes that fill the chip
-            const int ih = oh + dr1 - dr0, iw = Wc + dr1 - dr0;
-            const size_t lds = sizeof(float) * std::max<size_t>(20 * ((size_t)ih * iw + (size_t)bn * g.R * g.S),
-                                                                (size_t)4 * tp * (bn + 4));
-            if (lds > 60 * 1024) continue;
-            const unsigned inv = (unsigned)((0x100000000ull + iw - 1) / iw);
-            out = {wm, tm, tn, {oh, ih, iw, Hc, Wc, Hc / oh, dr0, dr0, inv}, lds};
-            return true;
-        }
-    return false;
-}
-
-template <int KS, int PAD, int WM, int TM, int TN>
-static hipError_t launch_s2(const float* dY, const float* B, float* dX, const ConvGeom& g, const S2Cfg& c, int acc,
-                            hipStream_t st) {
-    constexpr int BN = (4 / WM) * TN * 16;
-    dim3 grid((unsigned)(g.Nb * c.t.tiles_per_img), (unsigned)((g.Ncols + BN - 1) / BN));
-    launch((conv_dgrad_s2_f32<KS, PAD, WM, TM, TN>), grid, dim3(256), c.lds, st, dY, B, dX, g, c.t,
-                       (int)acc);
-    return hipGetLastError();
+    if (!buf_fits((double)g.Nb * g.Hs * g.Ws * g.Cs) || !buf_fits((double)g.Ncols * g.R * g.R * g.Cs)) return false;
+    const int ext = g.R == 3 ? 2 : 1;   // dY rows i, i + 1 (3x3) or i
+    bool found = false;
+    for (int tm : {2, 1}) {
+        S2Cfg c;
+        if (!box_pick(c.t, g.Nb, (g.Ho + 1) / 2, (g.Wo + 1) / 2, ext, 1, 0, tm * 64, 1, kTileBatches)) continue;
+        c.tm = tm;
+        c.tiles = box_tiles(c.t);
+        c.lds = sizeof(float) * std::max<size_t>(20 * ((size_t)c.t.IH * c.t.IW + (size_t)16 * g.R * g.R),
+                                                 (size_t)4 * tm * 64 * 20);
+        found = true;
+        out = c;
+        if ((long)c.tiles * ((g.Ncols + 15) / 16) >= 512) break;
+    }
+    return found;
 }
 
 static hipError_t dispatch_s2(const float* dY, const float* B, float* dX, const ConvGeom& g, const S2Cfg& c, int acc,
                               hipStream_t st) {
-#define S2(WM_, TM_, TN_)                                                                              \
-    if (c.wm == WM_ && c.tm == TM_ && c.tn == TN_) {                                                   \
-        if (g.R == 3) return launch_s2<3, 1, WM_, TM_, TN_>(dY, B, dX, g, c, acc, st);                 \
-        return launch_s2<1, 0, WM_, TM_, TN_>(dY, B, dX, g, c, acc, st);                               \
-    }
-    S2(4, 4, 1) S2(4, 2, 1) S2(4, 1, 1) S2(2, 2, 1) S2(2, 1, 1) S2(1, 1, 1)
-#undef S2
-    return hipErrorInvalidValue;
+    dim3 grid((unsigned)c.tiles, (unsigned)((g.Ncols + 15) / 16));
+    if (g.R == 3 && c.tm == 2)
+        launch((conv_dgrad_s2_f32<3, 1, 2>), grid, dim3(256), c.lds, st, dY, B, dX, g, c.t, acc);
+    else if (g.R == 3)
+        launch((conv_dgrad_s2_f32<3, 1, 1>), grid, dim3(256), c.lds, st, dY, B, dX, g, c.t, acc);
+    else if (c.tm == 2)
+        launch((conv_dgrad_s2_f32<1, 0, 2>), grid, dim3(256), c.lds, st, dY, B, dX, g, c.t, acc);
+    else
+        launch((conv_dgrad_s2_f32<1, 0, 1>), grid, dim3(256), c.lds, st, dY, B, dX, g, c.t, acc);
+    return hipGetLastError();
 }
 
 template <int MODE, int WM, int TM, int TN>
@@ -1074,10 +1066,10 @@ static hipError_t launch_mode(const float* src, const float* B, const float* bia
     return launch_cfg<MODE, 2, 1, 2>(src, B, bias, Y, g, acc, stats, st);
 }
 
-int conv_tile_rows(const ConvGeom& g) {
-    TileCfg t;
-    if (pick_tile(CONV_FWD, g, t)) return t.wm * t.tm * 16;
-    return pick_cfg(g).bm;
+TileCounts conv_tile_counts(const ConvGeom& g) {
+    TileCfg c;
+    if (pick_tile(CONV_FWD, g, c)) return TileCounts{c.tiles, c.t.OH, c.t.OW, c.t.nc, c.t.rows, c.t.Wo};
+    return tile_counts_rows((long)g.Nb * g.Ho * g.Wo, pick_cfg(g).bm);
 }
 
 hipError_t launch_conv_igemm(int mode, const float* src, const float* B, const float* bias, float* Y,
@@ -1093,8 +1085,7 @@ hipError_t launch_conv_igemm(int mode, const float* src, const float* B, const f
 
 int conv_dgrad_sum_tiles(const ConvGeom& gd) {
     TileCfg tc;
-    if (!pick_tile(CONV_DGRAD, gd, tc)) return 0;
-    return gd.Nb * tc.t.tiles_per_img;
+    return pick_tile(CONV_DGRAD, gd, tc) ? tc.tiles : 0;
 }
 
 bool conv_fold_ok(const ConvGeom& g, const WgradPlan& p) {
@@ -1231,155 +1222,153 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32(const float* __restrict__ 
     }
 }
 
-// Spatially tiled weight gradient (Cs % 16 == 0): a workgroup takes a tile
-// of TP output pixels (OH full rows of one image, or IMGS whole images), 16
-// output channels and 16 input channels, and produces the partial
-//     dW[co][r][s][c] = sum over the tile's pixels p of dY[p][co] * X[src(p, r, s)][c]
-// for every tap.  The tile's input rows (halo and padding included; for a
-// 1x1 conv just the pixels it reads) are staged in LDS once; each wave takes
-// NG groups of 16 pixels, keeps their dY values in registers and runs all
-// taps over them, so dY is read once and X once per channel block.  The
-// reduction dimension k of v_mfma_f32_16x16x4_f32 is the pixel: lane
-// (li, gi) supplies dY[p][co0 + li] and X[src(p)][c0 + li] for the same four
-// pixels p = 16 g + 4 gi + j.  Waves are summed in a fixed order and every
-// tile writes its own partial part[tile][co][(r, s, c)], summed in order by
-// the reduce kernel.
-struct WgTileGeom { int OH, IMGS, IH, IW, tiles_per_img, TP; unsigned IW_inv, IHW_inv; };
+// Spatially tiled weight gradient: a workgroup takes a run of boxes of NG * 64
+// pixel slots (BoxGeom; 16 output and 16 input channels) and produces the
+// partial
+//     dW[co][r][s][c] = sum over its boxes' pixels p of dY[p][co] * X[src(p, r, s)][c]
+// for every tap.  A box's input rows (halo and padding included; for a 1x1
+// conv just the pixels it reads) and its dY go into LDS once, the next box's
+// loads in flight during this one's MFMAs; each wave takes NG groups of 16
+// slots, keeps their dY values in registers and runs all taps over them.  The
+// reduction dimension k of v_mfma_f32_16x16x4_f32 is the pixel: lane (li, gi)
+// supplies dY[p][co0 + li] and X[src(p)][c0 + li] for the same four slots
+// p = 16 g + 4 gi + j, consecutive in one box row (OWs % 4 == 0); slots
+// without a pixel hold dY = 0.  Waves are summed in a fixed order and every
+// workgroup writes its own partial, summed in order by the reduce kernel.
+// Bound by the staging's latency at ResNet-20's sizes (one box per workgroup)
+// and by the MFMAs where several boxes pipeline; about 1024 workgroups, so
+// that large grids keep few partials.
+constexpr int kWgBatches = 9;   // staged input quads per thread and box, at most
 
-// Held to 128 registers (four waves per SIMD) where that needs no spilling:
-// every variant but the strided 1x1 one.
-template <int RS, int NG, int ST, bool K1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((RS == 9 || ST == 1) ? 4 : 1, 8)))
-void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__ X,
-                                                           float* __restrict__ part, WgArgs a, WgTileGeom t,
-                                                           const float* __restrict__ in_ss) {
+template <int RS, int NG, int ST>
+__global__ __launch_bounds__(256) void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__ X,
+                                                           float* __restrict__ part, WgArgs a, BoxGeom t, int tiles,
+                                                           int per, const float* __restrict__ in_ss) {
+    constexpr bool K1 = RS == 1;
     constexpr int LDW = 20;
     constexpr int JST = (K1 ? 1 : ST) * LDW;   // LDS distance between a lane's four pixels
     constexpr int TP = NG * 64;
-    constexpr int NU = 8;
     extern __shared__ float lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int gi = lane >> 4, li = lane & 15;
-    const int tile = blockIdx.x;
+    const int gi = lane >> 4, li = lane & 15, q = tid & 3;
     const int co0 = blockIdx.y * 16, c0 = blockIdx.z * 16;
-    const int img0 = t.IMGS == 1 ? tile / t.tiles_per_img : tile * t.IMGS;
-    const int oh0 = t.IMGS == 1 ? (tile - img0 * t.tiles_per_img) * t.OH : 0;
     const int Ktot = RS * a.Cin_p;
-    const long m0 = (long)tile * TP;
-    const int ohw = t.OH * a.Wo;
-    const int npix = t.IMGS * t.IH * t.IW;
-    float* Xs = lds;                         // [npix][LDW] input rows of the tile
-    float* Ds = lds + npix * LDW;            // [TP][LDW] dY of the tile, 16 channels
+    const int npix = t.IH * t.IW, nx = npix * 4, nxu = (nx + 255) >> 8;
+    float* Xs = lds;                         // [npix][LDW] input rows of the box
+    float* Ds = lds + npix * LDW;            // [TP][LDW] dY of the box, 16 channels
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(X, (long)a.Nb * a.Hi * a.Wi * a.Cin_p);
+    const __amdgpu_buffer_rsrc_t dr = buf_rsrc(dY, (long)a.Nb * a.Ho * a.Wo * a.Cout);
 
-    // stage X rows and the dY tile: element e = tid + 256 u has quad tid & 3.
-    // All of a batch's loads are issued before any value is used: elements
-    // without a source (zero padding, past the tiles) load X's first quad of
-    // the channel block, a valid address, and are zeroed afterwards (with
-    // conditional loads and the fold right behind each, the loads would go
-    // out one round trip at a time).
-    {
-        const int q = tid & 3;
-        const int nx = npix * 4, ntot = nx + TP * 4;
-        // the fold's scale and shift of this thread's channel quad (the same
-        // for all its elements)
-        float fsc[4] = {1.f, 1.f, 1.f, 1.f}, fsh[4] = {0.f, 0.f, 0.f, 0.f};
-        if (in_ss) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                fsc[k] = in_ss[c0 + q * 4 + k];
-                fsh[k] = in_ss[a.Cin_p + c0 + q * 4 + k];
-            }
-        }
-        for (int base = tid; base < ntot; base += NU * 256) {
-            f4 v[NU];
-            int d[NU];
-            bool z[NU];
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const int e = base + u * 256;
-                const float* sp = X + c0 + q * 4;
-                z[u] = true;
-                d[u] = -1;
-                if (e < nx) {
-                    const int pix = e >> 2;
-                    const int il = (int)__umulhi((unsigned)pix, t.IHW_inv);
-                    const int rem = pix - il * (t.IH * t.IW);
-                    const int ih = (int)__umulhi((unsigned)rem, t.IW_inv);
-                    const int iw = rem - ih * t.IW;
-                    const int h = K1 ? (oh0 + ih) * ST : oh0 * ST - a.pad + ih;
-                    const int w = K1 ? iw * ST : iw - a.pad;
-                    if (h >= 0 && h < a.Hi && w >= 0 && w < a.Wi) {
-                        sp = X + ((long)((img0 + il) * a.Hi + h) * a.Wi + w) * a.Cin_p + c0 + q * 4;
-                        z[u] = false;
-                    }
-                    d[u] = pix * LDW + q * 4;
-                } else if (e < ntot) {
-                    const int p = (e - nx) >> 2;
-                    sp = dY + (m0 + p) * a.Cout + co0 + q * 4;
-                    z[u] = false;
-                    d[u] = (npix + p) * LDW + q * 4;
-                }
-                v[u] = ld_global4(sp);
-            }
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                if (z[u]) v[u] = f4{0.f, 0.f, 0.f, 0.f};
-                // X read through a folded BN + ReLU (padding stays zero)
-                else if (in_ss && base + u * 256 < nx) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) v[u][k] = fmaxf(__builtin_fmaf(v[u][k], fsc[k], fsh[k]), 0.f);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-                if (d[u] >= 0) *(f4*)(lds + d[u]) = v[u];
-        }
+    // the fold's scale and shift of this thread's channel quad
+    f4 fsc{}, fsh{};
+    if (in_ss && c0 + q * 4 < a.Cin_p) {
+        fsc = *(const f4*)(in_ss + c0 + q * 4);
+        fsh = *(const f4*)(in_ss + a.Cin_p + c0 + q * 4);
     }
+    f4 xv[kWgBatches], dv[NG];
+    unsigned valid = 0;                      // batches whose quad lies inside X
+    auto load = [&](int tile) {
+        const int tr = box_div(tile, t.nc_inv), tc = tile - tr * t.nc;
+        const int R0 = tr * t.OH, w0 = tc * t.OW, P0 = box_prow(t, R0);
+        const int ohv = min(t.OH, t.rows - R0), owv = min(t.OW, t.Wo - w0);
+        valid = 0;
+#pragma unroll
+        for (int u = 0; u < kWgBatches; ++u)
+            if (u < nxu) {
+                const int pix = (tid + u * 256) >> 2;
+                const int ih = box_div(pix, t.IW_inv), iw = pix - ih * t.IW;
+                const int pr = P0 + ih;
+                const int n = box_div(pr, t.Hp_inv), hh = pr - n * t.Hp;
+                const int h = (K1 ? hh * ST : hh) - t.pad_eff;
+                const int w = (K1 ? (w0 + iw) * ST : w0 * ST + iw) - t.pad_eff;
+                unsigned off = kNoLoad;
+                if (ih < t.IH && n < a.Nb && h >= 0 && h < a.Hi && w >= 0 && w < a.Wi && c0 + q * 4 < a.Cin_p) {
+                    off = (unsigned)(((n * a.Hi + h) * a.Wi + w) * a.Cin_p + c0 + q * 4) * 4u;
+                    valid |= 1u << u;
+                }
+                xv[u] = buf_load4(xr, off, 0);
+            }
+#pragma unroll
+        for (int u = 0; u < NG; ++u) {
+            const int p = (tid + u * 256) >> 2;
+            const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+            const bool ok = oh < ohv && ow < owv && co0 + q * 4 < a.Cout;
+            dv[u] = buf_load4(dr, ok ? (unsigned)(((R0 + oh) * t.Wo + w0 + ow) * a.Cout + co0 + q * 4) * 4u : kNoLoad,
+                              0);
+        }
+    };
 
-    // this lane's pixels p = 16 (wave NG + g) + 4 gi + j: four consecutive
-    // pixels of one output row (Wo % 4 == 0), so one LDS base per group
-    int boff[NG];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        const int p = (wave * NG + g) * 16 + gi * 4;
-        const int il = p / ohw, rem = p - il * ohw;
-        const int ohl = rem / a.Wo, ow = rem - ohl * a.Wo;
-        boff[g] = (K1 ? p : (il * t.IH + ohl * ST) * t.IW + ow * ST) * LDW + li;
-    }
     int toff[RS];
 #pragma unroll
     for (int k = 0; k < RS; ++k) toff[k] = K1 ? 0 : ((k / 3) * t.IW + k % 3) * LDW;
-    __syncthreads();
-
     f4 acc[RS];
 #pragma unroll
     for (int k = 0; k < RS; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
-    // per group: the four dY values and all RS x 4 X operands are read before
-    // its MFMAs, the next group's reads are issued before this group's MFMAs
-    float bv[2][RS][4];
-    f4 av[2];
+
+    const int t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);
+    const int sdst = (tid >> 2) * LDW + q * 4;
+    load(t0);
+    for (int tile = t0; tile < t1; ++tile) {
+        if (in_ss) {
+            // X read through a folded BN + ReLU (padding stays zero)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) av[0][j] = Ds[(wave * NG * 16 + gi * 4 + j) * LDW + li];
+            for (int u = 0; u < kWgBatches; ++u)
+                if (u < nxu) {
 #pragma unroll
-    for (int k = 0; k < RS; ++k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bv[0][k][j] = Xs[boff[0] + toff[k] + j * JST];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (g + 1 < NG) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) av[(g + 1) & 1][j] = Ds[(((wave * NG + g + 1) * 16) + gi * 4 + j) * LDW + li];
-#pragma unroll
-            for (int k = 0; k < RS; ++k)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) bv[(g + 1) & 1][k][j] = Xs[boff[g + 1] + toff[k] + j * JST];
+                    for (int k = 0; k < 4; ++k)
+                        xv[u][k] = (valid >> u) & 1 ? fmaxf(__builtin_fmaf(xv[u][k], fsc[k], fsh[k]), 0.f) : 0.f;
+                }
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int u = 0; u < kWgBatches; ++u)
+            if (u < nxu && tid + u * 256 < nx) *(f4*)(Xs + sdst + u * 64 * LDW) = xv[u];
 #pragma unroll
-            for (int k = 0; k < RS; ++k) acc[k] = mfma16x16x4(av[g & 1][j], bv[g & 1][k][j], acc[k]);
+        for (int u = 0; u < NG; ++u) *(f4*)(Ds + sdst + u * 64 * LDW) = dv[u];
+        // the first of each group's four consecutive slots (rows past the
+        // box's, whose dY is zero, read the first)
+        int boff[NG];
+        {
+            const int tr = box_div(tile, t.nc_inv), R0 = tr * t.OH, P0 = box_prow(t, R0);
+            const int ohv = min(t.OH, t.rows - R0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int p = (wave * NG + g) * 16 + gi * 4;
+                const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+                const bool ok = oh < ohv;
+                boff[g] = ((ok ? box_prow(t, R0 + oh) - P0 : 0) * t.IW + (ok ? ow * (K1 ? 1 : ST) : 0)) * LDW + li;
+            }
+        }
+        lds_barrier();
+        if (tile + 1 < t1) load(tile + 1);
+        // per group: the four dY values and all RS x 4 X operands are read
+        // before its MFMAs, the next group's reads are issued before this
+        // group's MFMAs
+        float bv[2][RS][4];
+        f4 av[2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) av[0][j] = Ds[(wave * NG * 16 + gi * 4 + j) * LDW + li];
+#pragma unroll
+        for (int k = 0; k < RS; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bv[0][k][j] = Xs[boff[0] + toff[k] + j * JST];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            if (g + 1 < NG) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    av[(g + 1) & 1][j] = Ds[(((wave * NG + g + 1) * 16) + gi * 4 + j) * LDW + li];
+#pragma unroll
+                for (int k = 0; k < RS; ++k)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) bv[(g + 1) & 1][k][j] = Xs[boff[g + 1] + toff[k] + j * JST];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int k = 0; k < RS; ++k) acc[k] = mfma16x16x4(av[g & 1][j], bv[g & 1][k][j], acc[k]);
+        }
+        lds_barrier();   // the staged box is dead
     }
-    __syncthreads();   // the staged tiles are dead: their space takes the wave sums
 
     // each wave's RS x 16 x 16 block into its own LDS slice, then the four
     // slices summed in order
@@ -1389,56 +1378,49 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
 #pragma unroll
         for (int i = 0; i < 4; ++i) red[((wave * RS + k) * 16 + gi * 4 + i) * 16 + li] = acc[k][i];
     __syncthreads();
-    float* out = part + (long)tile * a.Cout * Ktot;
+    float* out = part + (long)blockIdx.x * a.Cout * Ktot;
     for (int e = tid; e < RS * 256; e += 256) {
         const int k = e >> 8, col = (e >> 4) & 15, c = e & 15;
         const float v = ((red[e] + red[RS * 256 + e]) + red[2 * RS * 256 + e]) + red[3 * RS * 256 + e];
-        out[(long)(co0 + col) * Ktot + k * a.Cin_p + c0 + c] = v;
+        if (co0 + col < a.Cout && c0 + c < a.Cin_p) out[(long)(co0 + col) * Ktot + k * a.Cin_p + c0 + c] = v;
     }
 }
 
-// Tile shape for the spatially tiled weight gradient, or false when it does
-// not apply (the GEMM-style kernel takes those passes).
+// Boxes of the spatially tiled weight gradient, or false when it does not
+// apply (the GEMM-style kernel takes those passes).  256 slots, or fewer where
+// that leaves less than 512 workgroups; runs of boxes for about 1024.
+struct WgTileCfg { int ng, tiles, per, splits; BoxGeom t; size_t lds; };
 static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride,
-                            int pad, WgTileGeom& t) {
-    if (Cin_p % 16 || Cout % 16 || Wo % 4 || (stride != 1 && stride != 2)) return false;
-    if (!((R == 3 && S == 3) || (R == 1 && S == 1 && pad == 0))) return false;
-    const bool k1 = R == 1;
-    for (int tp : {256, 128, 64}) {
-        int oh, imgs;
-        if (Ho * Wo >= tp) {
-            if (tp % Wo) continue;
-            oh = tp / Wo;
-            if (Ho % oh) continue;
-            imgs = 1;
-        } else {
-            if (tp % (Ho * Wo)) continue;
-            oh = Ho;
-            imgs = tp / (Ho * Wo);
-            if (Nb % imgs) continue;
-        }
-        const int ih = k1 ? oh : (oh - 1) * stride + R, iw = k1 ? Wo : (Wo - 1) * stride + S;
-        const size_t lds = sizeof(float) * std::max<size_t>(((size_t)imgs * ih * iw + tp) * 20, (size_t)4 * R * S * 256);
-        if (lds > 60 * 1024) continue;
-        const unsigned iw_inv = (unsigned)((0x100000000ull + iw - 1) / iw);
-        const unsigned ihw_inv = (unsigned)((0x100000000ull + ih * iw - 1) / (ih * iw));
-        t = WgTileGeom{oh, imgs, ih, iw, imgs == 1 ? Ho / oh : 0, tp, iw_inv, ihw_inv};
-        return true;
+                            int pad, WgTileCfg& out) {
+    if (Cin_p % 4 || Cout % 4 || R != S || (R != 1 && R != 3) || (stride != 1 && stride != 2)) return false;
+    if (!buf_fits((double)Nb * Hi * Wi * Cin_p) || !buf_fits((double)Nb * Ho * Wo * Cout)) return false;
+    const long blocks = (long)((Cout + 15) / 16) * ((Cin_p + 15) / 16);
+    bool found = false;
+    for (int ng : {4, 2, 1}) {
+        WgTileCfg c;
+        if (!box_pick(c.t, Nb, Ho, Wo, R, R == 1 ? 1 : stride, pad, ng * 64, 4, kWgBatches)) continue;
+        c.ng = ng;
+        c.lds = sizeof(float) *
+                std::max<size_t>(((size_t)c.t.IH * c.t.IW + ng * 64) * 20, (size_t)4 * R * S * 256);
+        c.tiles = box_tiles(c.t);
+        const long splits = std::min<long>(c.tiles, std::max<long>(1, 1024 / blocks));
+        c.per = (int)((c.tiles + splits - 1) / splits);
+        c.splits = (c.tiles + c.per - 1) / c.per;
+        found = true;
+        out = c;
+        if (c.splits * blocks >= 512) break;
     }
-    return false;
+    return found;
 }
 
 WgradPlan wgrad_plan(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride, int pad) {
     WgradPlan p{};
     const long M = (long)Nb * Ho * Wo;
     const int Ktot = R * S * Cin_p;
-    WgTileGeom t;
-    if (pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, t)) {
+    WgTileCfg c;
+    if (pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c)) {
         p.tile = 1;
-        p.oh = t.OH;
-        p.imgs = t.IMGS;
-        p.splits = (int)(M / t.TP);
-        p.pix_per_split = t.TP;
+        p.splits = c.splits;
         p.part_floats = (long)p.splits * Cout * Ktot;
         return p;
     }
@@ -1469,23 +1451,17 @@ static hipError_t launch_wg(const float* dY, const float* X, float* part, const 
     return hipGetLastError();
 }
 
-template <int RS, int NG, int ST, bool K1>
-static hipError_t launch_wg_tile(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileGeom& t,
+template <int RS, int ST>
+static hipError_t launch_wg_tile(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
                                  const float* in_ss, hipStream_t st) {
-    const long M = (long)a.Nb * a.Ho * a.Wo;
-    dim3 grid((unsigned)(M / t.TP), (unsigned)(a.Cout / 16), (unsigned)(a.Cin_p / 16));
-    const size_t lds = sizeof(float) * std::max<size_t>(((size_t)t.IMGS * t.IH * t.IW + t.TP) * 20, (size_t)4 * RS * 256);
-    launch((conv_wgrad_tile_f32<RS, NG, ST, K1>), grid, dim3(256), lds, st, dY, X, part, a, t, in_ss);
+    dim3 grid((unsigned)c.splits, (unsigned)((a.Cout + 15) / 16), (unsigned)((a.Cin_p + 15) / 16));
+    if (c.ng == 4)
+        launch((conv_wgrad_tile_f32<RS, 4, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per, in_ss);
+    else if (c.ng == 2)
+        launch((conv_wgrad_tile_f32<RS, 2, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per, in_ss);
+    else
+        launch((conv_wgrad_tile_f32<RS, 1, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per, in_ss);
     return hipGetLastError();
-}
-
-template <int RS, int ST, bool K1>
-static hipError_t launch_wg_tile_ng(const float* dY, const float* X, float* part, const WgArgs& a,
-                                    const WgTileGeom& t, const float* in_ss, hipStream_t st) {
-    const int ng = t.TP / 64;
-    if (ng == 4) return launch_wg_tile<RS, 4, ST, K1>(dY, X, part, a, t, in_ss, st);
-    if (ng == 2) return launch_wg_tile<RS, 2, ST, K1>(dY, X, part, a, t, in_ss, st);
-    return launch_wg_tile<RS, 1, ST, K1>(dY, X, part, a, t, in_ss, st);
 }
 
 hipError_t launch_conv_wgrad(const float* dY, const float* X, float* part, int Nb, int Hi, int Wi, int Cin_p,
@@ -1494,16 +1470,15 @@ hipError_t launch_conv_wgrad(const float* dY, const float* X, float* part, int N
     WgArgs a{Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, p.pix_per_split};
     if (in_ss && !p.tile) return hipErrorInvalidValue;   // folding needs the spatial kernel
     if (p.tile) {
-        WgTileGeom t;
-        if (!pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, t) || t.OH != p.oh ||
-            t.IMGS != p.imgs)
+        WgTileCfg c;
+        if (!pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c) || c.splits != p.splits)
             return hipErrorInvalidValue;
         if (R == 1) {
-            if (stride == 1) return launch_wg_tile_ng<1, 1, true>(dY, X, part, a, t, in_ss, st);
-            return launch_wg_tile_ng<1, 2, true>(dY, X, part, a, t, in_ss, st);
+            if (stride == 1) return launch_wg_tile<1, 1>(dY, X, part, a, c, in_ss, st);
+            return launch_wg_tile<1, 2>(dY, X, part, a, c, in_ss, st);
         }
-        if (stride == 1) return launch_wg_tile_ng<9, 1, false>(dY, X, part, a, t, in_ss, st);
-        return launch_wg_tile_ng<9, 2, false>(dY, X, part, a, t, in_ss, st);
+        if (stride == 1) return launch_wg_tile<9, 1>(dY, X, part, a, c, in_ss, st);
+        return launch_wg_tile<9, 2>(dY, X, part, a, c, in_ss, st);
     }
     if (p.tm == 1) return launch_wg<1, 4>(dY, X, part, a, p, st);
     if (p.tm == 2) return launch_wg<2, 4>(dY, X, part, a, p, st);

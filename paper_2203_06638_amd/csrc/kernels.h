@@ -84,7 +84,7 @@ constexpr int kFoldMaxC = 512;
 // passes with stats non-null also produce the batch-norm sums of Y: into
 // acc, q = 0: sum y and q = 1: sum y^2 (each row tile's share formed from its
 // mean and sum of squared deviations); as partials, the tile mean (p0) and
-// sum of squared deviations (p1), T = ceil(M / conv_tile_rows(g)) tiles.
+// sum of squared deviations (p1) of each tile of conv_tile_counts(g).
 // inbn (forward only; see conv_fold_ok): src is the input of a BN + ReLU
 // and the pass reads relu(bn(src)) without storing it.
 // Data gradients with stats (and bsum): the output g is the gradient at a
@@ -110,13 +110,18 @@ hipError_t launch_conv_igemm(int mode, const float* src, const float* B, const f
                              const BnFwd* inbn = nullptr, const BnBwdSum* bsum = nullptr);
 // Tiles of the spatial data-gradient kernel for g, or 0 when it does not take g.
 int conv_dgrad_sum_tiles(const ConvGeom& g);
-int conv_tile_rows(const ConvGeom& g);
+// Rows of the tiles whose partials a pass writes: tile t covers
+// min(OH, rows - (t / nc) OH) x min(OW, Wo - (t % nc) OW) output pixels.
+struct TileCounts { int tiles, OH, OW, nc; long rows; int Wo; };
+// tiles of R consecutive rows of M
+inline TileCounts tile_counts_rows(long M, int R) { return TileCounts{(int)((M + R - 1) / R), R, 1, 1, M, 1}; }
+TileCounts conv_tile_counts(const ConvGeom& g);
 
 // Weight gradient: part[split][Cout][Ktot] = partial sums over pixel ranges
 // of dY[p][cout] * im2col(X)[p][(r,s,c)].  wgrad_plan chooses the kernel:
-// spatial tiles (tile = 1: a split is a tile of OH rows of one image or of
-// `imgs` whole images) or GEMM tiles over ranges of pix_per_split pixels.
-struct WgradPlan { int tm, tn, splits, pix_per_split; long part_floats; int tile, oh, imgs; };
+// spatial tiles (tile = 1: a split is a run of pixel boxes) or GEMM tiles over
+// ranges of pix_per_split pixels.
+struct WgradPlan { int tm, tn, splits, pix_per_split; long part_floats; int tile; };
 WgradPlan wgrad_plan(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride, int pad);
 // in_ss (spatial-tile plans only): X is the input of a BN + ReLU whose
 // scale and shift are in_ss[c] and in_ss[Cin_p + c]; the pass reads
@@ -177,10 +182,10 @@ int stats_tiles(long M, int C);
 // into p0 / p1 [T][C], or the tile's share of the batch sums added into
 // acc [2][kAccSlots][C] (sum x, sum x^2)
 hipError_t launch_stats_partial(int dt, const void* x, long M, int C, const BnSums& out, hipStream_t st);
-// merges T tiles of R rows (fp64, fixed order) into aux = [mean | rstd |
+// merges the tiles (fp64, fixed order) into aux = [mean | rstd |
 // scale | shift]: rstd = 1/sqrt(var + eps) with the biased variance,
 // scale = gamma*rstd, shift = beta - mean*scale
-hipError_t launch_stats_finalize(const float* pmean, const float* pm2, int T, int R, long M, int C,
+hipError_t launch_stats_finalize(const float* pmean, const float* pm2, const TileCounts& tc, long M, int C,
                                  const float* gamma, const float* beta, float eps, float* aux, hipStream_t st);
 // out[c] = sum_t rows_t * pmean[t][c]: column sums from tile means
 hipError_t launch_sum_from_tiles(const float* pmean, int T, int R, long M, int C, float* out, hipStream_t st);

@@ -157,20 +157,23 @@ hipError_t launch_stats_partial(int dt, const void* x, long M, int C, const BnSu
 // partial sums meet in the fixed tree.  mean = sum n_t m_t / M,
 // M2 = sum (M2_t + n_t (m_t - mean)^2).
 __global__ __launch_bounds__(256) void stats_finalize_k(const float* __restrict__ pmean, const float* __restrict__ pm2,
-                                                        int T, int R, long M, int C, const float* __restrict__ gamma,
+                                                        TileCounts tc, long M, int C, const float* __restrict__ gamma,
                                                         const float* __restrict__ beta, float eps, float* aux) {
     __shared__ double red[256];
     const int c = blockIdx.x;
+    auto count = [&](int t) {
+        const int tr = tc.nc == 1 ? t : t / tc.nc, tq = t - tr * tc.nc;
+        return (double)min((long)tc.OH, tc.rows - (long)tr * tc.OH) * (double)min(tc.OW, tc.Wo - tq * tc.OW);
+    };
     double s = 0.0;
 #pragma unroll 4
-    for (int t = threadIdx.x; t < T; t += 256)
-        s += (double)min((long)R, M - (long)t * R) * (double)pmean[(long)t * C + c];
+    for (int t = threadIdx.x; t < tc.tiles; t += 256) s += count(t) * (double)pmean[(long)t * C + c];
     const double mu = tree_sum256(s, red) / (double)M;
     double q = 0.0;
 #pragma unroll 4
-    for (int t = threadIdx.x; t < T; t += 256) {
+    for (int t = threadIdx.x; t < tc.tiles; t += 256) {
         const double d = (double)pmean[(long)t * C + c] - mu;
-        q += (double)pm2[(long)t * C + c] + (double)min((long)R, M - (long)t * R) * d * d;
+        q += (double)pm2[(long)t * C + c] + count(t) * d * d;
     }
     q = tree_sum256(q, red);
     if (threadIdx.x == 0) {
@@ -183,9 +186,9 @@ __global__ __launch_bounds__(256) void stats_finalize_k(const float* __restrict_
     }
 }
 
-hipError_t launch_stats_finalize(const float* pmean, const float* pm2, int T, int R, long M, int C,
+hipError_t launch_stats_finalize(const float* pmean, const float* pm2, const TileCounts& tc, long M, int C,
                                  const float* gamma, const float* beta, float eps, float* aux, hipStream_t st) {
-    launch(stats_finalize_k, dim3(C), dim3(256), 0, st, pmean, pm2, T, R, M, C, gamma, beta, eps, aux);
+    launch(stats_finalize_k, dim3(C), dim3(256), 0, st, pmean, pm2, tc, M, C, gamma, beta, eps, aux);
     return hipGetLastError();
 }
 

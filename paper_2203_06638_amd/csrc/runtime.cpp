@@ -765,7 +765,7 @@ int bn_stats_standalone(lpp_ctx* c, Worker& w, int b) {
         const lpp::BnSums out{nullptr, w.ps0, w.ps1, nullptr};
         LAUNCH("bn_stats", eb * rows * C, st, lpp::launch_stats_partial(dt, x, rows, C, out, st));
         LAUNCH("bn_stats", 0.0, st,
-               lpp::launch_stats_finalize(w.ps0, w.ps1, lpp::stats_tiles(rows, C), lpp::stats_rows(rows, C), rows, C,
+               lpp::launch_stats_finalize(w.ps0, w.ps1, lpp::tile_counts_rows(rows, lpp::stats_rows(rows, C)), rows, C,
                                           w.v + B.poff, w.v + B.poff + C, M.desc.bn_eps, c->aux(w, b), st));
     } else {
         const lpp::BnSums out{c->acc_fwd(w, b), nullptr, nullptr, nullptr};
@@ -825,10 +825,10 @@ int run_forward(lpp_ctx* c, Worker& w) {
             if (G.stats_bn >= 0 && c->fixed_order) {
                 const Layer& B = M.layers[G.stats_bn];
                 const long rows = (long)N * Y.out.h * Y.out.w;
-                const int R = bf ? lpp::conv_bf16_tile_rows(g) : lpp::conv_tile_rows(g);
-                const int T = (int)((rows + R - 1) / R);
+                const lpp::TileCounts tc =
+                    bf ? lpp::tile_counts_rows(rows, lpp::conv_bf16_tile_rows(g)) : lpp::conv_tile_counts(g);
                 LAUNCH("bn_stats", 0.0, st,
-                       lpp::launch_stats_finalize(w.ps0, w.ps1, T, R, rows, Y.L.cout, w.v + B.poff,
+                       lpp::launch_stats_finalize(w.ps0, w.ps1, tc, rows, Y.L.cout, w.v + B.poff,
                                                   w.v + B.poff + Y.L.cout, M.desc.bn_eps, c->aux(w, G.stats_bn), st));
             }
             break;
@@ -1370,8 +1370,9 @@ int lpp_init(const lpp_model_desc* desc, int K, int P, const lpp_options* opt, l
             lpp::ConvGeom g{N, Y.in0.h, Y.in0.w, Y.cin_p, Y.out.h, Y.out.w, Y.L.cout, Y.L.k, Y.L.k, Y.L.stride,
                             Y.L.pad};
             g.fill = M.conv_fill;
-            const int tr = M.dt == lpp::DT_BF16 ? lpp::conv_bf16_tile_rows(g) : lpp::conv_tile_rows(g);
-            const long tiles = (rows_out + tr - 1) / tr;
+            const long tiles = M.dt == lpp::DT_BF16
+                                   ? lpp::tile_counts_rows(rows_out, lpp::conv_bf16_tile_rows(g)).tiles
+                                   : lpp::conv_tile_counts(g).tiles;
             ps = std::max<long>(ps, tiles * Y.L.cout);
             ps = std::max<long>(ps, (long)lpp::stats_tiles(rows_out, Y.L.cout) * Y.L.cout);
             if (Y.gsum_bn >= 0) {
