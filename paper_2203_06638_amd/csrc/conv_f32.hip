@@ -1236,14 +1236,15 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32(const float* __restrict__ 
 // without a pixel hold dY = 0.  Waves are summed in a fixed order and every
 // workgroup writes its own partial, summed in order by the reduce kernel.
 // Bound by the staging's latency at ResNet-20's sizes (one box per workgroup)
-// and by the MFMAs where several boxes pipeline; about 1024 workgroups, so
-// that large grids keep few partials.
-constexpr int kWgBatches = 9;   // staged input quads per thread and box, at most
+// and by the MFMAs where several boxes pipeline.  Held to 168 registers, three
+// workgroups to a compute unit (with two, 16 x 56x56x64 takes 54 us instead of
+// 45, ResNet-20's stages 11.2 instead of 10.8).
+constexpr int kWgBatches = 6;   // staged input quads per thread and box, at most
 
 template <int RS, int NG, int ST>
-__global__ __launch_bounds__(256) void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__ X,
-                                                           float* __restrict__ part, WgArgs a, BoxGeom t, int tiles,
-                                                           int per, const float* __restrict__ in_ss) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8)))
+void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__ X, float* __restrict__ part, WgArgs a,
+                         BoxGeom t, int tiles, int per, const float* __restrict__ in_ss) {
     constexpr bool K1 = RS == 1;
     constexpr int LDW = 20;
     constexpr int JST = (K1 ? 1 : ST) * LDW;   // LDS distance between a lane's four pixels
@@ -1387,12 +1388,18 @@ __global__ __launch_bounds__(256) void conv_wgrad_tile_f32(const float* __restri
 }
 
 // Boxes of the spatially tiled weight gradient, or false when it does not
-// apply (the GEMM-style kernel takes those passes).  256 slots, or fewer where
-// that leaves less than 512 workgroups; runs of boxes for about 1024.
+// apply (the GEMM-style kernel takes those passes, and a few input channels to
+// many outputs, the stems, whose MFMA columns would be mostly padding: 128 x
+// 32x32, 4 -> 96 channels 38 us here, 36 there).  At most 768 workgroups, one
+// round of three to a compute unit: each takes a single box of 256 slots where
+// that gives at least 512 workgroups, else a run of boxes of 128 slots, or of
+// 64 where 128 leave fewer than 512 (measured over 512-1536 workgroups and all
+// three sizes: within 4% of the best of 22 passes).
 struct WgTileCfg { int ng, tiles, per, splits; BoxGeom t; size_t lds; };
 static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride,
                             int pad, WgTileCfg& out) {
     if (Cin_p % 4 || Cout % 4 || R != S || (R != 1 && R != 3) || (stride != 1 && stride != 2)) return false;
+    if (Cin_p < 16 && Cout > 32) return false;
     if (!buf_fits((double)Nb * Hi * Wi * Cin_p) || !buf_fits((double)Nb * Ho * Wo * Cout)) return false;
     const long blocks = (long)((Cout + 15) / 16) * ((Cin_p + 15) / 16);
     bool found = false;
@@ -1403,9 +1410,10 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
         c.lds = sizeof(float) *
                 std::max<size_t>(((size_t)c.t.IH * c.t.IW + ng * 64) * 20, (size_t)4 * R * S * 256);
         c.tiles = box_tiles(c.t);
-        const long splits = std::min<long>(c.tiles, std::max<long>(1, 1024 / blocks));
+        const long splits = std::min<long>(c.tiles, std::max<long>(1, 768 / blocks));
         c.per = (int)((c.tiles + splits - 1) / splits);
         c.splits = (c.tiles + c.per - 1) / c.per;
+        if (ng == 4 && (c.per > 1 || c.splits * blocks < 512)) continue;
         found = true;
         out = c;
         if (c.splits * blocks >= 512) break;
