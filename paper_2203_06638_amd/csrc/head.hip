@@ -61,7 +61,7 @@ __device__ void softmax_ce_row(const float* z_s, int O, int y, int Nb, float* re
 // ---- fused form --------------------------------------------------------
 
 // One workgroup per sample: pooled features f (also written out for the
-// weight gradient), logits W f + b, softmax cross-entropy.  Pooling: thread
+// weight gradient where feat is not null), logits W f + b, softmax cross-entropy.  Pooling: thread
 // (q, l) sums channel quad q over pixels l, l + rl, ...; the rl partial sums
 // of a quad are added in LDS in a fixed order.  C % 4 == 0.
 template <class T>
@@ -89,16 +89,32 @@ __global__ __launch_bounds__(256) void head_fwd_k(const T* __restrict__ x, int N
             for (int k = 1; k < rl; ++k) tot += part[k * nq + t];
             const f4 f = tot / (float)HW;
             *(f4*)(f_s + 4 * (q0 + t)) = f;
-            *(f4*)(feat + (long)n * C + 4 * (q0 + t)) = f;
+            if (feat) *(f4*)(feat + (long)n * C + 4 * (q0 + t)) = f;
         }
         __syncthreads();
     }
-    for (int o = t; o < O; o += 256) {
-        float z = b ? b[o] : 0.f;
+    // 16 lanes to a class (whole 64-byte runs of its weight row), lane sums by
+    // a fixed xor tree
+    const int l16 = t & 15;
+    const bool quads = ((uintptr_t)W & 15) == 0;
+    for (int o = t >> 4; o < O; o += 16) {
         const float* w = W + (long)o * C;
-        for (int c = 0; c < C; ++c) z += w[c] * f_s[c];
-        z_s[o] = z;
-        logits[(long)n * O + o] = z;
+        float z = 0.f;
+        if (quads) {
+            for (int c = 4 * l16; c < C; c += 64) {
+                const f4 wv = *(const f4*)(w + c), fv = *(const f4*)(f_s + c);
+                z += wv[0] * fv[0] + wv[1] * fv[1] + wv[2] * fv[2] + wv[3] * fv[3];
+            }
+        } else {
+            for (int c = l16; c < C; c += 16) z += w[c] * f_s[c];
+        }
+#pragma unroll
+        for (int k = 8; k > 0; k >>= 1) z += __shfl_xor(z, k);
+        if (l16 == 0) {
+            if (b) z += b[o];
+            z_s[o] = z;
+            logits[(long)n * O + o] = z;
+        }
     }
     __syncthreads();
     softmax_ce_row(z_s, O, args->labels[n], Nb, red, dz + (long)n * O, loss_per + n);
@@ -109,13 +125,25 @@ template <class T>
 __global__ __launch_bounds__(256) void head_bwd_x_k(const float* __restrict__ dz, const float* __restrict__ W,
                                                     int Nb, int HW, int C, int O, T* __restrict__ dx, int acc) {
     __shared__ float df[kHeadMaxC];
+    __shared__ float part[256];
     const int n = blockIdx.x, t = threadIdx.x;
-    for (int c = t; c < C; c += 256) {
+    // gl threads to a channel, each over every gl-th class, added in order
+    const int nc = min(C, 256), gl = 256 / nc, g = t / nc;
+    for (int c0 = 0; c0 < C; c0 += nc) {
+        const int c = c0 + t - g * nc;
         float s = 0.f;
-        for (int o = 0; o < O; ++o) s += dz[(long)n * O + o] * W[(long)o * C + c];
-        df[c] = s / (float)HW;
+        if (g < gl && c < C) {
+#pragma unroll 4
+            for (int o = g; o < O; o += gl) s += dz[(long)n * O + o] * W[(long)o * C + c];
+        }
+        part[t] = s;
+        __syncthreads();
+        if (g == 0 && c < C) {
+            for (int k = 1; k < gl; ++k) s += part[t + k * nc];
+            df[c] = s / (float)HW;
+        }
+        __syncthreads();
     }
-    __syncthreads();
     const int C4 = C >> 2;
     T* out = dx + (long)n * HW * C;
     for (int i = t; i < HW * C4; i += 256) {
@@ -126,6 +154,17 @@ __global__ __launch_bounds__(256) void head_bwd_x_k(const float* __restrict__ dz
 }
 
 // ---- weight gradient (both forms) ----------------------------------------
+
+// The batch-mean loss by one wave: lane l adds samples l, l + 64, ..., lane
+// sums by a fixed xor tree.  (One thread adding 128 samples in turn took
+// longer than the rest of its kernel.)
+__device__ __forceinline__ void mean_loss(const float* __restrict__ loss_per, int Nb, float* __restrict__ loss) {
+    float s = 0.f;
+    for (int n = threadIdx.x & 63; n < Nb; n += 64) s += loss_per[n];
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) s += __shfl_xor(s, k);
+    if ((threadIdx.x & 63) == 0) loss[0] = s / (float)Nb;
+}
 
 // Narrow heads: one workgroup per class o.  dW[o][:] = sum_n dz[n][o] f[n][:]
 // with thread (q, l) summing channel quad q over samples l, l + rl, ... and the
@@ -138,11 +177,7 @@ __global__ __launch_bounds__(256) void head_bwd_w_rows_k(const float* __restrict
     __shared__ f4 part[256];
     __shared__ float pb[256];
     const int o = blockIdx.x, t = threadIdx.x;
-    if (o == 0 && t == 0) {
-        float s = 0.f;
-        for (int n = 0; n < Nb; ++n) s += loss_per[n];
-        loss[0] = s / (float)Nb;
-    }
+    if (o == 0 && t < 64) mean_loss(loss_per, Nb, loss);
     if (!gW) return;
     const int C4 = C >> 2;
     for (int q0 = 0; q0 < C4; q0 += 256) {
@@ -178,18 +213,14 @@ __global__ __launch_bounds__(256) void head_bwd_w_rows_k(const float* __restrict
 }
 
 // dW[o][c] = sum_n dz[n][o] f[n][c], db[o] = sum_n dz[n][o], samples in
-// order; thread 0 of block 0 also forms the batch-mean loss.  Q channels per
+// order; the first wave also forms the batch-mean loss.  Q channels per
 // thread (4 when C % 4 == 0).
 template <int Q>
 __global__ void head_bwd_w_k(const float* __restrict__ dz, const float* __restrict__ feat, int Nb, int C, int O,
                              float* __restrict__ gW, float* __restrict__ gb, const float* __restrict__ loss_per,
                              float* __restrict__ loss) {
     const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx == 0) {
-        float s = 0.f;
-        for (int n = 0; n < Nb; ++n) s += loss_per[n];
-        loss[0] = s / (float)Nb;
-    }
+    if (idx < 64) mean_loss(loss_per, Nb, loss);
     if (!gW) return;
     const int CQ = C / Q;
     if (idx < (long)O * CQ) {
@@ -332,6 +363,13 @@ __global__ __launch_bounds__(512) void head_dfeat_k(const float* __restrict__ dz
 
 bool head_wide(int C, int O) { return C % 16 == 0 && (long)C * O >= kHeadWideMin; }
 
+// Narrow heads over large feature maps pool (and broadcast the gradient) in a
+// pass of its own that fills the chip: the fused kernels walk a sample's
+// HW x C map with one workgroup (at 28x28x128: 19 us for 16 samples and 21 us
+// for 64, against 5-8 us for both launches).  Up to 16384 values a sample
+// the second launch costs more than the walk.
+static bool head_pool_apart(int HW, int C) { return (long)HW * C > 16384; }
+
 hipError_t launch_head_fwd(int dt, const void* x, int Nb, int HW, int C, const float* W, const float* b, int O,
                            const StepArgs* args, float* feat, float* logits, float* dz, float* loss_per,
                            hipStream_t st) {
@@ -345,7 +383,12 @@ hipError_t launch_head_fwd(int dt, const void* x, int Nb, int HW, int C, const f
         return hipGetLastError();
     }
     if (C > kHeadMaxC) return hipErrorInvalidValue;
-    if (dt == DT_BF16)
+    if (head_pool_apart(HW, C)) {
+        hipError_t e = launch_gap_fwd(dt, x, feat, Nb, HW, C, st);
+        if (e != hipSuccess) return e;
+        launch(head_fwd_k<float>, dim3(Nb), dim3(256), 0, st, (const float*)feat, Nb, 1, C, W, b, O, args,
+               (float*)nullptr, logits, dz, loss_per);
+    } else if (dt == DT_BF16)
         launch(head_fwd_k<bf16>, dim3(Nb), dim3(256), 0, st, (const bf16*)x, Nb, HW, C, W, b, O, args, feat, logits,
                dz, loss_per);
     else
@@ -377,6 +420,11 @@ hipError_t launch_head_bwd_x(int dt, const float* dz, const float* W, int Nb, in
         return launch_gap_bwd(dt, scratch, dx, Nb, HW, C, acc, st);
     }
     if (C > kHeadMaxC) return hipErrorInvalidValue;
+    if (head_pool_apart(HW, C)) {
+        if (!scratch) return hipErrorInvalidValue;
+        launch(head_bwd_x_k<float>, dim3(Nb), dim3(256), 0, st, dz, W, Nb, 1, C, O, scratch, 0);
+        return launch_gap_bwd(dt, scratch, dx, Nb, HW, C, acc, st);
+    }
     if (dt == DT_BF16)
         launch(head_bwd_x_k<bf16>, dim3(Nb), dim3(256), 0, st, dz, W, Nb, HW, C, O, (bf16*)dx, (int)acc);
     else
