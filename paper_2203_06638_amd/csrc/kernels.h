@@ -187,11 +187,20 @@ hipError_t launch_stats_partial(int dt, const void* x, long M, int C, const BnSu
 // scale = gamma*rstd, shift = beta - mean*scale
 hipError_t launch_stats_finalize(const float* pmean, const float* pm2, const TileCounts& tc, long M, int C,
                                  const float* gamma, const float* beta, float eps, float* aux, hipStream_t st);
-// out[c] = sum_t rows_t * pmean[t][c]: column sums from tile means
-hipError_t launch_sum_from_tiles(const float* pmean, int T, int R, long M, int C, float* out, hipStream_t st);
-// the same over C columns of partials stored with row stride ld
-hipError_t launch_sum_from_tiles_ld(const float* pmean, int ld, int T, int R, long M, int C, float* out,
-                                    hipStream_t st);
+// Column sums from tile means, several tensors in one launch: job j's out[c] =
+// sum over its tiles of R rows (of M) of rows_t * pmean[t * ld + c], c < C.
+constexpr int kTileSumMaxJobs = 32;
+struct TileSumJob {
+    const float* pmean;
+    float* out;
+    long M;
+    int ld, tiles, R, C;
+    int wg0;              // the job's first workgroup
+};
+struct TileSumTable { TileSumJob job[kTileSumMaxJobs]; int n, wgs; };
+// appends a job (false when the table is full)
+bool tile_sum_add(TileSumTable& t, const float* pmean, int ld, int tiles, int R, long M, int C, float* out);
+hipError_t launch_tile_sums(const TileSumTable& t, hipStream_t st);
 // A training-mode batch norm as the per-channel map x*scale + shift.  With
 // acc set, scale and shift come from the batch sums acc [2][kAccSlots][C]
 // over M rows (mean, biased variance, rstd = 1/sqrt(var + eps),
@@ -273,7 +282,9 @@ hipError_t launch_relu_fwd(int dt, const void* x, void* y, long n, hipStream_t s
 hipError_t launch_relu_bwd(int dt, const void* dy, const void* x, void* dx, long n, bool accumulate, hipStream_t st);
 // dy (M x C, C a multiple of 4) := dy where y > 0, else 0, in place, y a
 // ReLU's stored output; pmean[tile][c] = the tile's mean of the masked
-// column c over stats_tiles(M, C) row tiles of stats_rows(M, C) rows.
+// column c over mask_tiles(M, C) row tiles of mask_rows(M, C) rows.
+int mask_rows(long M, int C);
+int mask_tiles(long M, int C);
 hipError_t launch_relu_mask_colsum(int dt, void* dy, const void* y, long M, int C, float* pmean, hipStream_t st);
 // Backward of y = concat(a, b) over channels where a and b are stored ReLU
 // outputs: da / db (null: not wanted) := the slices of dy, zero where ya / yb

@@ -105,41 +105,59 @@ __global__ __launch_bounds__(256) void stats_partial_k(const T* __restrict__ x, 
     }
 }
 
-// One workgroup per channel: thread j takes tiles j, j+256, ... and the 256
-// partial sums meet in a fixed-shape LDS tree.  mean = sum n_t m_t / M,
-// M2 = sum (M2_t + n_t (m_t - mean)^2).
-__device__ __forceinline__ double tree_sum256(double v, double* red) {
-    const int t = threadIdx.x;
-    red[t] = v;
+// Merges of per-tile partials in fp64 and a fixed order: a workgroup takes
+// four channels, thread (cl, tg) the tiles tg, tg + 64, ... of channel
+// 4 blockIdx.x + cl (whole 16-byte runs of a tile's row, eight tiles' loads in
+// flight), and the 64 thread sums meet in a fixed tree: shuffles over a wave,
+// then the four waves in order.  (One workgroup of 256 tile lanes per channel
+// spent its time in eight barriers a sum: 4.9 us for the statistics of 64
+// channels over 512 tiles, a launch being 2.3 us of that; now 3.)
+constexpr int kMergeC = 4, kMergeT = 64;
+template <int N>
+__device__ __forceinline__ void merge_tree(double (&v)[N]) {
+    __shared__ double red[4][kMergeC][N];
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+        for (int o = kMergeC; o < 64; o <<= 1) v[k] += __shfl_xor(v[k], o);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane < kMergeC)
+#pragma unroll
+        for (int k = 0; k < N; ++k) red[wave][lane][k] = v[k];
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
+    const int cl = threadIdx.x & (kMergeC - 1);
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = ((red[0][cl][k] + red[1][cl][k]) + red[2][cl][k]) + red[3][cl][k];
+}
+
+// out[c] = sum over tiles of n_t * mean_t (the column sum) for every job's
+// columns
+__global__ __launch_bounds__(256) void sum_from_tiles_k(const TileSumTable t) {
+    int j = 0;
+    while (j + 1 < t.n && (int)blockIdx.x >= t.job[j + 1].wg0) ++j;
+    const TileSumJob& J = t.job[j];
+    const int c = ((int)blockIdx.x - J.wg0) * kMergeC + (threadIdx.x & (kMergeC - 1));
+    double s[1] = {0.0};
+    if (c < J.C) {
+#pragma unroll 8
+        for (int k = threadIdx.x / kMergeC; k < J.tiles; k += kMergeT)
+            s[0] += (double)min((long)J.R, J.M - (long)k * J.R) * (double)J.pmean[(long)k * J.ld + c];
     }
-    const double r = red[0];
-    __syncthreads();
-    return r;
+    merge_tree<1>(s);
+    if (threadIdx.x < kMergeC && c < J.C) J.out[c] = (float)s[0];
 }
 
-// out[c] = sum over tiles of n_t * mean_t (the column sum), fixed order
-__global__ __launch_bounds__(256) void sum_from_tiles_k(const float* __restrict__ pmean, int ld, int T, int R, long M,
-                                                        float* __restrict__ out) {
-    __shared__ double red[256];
-    const int c = blockIdx.x;
-    double s = 0.0;
-    for (int t = threadIdx.x; t < T; t += 256)
-        s += (double)min((long)R, M - (long)t * R) * (double)pmean[(long)t * ld + c];
-    s = tree_sum256(s, red);
-    if (threadIdx.x == 0) out[c] = (float)s;
+bool tile_sum_add(TileSumTable& t, const float* pmean, int ld, int tiles, int R, long M, int C, float* out) {
+    if (t.n >= kTileSumMaxJobs) return false;
+    if (t.n == 0) t.wgs = 0;
+    t.job[t.n++] = TileSumJob{pmean, out, M, ld, tiles, R, C, t.wgs};
+    t.wgs += (C + kMergeC - 1) / kMergeC;
+    return true;
 }
 
-hipError_t launch_sum_from_tiles(const float* pmean, int T, int R, long M, int C, float* out, hipStream_t st) {
-    launch(sum_from_tiles_k, dim3(C), dim3(256), 0, st, pmean, C, T, R, M, out);
-    return hipGetLastError();
-}
-hipError_t launch_sum_from_tiles_ld(const float* pmean, int ld, int T, int R, long M, int C, float* out,
-                                    hipStream_t st) {
-    launch(sum_from_tiles_k, dim3(C), dim3(256), 0, st, pmean, ld, T, R, M, out);
+hipError_t launch_tile_sums(const TileSumTable& t, hipStream_t st) {
+    if (t.n == 0) return hipSuccess;
+    launch(sum_from_tiles_k, dim3((unsigned)t.wgs), dim3(256), 0, st, t);
     return hipGetLastError();
 }
 
@@ -153,31 +171,33 @@ hipError_t launch_stats_partial(int dt, const void* x, long M, int C, const BnSu
     return hipGetLastError();
 }
 
-// One workgroup per channel: thread j takes tiles j, j + 256, ... and the
-// partial sums meet in the fixed tree.  mean = sum n_t m_t / M,
-// M2 = sum (M2_t + n_t (m_t - mean)^2).
+// mean = sum n_t m_t / M and the biased variance sum (M2_t + n_t m_t^2) / M -
+// mean^2 of each channel, both sums about the first tile's mean K, so that the
+// subtraction cancels only the means' own spread
 __global__ __launch_bounds__(256) void stats_finalize_k(const float* __restrict__ pmean, const float* __restrict__ pm2,
                                                         TileCounts tc, long M, int C, const float* __restrict__ gamma,
                                                         const float* __restrict__ beta, float eps, float* aux) {
-    __shared__ double red[256];
-    const int c = blockIdx.x;
-    auto count = [&](int t) {
-        const int tr = tc.nc == 1 ? t : t / tc.nc, tq = t - tr * tc.nc;
-        return (double)min((long)tc.OH, tc.rows - (long)tr * tc.OH) * (double)min(tc.OW, tc.Wo - tq * tc.OW);
-    };
-    double s = 0.0;
-#pragma unroll 4
-    for (int t = threadIdx.x; t < tc.tiles; t += 256) s += count(t) * (double)pmean[(long)t * C + c];
-    const double mu = tree_sum256(s, red) / (double)M;
-    double q = 0.0;
-#pragma unroll 4
-    for (int t = threadIdx.x; t < tc.tiles; t += 256) {
-        const double d = (double)pmean[(long)t * C + c] - mu;
-        q += (double)pm2[(long)t * C + c] + count(t) * d * d;
+    const int c = blockIdx.x * kMergeC + (threadIdx.x & (kMergeC - 1));
+    double v[2] = {0.0, 0.0};
+    double K = 0.0;
+    if (c < C) {
+        K = (double)pmean[c];
+#pragma unroll 8
+        for (int t = threadIdx.x / kMergeC; t < tc.tiles; t += kMergeT) {
+            const int tr = tc.nc == 1 ? t : t / tc.nc, tq = t - tr * tc.nc;
+            const double n = (double)min((long)tc.OH, tc.rows - (long)tr * tc.OH) *
+                             (double)min(tc.OW, tc.Wo - tq * tc.OW);
+            const double d = (double)pmean[(long)t * C + c] - K;
+            v[0] += n * d;
+            v[1] += (double)pm2[(long)t * C + c] + n * d * d;
+        }
     }
-    q = tree_sum256(q, red);
-    if (threadIdx.x == 0) {
-        const double r = 1.0 / sqrt(q / (double)M + (double)eps);
+    merge_tree<2>(v);
+    if (threadIdx.x < kMergeC && c < C) {
+        const double dm = v[0] / (double)M, mu = K + dm;
+        double var = v[1] / (double)M - dm * dm;
+        var = var > 0.0 ? var : 0.0;
+        const double r = 1.0 / sqrt(var + (double)eps);
         const double sc = (double)gamma[c] * r;
         aux[c] = (float)mu;
         aux[C + c] = (float)r;
@@ -188,7 +208,7 @@ __global__ __launch_bounds__(256) void stats_finalize_k(const float* __restrict_
 
 hipError_t launch_stats_finalize(const float* pmean, const float* pm2, const TileCounts& tc, long M, int C,
                                  const float* gamma, const float* beta, float eps, float* aux, hipStream_t st) {
-    launch(stats_finalize_k, dim3(C), dim3(256), 0, st, pmean, pm2, tc, M, C, gamma, beta, eps, aux);
+    launch(stats_finalize_k, dim3((C + kMergeC - 1) / kMergeC), dim3(256), 0, st, pmean, pm2, tc, M, C, gamma, beta, eps, aux);
     return hipGetLastError();
 }
 
@@ -537,20 +557,20 @@ __global__ __launch_bounds__(256) void bn_bwd_finalize_k(const float* __restrict
                                                          float* coef1, const float* __restrict__ gamma2,
                                                          const float* __restrict__ rstd2, float* gg2, float* gb2,
                                                          float* coef2) {
-    __shared__ double red[256];
-    const int c = blockIdx.x;
+    const int c = blockIdx.x * kMergeC + (threadIdx.x & (kMergeC - 1));
     const bool dual = coef2 != nullptr;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-#pragma unroll 4
-    for (int t = threadIdx.x; t < T; t += 256) {
-        s0 += (double)p0[(long)t * C + c];
-        s1 += (double)p1[(long)t * C + c];
-        if (dual) s2 += (double)p2[(long)t * C + c];
+    double v[3] = {0.0, 0.0, 0.0};
+    if (c < C) {
+#pragma unroll 8
+        for (int t = threadIdx.x / kMergeC; t < T; t += kMergeT) {
+            v[0] += (double)p0[(long)t * C + c];
+            v[1] += (double)p1[(long)t * C + c];
+            if (dual) v[2] += (double)p2[(long)t * C + c];
+        }
     }
-    const double t0 = tree_sum256(s0, red);
-    const double t1 = tree_sum256(s1, red);
-    const double t2 = dual ? tree_sum256(s2, red) : 0.0;
-    if (threadIdx.x != 0) return;
+    merge_tree<3>(v);
+    if (threadIdx.x >= kMergeC || c >= C) return;
+    const double t0 = v[0], t1 = v[1], t2 = v[2];
     if (gg1) gg1[c] = (float)t1;
     if (gb1) gb1[c] = (float)t0;
     coef1[c] = gamma1[c] * rstd1[c];
@@ -595,7 +615,7 @@ hipError_t launch_bn_bwd_finalize(const float* p0, const float* p1, const float*
                                   const float* gamma1, const float* rstd1, float* gg1, float* gb1, float* coef1,
                                   const float* gamma2, const float* rstd2, float* gg2, float* gb2, float* coef2,
                                   hipStream_t st) {
-    launch(bn_bwd_finalize_k, dim3(C), dim3(256), 0, st, p0, p1, p2, T, M, C, gamma1, rstd1, gg1, gb1,
+    launch(bn_bwd_finalize_k, dim3((C + kMergeC - 1) / kMergeC), dim3(256), 0, st, p0, p1, p2, T, M, C, gamma1, rstd1, gg1, gb1,
                        coef1, gamma2, rstd2, gg2, gb2, coef2);
     return hipGetLastError();
 }
@@ -674,8 +694,46 @@ __global__ void copy_acc_k(const T* __restrict__ s, T* __restrict__ d, long n4, 
 // tile of stats_rows(M, C) rows the mean over the tile of each masked
 // column, pmean[tile][c] -- a conv bias gradient's partials, summed by
 // sum_from_tiles.  Tiling as stats_partial_k.
+// Row tiles of the masking passes: about 512 of them, of at least 16 rows
+int mask_rows(long M, int C) {
+    const long gy = ((C >> 2) + 255) / 256;
+    long r = (M * gy + 511) / 512;
+    return (int)(r < 16 ? 16 : r);
+}
+int mask_tiles(long M, int C) {
+    const int R = mask_rows(M, C);
+    return (int)((M + R - 1) / R);
+}
+
+// Rows r0 + lr, r0 + lr + rl, ... < r1, four at a time: their loads are issued
+// together, before any is masked and stored (one at a time, with a quarter of
+// the workgroups, concat_relu_bwd took 21 us on 32768 x 128 fp32, 2.4 TB/s)
+template <class T, class Store>
+__device__ __forceinline__ f4 mask_rows4(const T* g, long gs, const T* y, long ys, long r0, long r1, int rl,
+                                         Store store) {
+    f4 s = f4{0.f, 0.f, 0.f, 0.f};
+    for (long r = r0; r < r1; r += 4 * rl) {
+        f4 gv[4], yv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (r + u * rl < r1) {
+                gv[u] = ld4(g, (r + u * rl) * gs);
+                yv[u] = ld4(y, (r + u * rl) * ys);
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (r + u * rl < r1) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) gv[u][k] = yv[u][k] > 0.f ? gv[u][k] : 0.f;
+                store(r + u * rl, gv[u]);
+                s += gv[u];
+            }
+    }
+    return s;
+}
+
 template <class T>
-__global__ __launch_bounds__(256) void relu_mask_colsum_k(T* __restrict__ dy, const T* __restrict__ y, long M, int C,
+__global__ __launch_bounds__(256) void relu_mask_colsum_k(T* dy, const T* __restrict__ y, long M, int C,
                                                           int R, float* __restrict__ pmean) {
     __shared__ f4 red[256];
     const int tid = threadIdx.x;
@@ -689,14 +747,8 @@ __global__ __launch_bounds__(256) void relu_mask_colsum_k(T* __restrict__ dy, co
         const int q = qbase + tid % nq, lr = tid / nq;
         f4 s = f4{0.f, 0.f, 0.f, 0.f};
         if (lr < rl)
-            for (long r = r0 + lr; r < r1; r += rl) {
-                f4 g = ld4(dy, r * C4 + q);
-                const f4 v = ld4(y, r * C4 + q);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) g[k] = v[k] > 0.f ? g[k] : 0.f;
-                st4(dy, r * C4 + q, g);
-                s += g;
-            }
+            s = mask_rows4(dy + q * 4, C4, y + q * 4, C4, r0 + lr, r1, rl,
+                           [&](long r, f4 g) { st4(dy, r * C4 + q, g); });
         red[tid] = s;
         __syncthreads();
         if (tid < nq) {
@@ -710,8 +762,8 @@ __global__ __launch_bounds__(256) void relu_mask_colsum_k(T* __restrict__ dy, co
 
 hipError_t launch_relu_mask_colsum(int dt, void* dy, const void* y, long M, int C, float* pmean, hipStream_t st) {
     if (C % 4) return hipErrorInvalidValue;
-    const dim3 grid(stats_tiles(M, C), ((C >> 2) + 255) / 256);
-    const int R = stats_rows(M, C);
+    const dim3 grid(mask_tiles(M, C), ((C >> 2) + 255) / 256);
+    const int R = mask_rows(M, C);
     if (dt == DT_BF16)
         launch(relu_mask_colsum_k<bf16>, grid, dim3(256), 0, st, (bf16*)dy, (const bf16*)y, M, C, R, pmean);
     else
@@ -722,7 +774,7 @@ hipError_t launch_relu_mask_colsum(int dt, void* dy, const void* y, long M, int 
 // Backward of a channel concatenation whose two inputs are ReLU outputs
 // (each applied by its producing conv): the slices of dy, masked where the
 // stored ReLU output is zero, into da and db (null: not wanted), and per row
-// tile of stats_rows(M, C) rows the tile means of the masked columns,
+// tile of mask_rows(M, C) rows the tile means of the masked columns,
 // pmean[tile][c] over the concatenated channels c < C = ca + cb.
 template <class T>
 __global__ __launch_bounds__(256) void concat_relu_bwd_k(const T* __restrict__ dy, const T* __restrict__ ya,
@@ -745,14 +797,9 @@ __global__ __launch_bounds__(256) void concat_relu_bwd_k(const T* __restrict__ d
         const int qq = in_a ? q : q - A4, cq = in_a ? A4 : B4;
         f4 s = f4{0.f, 0.f, 0.f, 0.f};
         if (lr < rl)
-            for (long r = r0 + lr; r < r1; r += rl) {
-                f4 g = ld4(dy, r * C4 + q);
-                const f4 v = ld4(yv, r * cq + qq);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) g[k] = v[k] > 0.f ? g[k] : 0.f;
+            s = mask_rows4(dy + q * 4, C4, yv + qq * 4, cq, r0 + lr, r1, rl, [&](long r, f4 g) {
                 if (dv) st4(dv, r * cq + qq, g);
-                s += g;
-            }
+            });
         if (pmean) {
             red[tid] = s;
             __syncthreads();
@@ -770,8 +817,8 @@ hipError_t launch_concat_relu_bwd(int dt, const void* dy, const void* ya, const 
                                   int ca, int cb, float* pmean, hipStream_t st) {
     if ((ca | cb) & 3) return hipErrorInvalidValue;
     const int C = ca + cb;
-    const dim3 grid(stats_tiles(M, C), ((C >> 2) + 255) / 256);
-    const int R = stats_rows(M, C);
+    const dim3 grid(mask_tiles(M, C), ((C >> 2) + 255) / 256);
+    const int R = mask_rows(M, C);
     if (dt == DT_BF16)
         launch(concat_relu_bwd_k<bf16>, grid, dim3(256), 0, st, (const bf16*)dy, (const bf16*)ya, (const bf16*)yb,
                (bf16*)da, (bf16*)db, M, ca, cb, R, pmean);

@@ -70,6 +70,10 @@ struct Layer {
     // data; BN: its reduction accumulators (doubles [5][kAccSlots][C]: batch
     // sums of the forward, then sums of the backward)
     size_t act = 0, dact = 0, aux = 0, acc = 0;
+    // conv, concat: per-tile column means its bias gradient (a concat: those of
+    // the two convs whose ReLUs its backward applies) is summed from, kept
+    // until the backward's one launch of sums
+    size_t bpart = 0;
 };
 
 struct Plan {
@@ -645,6 +649,7 @@ struct lpp_ctx {
     const void* wdg(Worker& w, const Layer& Y) { return (const char*)w.wbuf + Y.wd_off * lpp_dt_size(); }
     size_t lpp_dt_size() const { return M.dt == lpp::DT_BF16 ? 2 : 4; }
     float* aux(Worker& w, int l) { return (float*)(w.ws + M.layers[l].aux); }
+    float* bpart(Worker& w, int l) { return (float*)(w.ws + M.layers[l].bpart); }
     double* acc_fwd(Worker& w, int l) { return (double*)(w.ws + M.layers[l].acc); }
     double* acc_bwd(Worker& w, int l) {
         return (double*)(w.ws + M.layers[l].acc) + 2L * lpp::kAccSlots * M.layers[l].out.c;
@@ -941,6 +946,23 @@ int run_backward(lpp_ctx* c, Worker& w, int partition) {
         woff = 0;
         return LPP_OK;
     };
+    // bias gradients are summed from their tile means by one launch at the end
+    // (when the table is full, and at the end)
+    lpp::TileSumTable sums{};
+    auto flush_sums = [&]() -> int {
+        if (sums.n == 0) return LPP_OK;
+        LAUNCH("bias_grad", 0.0, st, lpp::launch_tile_sums(sums, st));
+        sums.n = 0;
+        return LPP_OK;
+    };
+    auto add_sum = [&](const float* pmean, int ld, int tiles, int R, long rows, int C, float* out) -> int {
+        if (sums.n == lpp::kTileSumMaxJobs) {
+            int rc = flush_sums();
+            if (rc) return rc;
+        }
+        lpp::tile_sum_add(sums, pmean, ld, tiles, R, rows, C, out);
+        return LPP_OK;
+    };
     for (int gi = (int)M.groups.size() - 1; gi >= 0; --gi) {
         const Group& G = M.groups[gi];
         if (!pl.run[G.out]) continue;
@@ -958,10 +980,10 @@ int run_backward(lpp_ctx* c, Worker& w, int partition) {
             const bool bias_fused = G.relu >= 0 && !Y.pw && Y.L.bias && pl.wgrad[G.a];
             if (bias_fused && !G.premask) {
                 LAUNCH("relu", 3.0 * eb * Mo * Y.out.c, st,
-                       lpp::launch_relu_mask_colsum(dt, dy, c->act(w, G.out), Mo, Y.L.cout, w.ps0, st));
-                LAUNCH("bias_grad", 0.0, st,
-                       lpp::launch_sum_from_tiles(w.ps0, lpp::stats_tiles(Mo, Y.L.cout), lpp::stats_rows(Mo, Y.L.cout),
-                                                  Mo, Y.L.cout, w.g + Y.poff + Y.wcount, st));
+                       lpp::launch_relu_mask_colsum(dt, dy, c->act(w, G.out), Mo, Y.L.cout, c->bpart(w, G.a), st));
+                int rc = add_sum(c->bpart(w, G.a), Y.L.cout, lpp::mask_tiles(Mo, Y.L.cout),
+                                 lpp::mask_rows(Mo, Y.L.cout), Mo, Y.L.cout, w.g + Y.poff + Y.wcount);
+                if (rc) return rc;
             } else if (G.relu >= 0 && !G.premask) {
                 LAUNCH("relu", 3.0 * eb * Mo * Y.out.c, st,
                        lpp::launch_relu_bwd(dt, dy, c->act(w, G.out), dy, Mo * Y.out.c, false, st));
@@ -1021,12 +1043,12 @@ int run_backward(lpp_ctx* c, Worker& w, int partition) {
                                                   Y.L.pad, Y.wg, st));
                 if (Y.L.bias && !bias_fused) {
                     // column sums of dY, from per-tile means
-                    const lpp::BnSums tiles{nullptr, w.ps0, w.ps1, nullptr};
+                    const lpp::BnSums tiles{nullptr, c->bpart(w, G.a), w.ps1, nullptr};
                     LAUNCH("bias_grad", eb * Mo * Y.L.cout, st,
                            lpp::launch_stats_partial(dt, dy, Mo, Y.L.cout, tiles, st));
-                    LAUNCH("bias_grad", 0.0, st,
-                           lpp::launch_sum_from_tiles(w.ps0, lpp::stats_tiles(Mo, Y.L.cout), lpp::stats_rows(Mo, Y.L.cout), Mo, Y.L.cout,
-                                                      w.g + Y.poff + Y.wcount, st));
+                    int rc = add_sum(c->bpart(w, G.a), Y.L.cout, lpp::stats_tiles(Mo, Y.L.cout),
+                                     lpp::stats_rows(Mo, Y.L.cout), Mo, Y.L.cout, w.g + Y.poff + Y.wcount);
+                    if (rc) return rc;
                 }
             }
             if (dx0) {
@@ -1163,14 +1185,11 @@ int run_backward(lpp_ctx* c, Worker& w, int partition) {
                 LAUNCH("relu", (1.0 + (dx0 ? 2.0 : 0.0) * ca / C + (pl.din1[G.a] ? 2.0 : 0.0) * cb / C) * eb * Min * C, st,
                        lpp::launch_concat_relu_bwd(dt, dy, c->act(w, Y.L.in0), c->act(w, Y.L.in1), dx0,
                                                    pl.din1[G.a] ? c->dact(w, Y.L.in1) : nullptr, Min, ca, cb,
-                                                   (ba || bb) ? w.ps0 : nullptr, st));
-                const int T = lpp::stats_tiles(Min, C), R = lpp::stats_rows(Min, C);
-                if (ba)
-                    LAUNCH("bias_grad", 0.0, st,
-                           lpp::launch_sum_from_tiles_ld(w.ps0, C, T, R, Min, ca, w.g + Ca.poff + Ca.wcount, st));
-                if (bb)
-                    LAUNCH("bias_grad", 0.0, st,
-                           lpp::launch_sum_from_tiles_ld(w.ps0 + ca, C, T, R, Min, cb, w.g + Cb.poff + Cb.wcount, st));
+                                                   (ba || bb) ? c->bpart(w, G.a) : nullptr, st));
+                const int T = lpp::mask_tiles(Min, C), R = lpp::mask_rows(Min, C);
+                int rc = ba ? add_sum(c->bpart(w, G.a), C, T, R, Min, ca, w.g + Ca.poff + Ca.wcount) : LPP_OK;
+                if (!rc && bb) rc = add_sum(c->bpart(w, G.a) + ca, C, T, R, Min, cb, w.g + Cb.poff + Cb.wcount);
+                if (rc) return rc;
                 break;
             }
             if (dx0 || pl.din1[G.a])
@@ -1227,6 +1246,8 @@ int run_backward(lpp_ctx* c, Worker& w, int partition) {
     if (head && !loss_done)
         LAUNCH("head", 0.0, st,
                lpp::launch_head_bwd_w(nullptr, nullptr, N, 1, 1, nullptr, nullptr, w.loss + 1, w.loss, st));
+    int rc = flush_sums();
+    if (rc) return rc;
     return flush_reduce();
 }
 
@@ -1365,7 +1386,11 @@ int lpp_init(const lpp_model_desc* desc, int K, int P, const lpp_options* opt, l
         const long rin = (long)N * Y.in0.h * Y.in0.w;
         if (Y.L.op == LPP_BN) ps = std::max<long>(ps, (long)lpp::stats_tiles(rin, Y.out.c) * Y.out.c);
         if (Y.L.op == LPP_LINEAR) ps = std::max<long>(ps, (long)N * Y.L.cin);   // the wide head's dfeat
-        if (Y.L.op == LPP_CONCAT) ps = std::max<long>(ps, (long)lpp::stats_tiles(rows_out, Y.out.c) * Y.out.c);
+        if (Y.L.op == LPP_CONCAT) Y.bpart = take(sizeof(float) * lpp::mask_tiles(rows_out, Y.out.c) * (size_t)Y.out.c);
+        if (Y.L.op == LPP_CONV && !Y.pw && Y.L.bias)
+            Y.bpart = take(sizeof(float) *
+                           std::max(lpp::mask_tiles(rows_out, Y.out.c), lpp::stats_tiles(rows_out, Y.out.c)) *
+                           (size_t)Y.out.c);
         if (Y.L.op == LPP_CONV && !Y.pw) {
             lpp::ConvGeom g{N, Y.in0.h, Y.in0.w, Y.cin_p, Y.out.h, Y.out.w, Y.L.cout, Y.L.k, Y.L.k, Y.L.stride,
                             Y.L.pad};
