@@ -1076,6 +1076,73 @@ __global__ __launch_bounds__(256) void maxpool_bwd_k(const T* __restrict__ dy, c
     stv<VW>(dx + (long)idx * VW, s);
 }
 
+// The same for 3x3 windows of stride 2 and padding 1: a thread takes a 2x2
+// block of input pixels, whose windows are (i, i + 1) x (j, j + 1): row 2i
+// lies in window row i (tap row 1), row 2i + 1 in i (2) and i + 1 (0).  Every
+// window is read by four threads instead of nine, its loads issued together,
+// and each pixel's sum keeps the (p, q) order.  (64 x 112x112x64 bf16: 64 us
+// with a pixel a thread, 34 us so.)
+template <class T, int VW>
+__global__ __launch_bounds__(256) void maxpool_bwd_s2_k(const T* __restrict__ dy, const uint8_t* __restrict__ arg,
+                                                        T* __restrict__ dx, int Nb, int H, int W, int C, int Ho,
+                                                        int Wo, int acc) {
+    const int CV = C / VW, Hb = (H + 1) >> 1, Wb = (W + 1) >> 1;
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx >= Nb * Hb * Wb * CV) return;
+    const int cv = idx % CV;
+    int t = idx / CV;
+    const int j = t % Wb;
+    t /= Wb;
+    const int i = t % Hb, n = t / Hb;
+    float g[4][VW];
+    uint8_t a[4][VW];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int p = i + (u >> 1), q = j + (u & 1);
+        const bool in = p < Ho && q < Wo;
+        const long o = (((long)n * Ho + (in ? p : 0)) * Wo + (in ? q : 0)) * C + cv * VW;
+        if constexpr (VW == 8) {
+            uint2 v = *(const uint2*)(arg + o);
+            if (!in) v = uint2{0xffffffffu, 0xffffffffu};   // no tap
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                a[u][e] = (uint8_t)(v.x >> (8 * e));
+                a[u][4 + e] = (uint8_t)(v.y >> (8 * e));
+            }
+        } else {
+            uint32_t v = *(const uint32_t*)(arg + o);
+            if (!in) v = 0xffffffffu;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[u][e] = (uint8_t)(v >> (8 * e));
+        }
+        ldv<VW>(dy + o, g[u]);
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const int h = 2 * i + (x >> 1), w = 2 * j + (x & 1);
+        if (h >= H || w >= W) continue;
+        float s[VW];
+#pragma unroll
+        for (int e = 0; e < VW; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = (x >> 1) + 1 - 2 * (u >> 1), c = (x & 1) + 1 - 2 * (u & 1);
+            if (r < 0 || c < 0) continue;          // the window lies past the pixel
+#pragma unroll
+            for (int e = 0; e < VW; ++e)
+                if (a[u][e] == r * 3 + c) s[e] += g[u][e];
+        }
+        const long o = (((long)n * H + h) * W + w) * C + cv * VW;
+        if (acc) {
+            float d[VW];
+            ldv<VW>(dx + o, d);
+#pragma unroll
+            for (int e = 0; e < VW; ++e) s[e] = d[e] + s[e];
+        }
+        stv<VW>(dx + o, s);
+    }
+}
+
 // Channel means over the HW pixels of an image.  A workgroup takes one image
 // and VL channel vectors (VW consecutive channels), 256 / VL threads to a
 // vector: each sums every (256 / VL)-th pixel, four loads in flight, and the
@@ -1173,6 +1240,16 @@ hipError_t launch_maxpool_bwd(int dt, const void* dy, const uint8_t* arg, void* 
                               int Ho, int Wo, int k, int stride, int pad, bool accumulate, hipStream_t st) {
     const long total = (long)Nb * H * W * C;
     if (total >= 0x7fffffffL || (long)Nb * Ho * Wo * C >= 0x7fffffffL) return hipErrorInvalidValue;
+    if (k == 3 && stride == 2 && pad == 1 && C % (dt == DT_BF16 ? 8 : 4) == 0) {
+        const long blocks = (long)Nb * ((H + 1) / 2) * ((W + 1) / 2) * C;
+        if (dt == DT_BF16)
+            launch(maxpool_bwd_s2_k<bf16, 8>, dim3(nblocks(blocks / 8, 256)), dim3(256), 0, st, (const bf16*)dy, arg,
+                   (bf16*)dx, Nb, H, W, C, Ho, Wo, (int)accumulate);
+        else
+            launch(maxpool_bwd_s2_k<float, 4>, dim3(nblocks(blocks / 4, 256)), dim3(256), 0, st, (const float*)dy, arg,
+                   (float*)dx, Nb, H, W, C, Ho, Wo, (int)accumulate);
+        return hipGetLastError();
+    }
     if (dt == DT_BF16) {
         if (C % 8 == 0)
             launch(maxpool_bwd_k<bf16, 8>, dim3(nblocks(total / 8, 256)), dim3(256), 0, st, (const bf16*)dy, arg,
