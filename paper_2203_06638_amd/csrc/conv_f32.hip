@@ -486,6 +486,127 @@ static bool box_pick(BoxGeom& out, int Nb, int Hper, int Wo, int ext, int step, 
 // Bytes of a tensor of n floats addressable with the kernels' 32-bit offsets
 static bool buf_fits(double n) { return 4.0 * n < 2147483648.0; }
 
+// Epilogue of a box tile: bias, the output block through LDS, the store (set,
+// add, ReLU) and the batch-norm sums (STATS).
+template <int MODE, int TM, int TN, bool STATS>
+__device__ __forceinline__ void box_store(f4 (&acc)[TM][TN], float* lds, const float* __restrict__ bias,
+                                          float* __restrict__ Y, const ConvGeom& g, const BoxGeom& t, int accumulate,
+                                          const BnSums& sums, const BnBwdSum& bs, int R0, int w0, int ohv, int owv,
+                                          int n0) {
+    constexpr int BN = TN * 16;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int gi = lane >> 4, li = lane & 15;
+    if (bias) {
+#pragma unroll
+        for (int y = 0; y < TN; ++y) {
+            const int n = n0 + y * 16 + li;
+            const float bb = n < g.Ncols ? bias[n] : 0.f;
+#pragma unroll
+            for (int x = 0; x < TM; ++x)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[x][y][i] += bb;
+        }
+    }
+    // the wave's TM*16 x TN*16 output block, transposed through LDS so that
+    // every lane stores whole float4 channel quads of one pixel
+    f4 bs0 = f4{0.f, 0.f, 0.f, 0.f}, bs1 = bs0;   // data gradient with STATS: sum gm, sum gm*xhat
+    {
+        constexpr int OP = TN * 16 + 4;           // LDS pitch of a pixel row
+        float* Ot = lds + wave * (TM * 16 * OP);
+#pragma unroll
+        for (int x = 0; x < TM; ++x)
+#pragma unroll
+            for (int y = 0; y < TN; ++y)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) Ot[(x * 16 + gi * 4 + i) * OP + y * 16 + li] = acc[x][y][i];
+        __builtin_amdgcn_wave_barrier();          // a wave's LDS accesses execute in order
+        constexpr int QPP = TN * 4;               // float4 quads per pixel of the block
+        const int qd = lane % QPP, n = n0 + qd * 4;   // (64 % QPP == 0: a lane keeps one channel quad)
+        f4 bmu{}, brs{}, bsc{}, bsh{};
+        if (MODE == CONV_DGRAD && STATS && n < g.Ncols) {
+            bmu = *(const f4*)(bs.aux + n);
+            brs = *(const f4*)(bs.aux + g.Ncols + n);
+            bsc = *(const f4*)(bs.aux + 2 * g.Ncols + n);
+            bsh = *(const f4*)(bs.aux + 3 * g.Ncols + n);
+        }
+#pragma unroll
+        for (int k = 0; k < TM * 16 * QPP / 64; ++k) {
+            const int pl = (k * 64 + lane) / QPP;
+            const int p = wave * TM * 16 + pl;
+            const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+            if (oh < ohv && ow < owv && n < g.Ncols) {
+                const long e = ((long)(R0 + oh) * t.Wo + w0 + ow) * g.Ncols + n;
+                const f4 v = *(const f4*)(Ot + pl * OP + qd * 4);
+                f4* o = (f4*)(Y + e);
+                const f4 tot = accumulate == kStoreAdd ? *o + v : (accumulate == kStoreRelu ? relu4(v) : v);
+                *o = tot;
+                if (MODE == CONV_DGRAD && STATS) {
+                    // gm = the stored gradient where the forward's ReLU passed
+                    // (its output y > 0, or fma(x, scale, shift) > 0), xhat of the BN input
+                    const f4 x = *(const f4*)(bs.x1 + e);
+                    const f4 yv = bs.y ? *(const f4*)(bs.y + e) : f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const bool pass = bs.y ? yv[j] > 0.f : __builtin_fmaf(x[j], bsc[j], bsh[j]) > 0.f;
+                        const float gm = pass ? tot[j] : 0.f;
+                        bs0[j] += gm;
+                        bs1[j] += gm * ((x[j] - bmu[j]) * brs[j]);
+                    }
+                }
+            }
+        }
+    }
+    if constexpr (MODE == CONV_DGRAD && STATS) {
+        // lanes of one channel quad summed by a fixed xor tree, then the four waves in order
+        constexpr int QPP = TN * 4;
+#pragma unroll
+        for (int o = QPP; o < 64; o <<= 1) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                bs0[j] += __shfl_xor(bs0[j], o);
+                bs1[j] += __shfl_xor(bs1[j], o);
+            }
+        }
+        __shared__ f4 bred[4][2][QPP];
+        if (lane < QPP) {
+            bred[wave][0][lane] = bs0;
+            bred[wave][1][lane] = bs1;
+        }
+        __syncthreads();
+        if (tid < 2 * BN) {
+            const int k = tid / BN, cl = tid - k * BN, c = n0 + cl;
+            float s = bred[0][k][cl >> 2][cl & 3];
+            for (int w = 1; w < 4; ++w) s += bred[w][k][cl >> 2][cl & 3];
+            if (c < g.Ncols) {
+                if (sums.acc) acc_add(sums.acc, k, (int)blockIdx.x, g.Ncols, c, (double)s);
+                else (k ? sums.p1 : sums.p0)[(long)blockIdx.x * g.Ncols + c] = s;
+            }
+        }
+    }
+    if constexpr (MODE == CONV_FWD && STATS) {
+        __shared__ float red[4][3][BN];
+        const auto store = [&](int c, float n, float mu, float m2) {
+            if (n0 + c < g.Ncols) tile_moments_store(sums, (int)blockIdx.x, g.Ncols, n0 + c, n, mu, m2);
+        };
+        if (ohv * owv == TM * 64) {
+            tile_moments<TM, TN, 4, BN, true>(acc, wave, 0, [](int, int) { return true; }, red, store);
+        } else {
+            // slots of this lane's accumulator rows that hold a pixel
+            unsigned ok = 0;
+#pragma unroll
+            for (int x = 0; x < TM; ++x)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int p = (wave * TM + x) * 16 + gi * 4 + i;
+                    const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+                    if (oh < ohv && ow < owv) ok |= 1u << (x * 4 + i);
+                }
+            tile_moments<TM, TN, 4, BN, false>(
+                acc, wave, 0, [&](int x, int i) { return ((ok >> (x * 4 + i)) & 1) != 0; }, red, store);
+        }
+    }
+}
+
 // Spatially tiled convolution (3x3 and 1x1 passes with Cs % 4 == 0: forward
 // with any stride, stride-1 data gradients; the data gradient of a stride-1
 // conv is a forward conv of dY with the filter flipped and padding KS-1-pad).
@@ -631,115 +752,7 @@ __global__ __launch_bounds__(256) void conv_tile_f32(const float* __restrict__ s
         lds_barrier();
     }
 
-    if (bias) {
-#pragma unroll
-        for (int y = 0; y < TN; ++y) {
-            const int n = n0 + y * 16 + li;
-            const float bb = n < g.Ncols ? bias[n] : 0.f;
-#pragma unroll
-            for (int x = 0; x < TM; ++x)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[x][y][i] += bb;
-        }
-    }
-    // the wave's TM*16 x TN*16 output block, transposed through LDS so that
-    // every lane stores whole float4 channel quads of one pixel
-    f4 bs0 = f4{0.f, 0.f, 0.f, 0.f}, bs1 = bs0;   // data gradient with STATS: sum gm, sum gm*xhat
-    {
-        constexpr int OP = TN * 16 + 4;           // LDS pitch of a pixel row
-        float* Ot = lds + wave * (TM * 16 * OP);
-#pragma unroll
-        for (int x = 0; x < TM; ++x)
-#pragma unroll
-            for (int y = 0; y < TN; ++y)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) Ot[(x * 16 + gi * 4 + i) * OP + y * 16 + li] = acc[x][y][i];
-        __builtin_amdgcn_wave_barrier();          // a wave's LDS accesses execute in order
-        constexpr int QPP = TN * 4;               // float4 quads per pixel of the block
-        const int qd = lane % QPP, n = n0 + qd * 4;   // (64 % QPP == 0: a lane keeps one channel quad)
-        f4 bmu{}, brs{}, bsc{}, bsh{};
-        if (MODE == CONV_DGRAD && STATS && n < g.Ncols) {
-            bmu = *(const f4*)(bs.aux + n);
-            brs = *(const f4*)(bs.aux + g.Ncols + n);
-            bsc = *(const f4*)(bs.aux + 2 * g.Ncols + n);
-            bsh = *(const f4*)(bs.aux + 3 * g.Ncols + n);
-        }
-#pragma unroll
-        for (int k = 0; k < TM * 16 * QPP / 64; ++k) {
-            const int pl = (k * 64 + lane) / QPP;
-            const int p = wave * TM * 16 + pl;
-            const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
-            if (oh < ohv && ow < owv && n < g.Ncols) {
-                const long e = ((long)(R0 + oh) * t.Wo + w0 + ow) * g.Ncols + n;
-                const f4 v = *(const f4*)(Ot + pl * OP + qd * 4);
-                f4* o = (f4*)(Y + e);
-                const f4 tot = accumulate == kStoreAdd ? *o + v : (accumulate == kStoreRelu ? relu4(v) : v);
-                *o = tot;
-                if (MODE == CONV_DGRAD && STATS) {
-                    // gm = the stored gradient where the forward's ReLU passed
-                    // (its output y > 0, or fma(x, scale, shift) > 0), xhat of the BN input
-                    const f4 x = *(const f4*)(bs.x1 + e);
-                    const f4 yv = bs.y ? *(const f4*)(bs.y + e) : f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const bool pass = bs.y ? yv[j] > 0.f : __builtin_fmaf(x[j], bsc[j], bsh[j]) > 0.f;
-                        const float gm = pass ? tot[j] : 0.f;
-                        bs0[j] += gm;
-                        bs1[j] += gm * ((x[j] - bmu[j]) * brs[j]);
-                    }
-                }
-            }
-        }
-    }
-    if constexpr (MODE == CONV_DGRAD && STATS) {
-        // lanes of one channel quad summed by a fixed xor tree, then the four waves in order
-        constexpr int QPP = TN * 4;
-#pragma unroll
-        for (int o = QPP; o < 64; o <<= 1) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bs0[j] += __shfl_xor(bs0[j], o);
-                bs1[j] += __shfl_xor(bs1[j], o);
-            }
-        }
-        __shared__ f4 bred[4][2][QPP];
-        if (lane < QPP) {
-            bred[wave][0][lane] = bs0;
-            bred[wave][1][lane] = bs1;
-        }
-        __syncthreads();
-        if (tid < 2 * BN) {
-            const int k = tid / BN, cl = tid - k * BN, c = n0 + cl;
-            float s = bred[0][k][cl >> 2][cl & 3];
-            for (int w = 1; w < 4; ++w) s += bred[w][k][cl >> 2][cl & 3];
-            if (c < g.Ncols) {
-                if (sums.acc) acc_add(sums.acc, k, (int)blockIdx.x, g.Ncols, c, (double)s);
-                else (k ? sums.p1 : sums.p0)[(long)blockIdx.x * g.Ncols + c] = s;
-            }
-        }
-    }
-    if constexpr (MODE == CONV_FWD && STATS) {
-        __shared__ float red[4][3][BN];
-        const auto store = [&](int c, float n, float mu, float m2) {
-            if (n0 + c < g.Ncols) tile_moments_store(sums, (int)blockIdx.x, g.Ncols, n0 + c, n, mu, m2);
-        };
-        if (ohv * owv == TM * 64) {
-            tile_moments<TM, TN, 4, BN, true>(acc, wave, 0, [](int, int) { return true; }, red, store);
-        } else {
-            // slots of this lane's accumulator rows that hold a pixel
-            unsigned ok = 0;
-#pragma unroll
-            for (int x = 0; x < TM; ++x)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int p = (wave * TM + x) * 16 + gi * 4 + i;
-                    const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
-                    if (oh < ohv && ow < owv) ok |= 1u << (x * 4 + i);
-                }
-            tile_moments<TM, TN, 4, BN, false>(
-                acc, wave, 0, [&](int x, int i) { return ((ok >> (x * 4 + i)) & 1) != 0; }, red, store);
-        }
-    }
+    box_store<MODE, TM, TN, STATS>(acc, lds, bias, Y, g, t, accumulate, sums, bs, R0, w0, ohv, owv, n0);
 }
 
 struct TileCfg { int tm, tn, tiles; BoxGeom t; size_t lds; };
@@ -814,6 +827,136 @@ static hipError_t dispatch_tile(const float* src, const float* B, const float* b
     if (c.tn == 2) return launch_tile<MODE, 1, 2, 2>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);
     if (c.tm == 2) return launch_tile<MODE, 1, 2, 1>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);
     return launch_tile<MODE, 1, 1, 1>(src, B, bias, Y, g, c, acc, stats, inbn, bsv, st);
+}
+
+// Forward pass of a stem (a source of 4 stored channels: the padded image).
+// Four consecutive pixels of a row are 16 consecutive floats, so an MFMA group
+// of 16 k-values is four taps of a filter row: a KS x KS filter takes
+// KS * NSG groups (NSG = ceil(KS / 4); 3x3: 3, 7x7: 14) instead of one per tap
+// with three quarters of the channels empty.  Taps past the filter row read a
+// zero quad (and meet a zero weight).  The box's input, one quad a pixel, and
+// the whole filter slice are staged once; several workgroups to a compute unit
+// overlap their phases, so registers are held to what five allow (without the
+// bound the compiler hoists every LDS read, two workgroups fit, and the passes
+// below take 32 and 82 us).  128 x 32x32, 4 -> 96: 35 us on the gather kernel,
+// 22 here; 16 x 224x224, 7x7/2, 4 -> 64: 88, 68.
+template <int KS, int TN, bool STATS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void conv_stem_f32(const float* __restrict__ src, const float* __restrict__ B,
+                                                     const float* __restrict__ bias, float* __restrict__ Y, ConvGeom g,
+                                                     BoxGeom t, int accumulate, BnSums sums) {
+    constexpr int TM = 2, BN = TN * 16, NSG = (KS + 3) / 4, LDW = 20;
+    constexpr int WR = BN * KS * NSG;                 // LDS rows of the filter slice
+    constexpr int NW = (WR * 4 + 255) / 256;
+    extern __shared__ float lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int gi = lane >> 4, li = lane & 15;
+    const int tr = box_div((int)blockIdx.x, t.nc_inv), tc = (int)blockIdx.x - tr * t.nc;
+    const int R0 = tr * t.OH, w0 = tc * t.OW;
+    const int ohv = min(t.OH, t.rows - R0), owv = min(t.OW, t.Wo - w0);
+    const int n0 = blockIdx.y * BN;
+    const int P0 = box_prow(t, R0);
+    const int npix = t.IH * t.IW;
+    float* Ws = lds;                                  // [WR][LDW]
+    float* Xs = lds + WR * LDW;                       // [npix][4], then a zero quad
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(src, (long)g.Nb * g.Hs * g.Ws * 4);
+    const __amdgpu_buffer_rsrc_t wr = buf_rsrc(B, (long)g.Ncols * KS * KS * 4);
+    f4 xv[kTileBatches], wv[NW];
+#pragma unroll
+    for (int u = 0; u < kTileBatches; ++u)
+        if (u * 256 < npix) {
+            const int pix = tid + u * 256;
+            const int ih = box_div(pix, t.IW_inv), iw = pix - ih * t.IW;
+            const int pr = P0 + ih;
+            const int n = box_div(pr, t.Hp_inv), h = pr - n * t.Hp - t.pad_eff, w = w0 * g.stride + iw - t.pad_eff;
+            const bool ok = ih < t.IH && n < g.Nb && h >= 0 && h < g.Hs && w >= 0 && w < g.Ws;
+            xv[u] = buf_load4(xr, ok ? (unsigned)((n * g.Hs + h) * g.Ws + w) * 16u : kNoLoad, 0);
+        }
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+        const int e = tid + u * 256, row = e >> 2;    // (channel, filter row, group)
+        const int nl = row / (KS * NSG), rg = row - nl * (KS * NSG), r = rg / NSG;
+        const int s = (rg - r * NSG) * 4 + (e & 3);
+        wv[u] = buf_load4(wr, nl < BN && n0 + nl < g.Ncols && s < KS ? (unsigned)(((n0 + nl) * KS + r) * KS + s) * 16u
+                                                                     : kNoLoad, 0);
+    }
+    int abase[TM];
+#pragma unroll
+    for (int x = 0; x < TM; ++x) {
+        const int p = (wave * TM + x) * 16 + li;
+        const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+        const bool ok = oh < ohv && ow < owv;
+        abase[x] = ((ok ? box_prow(t, R0 + oh) - P0 : 0) * t.IW + (ok ? ow * g.stride : 0) + gi) * 4;
+    }
+#pragma unroll
+    for (int u = 0; u < kTileBatches; ++u)
+        if (u * 256 < npix && tid + u * 256 < npix) *(f4*)(Xs + (tid + u * 256) * 4) = xv[u];
+    if (tid == 0) *(f4*)(Xs + npix * 4) = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < NW; ++u)
+        if (tid + u * 256 < WR * 4) *(f4*)(Ws + ((tid + u * 256) >> 2) * LDW + (tid & 3) * 4) = wv[u];
+    f4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();
+#pragma unroll
+    for (int r = KS - 1; r >= 0; --r)
+#pragma unroll
+        for (int sg = 0; sg < NSG; ++sg) {
+            // lanes whose tap 4 sg + gi lies past the filter row
+            const bool past = sg == NSG - 1 && (sg * 4 + gi) >= KS;
+            f4 a[TM], b[TN];
+#pragma unroll
+            for (int x = 0; x < TM; ++x) a[x] = *(const f4*)(Xs + (past ? npix * 4 : abase[x] + (r * t.IW + sg * 4) * 4));
+#pragma unroll
+            for (int y = 0; y < TN; ++y)
+                b[y] = *(const f4*)(Ws + (((y * 16 + li) * KS + r) * NSG + sg) * LDW + gi * 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int x = 0; x < TM; ++x)
+#pragma unroll
+                    for (int y = 0; y < TN; ++y) acc[x][y] = mfma16x16x4(a[x][j], b[y][j], acc[x][y]);
+        }
+    __syncthreads();
+    box_store<CONV_FWD, TM, TN, STATS>(acc, lds, bias, Y, g, t, accumulate, sums, BnBwdSum{}, R0, w0, ohv, owv, n0);
+}
+
+// Box of a stem's forward pass (128 slots; 32 output channels, 16 where there
+// are no more), or false when the kernel does not take it.
+struct StemCfg { int tn, tiles; BoxGeom t; size_t lds; };
+static bool pick_stem(const ConvGeom& g, StemCfg& c) {
+    if (g.Cs != 4 || g.Ncols % 4 || g.R != g.S || (g.R != 3 && g.R != 7)) return false;
+    if (!buf_fits((double)g.Nb * g.Hs * g.Ws * 4)) return false;
+    // (box_pick counts batches of 64 pixels with a quad group each; here a batch is 256 pixels)
+    if (!box_pick(c.t, g.Nb, g.Ho, g.Wo, g.R, g.stride, g.pad, 128, 1, 4 * kTileBatches)) return false;
+    c.tn = g.Ncols > 16 ? 2 : 1;
+    c.tiles = box_tiles(c.t);
+    c.lds = sizeof(float) * std::max<size_t>((size_t)c.tn * 16 * g.R * ((g.R + 3) / 4) * 20 +
+                                                 ((size_t)c.t.IH * c.t.IW + 1) * 4,
+                                             (size_t)4 * 32 * (c.tn * 16 + 4));
+    return true;
+}
+
+template <int KS, int TN>
+static hipError_t launch_stem(const float* src, const float* B, const float* bias, float* Y, const ConvGeom& g,
+                              const StemCfg& c, int acc, const BnSums* stats, hipStream_t st) {
+    dim3 grid((unsigned)c.tiles, (unsigned)((g.Ncols + TN * 16 - 1) / (TN * 16)));
+    const BnSums sm = stats ? *stats : BnSums{};
+    if (stats) launch((conv_stem_f32<KS, TN, true>), grid, dim3(256), c.lds, st, src, B, bias, Y, g, c.t, acc, sm);
+    else launch((conv_stem_f32<KS, TN, false>), grid, dim3(256), c.lds, st, src, B, bias, Y, g, c.t, acc, sm);
+    return hipGetLastError();
+}
+
+static hipError_t dispatch_stem(const float* src, const float* B, const float* bias, float* Y, const ConvGeom& g,
+                                const StemCfg& c, int acc, const BnSums* stats, hipStream_t st) {
+    if (g.R == 3) {
+        if (c.tn == 2) return launch_stem<3, 2>(src, B, bias, Y, g, c, acc, stats, st);
+        return launch_stem<3, 1>(src, B, bias, Y, g, c, acc, stats, st);
+    }
+    if (c.tn == 2) return launch_stem<7, 2>(src, B, bias, Y, g, c, acc, stats, st);
+    return launch_stem<7, 1>(src, B, bias, Y, g, c, acc, stats, st);
 }
 
 // Data gradient of a stride-2 conv, split by output parity.  dX pixel
@@ -1039,6 +1182,10 @@ static hipError_t launch_mode(const float* src, const float* B, const float* bia
     TileCfg tc;
     if (pick_tile(MODE, g, tc)) return dispatch_tile<MODE>(src, B, bias, Y, g, tc, acc, stats, inbn, bsv, st);
     if (inbn || bsv) return hipErrorInvalidValue;   // folding and backward sums need the spatial kernel
+    if (MODE == CONV_FWD) {
+        StemCfg sc;
+        if (pick_stem(g, sc)) return dispatch_stem(src, B, bias, Y, g, sc, acc, stats, st);
+    }
     if (MODE == CONV_DGRAD) {
         S2Cfg sc;
         if (pick_s2(g, sc)) return dispatch_s2(src, B, Y, g, sc, acc, st);
@@ -1069,6 +1216,8 @@ static hipError_t launch_mode(const float* src, const float* B, const float* bia
 TileCounts conv_tile_counts(const ConvGeom& g) {
     TileCfg c;
     if (pick_tile(CONV_FWD, g, c)) return TileCounts{c.tiles, c.t.OH, c.t.OW, c.t.nc, c.t.rows, c.t.Wo};
+    StemCfg sc;
+    if (pick_stem(g, sc)) return TileCounts{sc.tiles, sc.t.OH, sc.t.OW, sc.t.nc, sc.t.rows, sc.t.Wo};
     return tile_counts_rows((long)g.Nb * g.Ho * g.Wo, pick_cfg(g).bm);
 }
 
@@ -1090,7 +1239,7 @@ int conv_dgrad_sum_tiles(const ConvGeom& gd) {
 
 bool conv_fold_ok(const ConvGeom& g, const WgradPlan& p) {
     TileCfg tc;
-    return g.Cs <= kFoldMaxC && p.tile && pick_tile(CONV_FWD, g, tc);
+    return g.Cs <= kFoldMaxC && p.tile == 1 && pick_tile(CONV_FWD, g, tc);
 }
 
 // ------------------------------------------------------------------------
@@ -1388,9 +1537,7 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
 }
 
 // Boxes of the spatially tiled weight gradient, or false when it does not
-// apply (the GEMM-style kernel takes those passes, and a few input channels to
-// many outputs, the stems, whose MFMA columns would be mostly padding: 128 x
-// 32x32, 4 -> 96 channels 38 us here, 36 there).  At most 768 workgroups, one
+// apply (the GEMM-style kernel takes those passes).  At most 768 workgroups, one
 // round of three to a compute unit: each takes a single box of 256 slots where
 // that gives at least 512 workgroups, else a run of boxes of 128 slots, or of
 // 64 where 128 leave fewer than 512 (measured over 512-1536 workgroups and all
@@ -1399,7 +1546,7 @@ struct WgTileCfg { int ng, tiles, per, splits; BoxGeom t; size_t lds; };
 static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride,
                             int pad, WgTileCfg& out) {
     if (Cin_p % 4 || Cout % 4 || R != S || (R != 1 && R != 3) || (stride != 1 && stride != 2)) return false;
-    if (Cin_p < 16 && Cout > 32) return false;
+    if (Cin_p < 16 && Cout > 32) return false;   // mostly empty MFMA columns: the GEMM kernel is as fast
     if (!buf_fits((double)Nb * Hi * Wi * Cin_p) || !buf_fits((double)Nb * Ho * Wo * Cout)) return false;
     const long blocks = (long)((Cout + 15) / 16) * ((Cin_p + 15) / 16);
     bool found = false;
@@ -1421,13 +1568,153 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
     return found;
 }
 
+// Weight gradient of a stem (4 stored input channels): as conv_wgrad_tile_f32,
+// with 16 MFMA columns = four taps of a filter row x 4 channels (KS * NSG
+// column tiles: 3x3 three, 7x7 fourteen) read from LDS as they lie, 16
+// consecutive floats from the pixel of the first tap.  Columns past the filter
+// row are formed and dropped.  (128 x 32x32, 4 -> 16: 10.3 us with a column
+// tile per tap, 7.4 here; 4 -> 96: 36, 19; 7x7/2, 4 -> 64: 97, 82.)
+template <int KS, int NG, int ST>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 3 ? 4 : 3, 8)))
+void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__ X,
+                                                           float* __restrict__ part, WgArgs a, BoxGeom t, int tiles,
+                                                           int per) {
+    constexpr int NSG = (KS + 3) / 4, RG = KS * NSG, LDW = 20, JST = ST * 4, TP = NG * 64;
+    extern __shared__ float lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int gi = lane >> 4, li = lane & 15, q = tid & 3;
+    const int co0 = blockIdx.y * 16;
+    const int npix = t.IH * t.IW;
+    float* Ds = lds;                          // [TP][LDW] dY of the box, 16 channels
+    float* Xs = lds + TP * LDW;               // [npix][4] input, 16 floats of slack behind
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(X, (long)a.Nb * a.Hi * a.Wi * 4);
+    const __amdgpu_buffer_rsrc_t dr = buf_rsrc(dY, (long)a.Nb * a.Ho * a.Wo * a.Cout);
+    f4 xv[kTileBatches], dv[NG];
+    auto load = [&](int tile) {
+        const int tr = box_div(tile, t.nc_inv), tc = tile - tr * t.nc;
+        const int R0 = tr * t.OH, w0 = tc * t.OW, P0 = box_prow(t, R0);
+        const int ohv = min(t.OH, t.rows - R0), owv = min(t.OW, t.Wo - w0);
+#pragma unroll
+        for (int u = 0; u < kTileBatches; ++u)
+            if (u * 256 < npix) {
+                const int pix = tid + u * 256;
+                const int ih = box_div(pix, t.IW_inv), iw = pix - ih * t.IW;
+                const int pr = P0 + ih;
+                const int n = box_div(pr, t.Hp_inv), h = pr - n * t.Hp - t.pad_eff, w = w0 * ST + iw - t.pad_eff;
+                const bool ok = ih < t.IH && n < a.Nb && h >= 0 && h < a.Hi && w >= 0 && w < a.Wi;
+                xv[u] = buf_load4(xr, ok ? (unsigned)((n * a.Hi + h) * a.Wi + w) * 16u : kNoLoad, 0);
+            }
+#pragma unroll
+        for (int u = 0; u < NG; ++u) {
+            const int p = (tid + u * 256) >> 2;
+            const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+            const bool ok = oh < ohv && ow < owv && co0 + q * 4 < a.Cout;
+            dv[u] = buf_load4(dr, ok ? (unsigned)(((R0 + oh) * t.Wo + w0 + ow) * a.Cout + co0 + q * 4) * 4u : kNoLoad,
+                              0);
+        }
+    };
+    f4 acc[RG];
+#pragma unroll
+    for (int k = 0; k < RG; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+    const int t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);
+    load(t0);
+    for (int tile = t0; tile < t1; ++tile) {
+#pragma unroll
+        for (int u = 0; u < kTileBatches; ++u)
+            if (u * 256 < npix && tid + u * 256 < npix) *(f4*)(Xs + (tid + u * 256) * 4) = xv[u];
+        // (the last columns' reads of the last pixels run past the input: finite values, dropped)
+        if (tid < 16) Xs[npix * 4 + tid] = 0.f;
+#pragma unroll
+        for (int u = 0; u < NG; ++u) *(f4*)(Ds + ((tid + u * 256) >> 2) * LDW + q * 4) = dv[u];
+        const int tr = box_div(tile, t.nc_inv), R0 = tr * t.OH, P0 = box_prow(t, R0);
+        const int ohv = min(t.OH, t.rows - R0);
+        int boff[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int p = (wave * NG + g) * 16 + gi * 4;
+            const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+            boff[g] = oh < ohv ? ((box_prow(t, R0 + oh) - P0) * t.IW + ow * ST) * 4 + li : li;
+        }
+        lds_barrier();
+        if (tile + 1 < t1) load(tile + 1);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            float av[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) av[j] = Ds[((wave * NG + g) * 16 + gi * 4 + j) * LDW + li];
+#pragma unroll
+            for (int k = 0; k < RG; ++k) {
+                const int toff = ((k / NSG) * t.IW + (k % NSG) * 4) * 4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[k] = mfma16x16x4(av[j], Xs[boff[g] + toff + j * JST], acc[k]);
+            }
+        }
+        lds_barrier();
+    }
+    // the four waves' blocks summed in order, KS rows at a time
+    float* red = lds;   // [4][NSG][16 co][16]
+    float* out = part + (long)blockIdx.x * a.Cout * (KS * KS * 4);
+#pragma unroll
+    for (int r = 0; r < KS; ++r) {
+#pragma unroll
+        for (int sg = 0; sg < NSG; ++sg)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                red[((wave * NSG + sg) * 16 + gi * 4 + i) * 16 + li] = acc[r * NSG + sg][i];
+        __syncthreads();
+        for (int e = tid; e < NSG * 256; e += 256) {
+            const int sg = e >> 8, col = (e >> 4) & 15, cc = e & 15, s = sg * 4 + (cc >> 2);
+            const float v = ((red[e] + red[NSG * 256 + e]) + red[2 * NSG * 256 + e]) + red[3 * NSG * 256 + e];
+            if (s < KS && co0 + col < a.Cout) out[(long)(co0 + col) * (KS * KS * 4) + (r * KS + s) * 4 + (cc & 3)] = v;
+        }
+        __syncthreads();
+    }
+}
+
+// Boxes of a stem's weight gradient: 256 or 128 slots, at most 1024 workgroups.
+static bool pick_wgrad_stem(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride,
+                            int pad, WgTileCfg& out) {
+    if (Cin_p != 4 || Cout % 4 || R != S || (R != 3 && R != 7) || (stride != 1 && stride != 2)) return false;
+    if (!buf_fits((double)Nb * Hi * Wi * 4) || !buf_fits((double)Nb * Ho * Wo * Cout)) return false;
+    const long blocks = (Cout + 15) / 16;
+    bool found = false;
+    for (int ng : {4, 2}) {
+        WgTileCfg c;
+        if (!box_pick(c.t, Nb, Ho, Wo, R, stride, pad, ng * 64, 4, 4 * kTileBatches)) continue;
+        c.ng = ng;
+        // a column tile reads up to 16 floats past its first tap's pixel
+        c.lds = sizeof(float) * std::max<size_t>((size_t)ng * 64 * 20 + ((size_t)c.t.IH * c.t.IW + 4) * 4,
+                                                 (size_t)4 * ((R + 3) / 4) * 256);
+        c.tiles = box_tiles(c.t);
+        const long splits = std::min<long>(c.tiles, std::max<long>(1, 1024 / blocks));
+        c.per = (int)((c.tiles + splits - 1) / splits);
+        c.splits = (c.tiles + c.per - 1) / c.per;
+        found = true;
+        out = c;
+        if (c.splits * blocks >= 512) break;
+    }
+    return found;
+}
+
+template <int KS, int ST>
+static hipError_t launch_wg_stem(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
+                                 hipStream_t st) {
+    dim3 grid((unsigned)c.splits, (unsigned)((a.Cout + 15) / 16));
+    if (c.ng == 4)
+        launch((conv_wgrad_stem_f32<KS, 4, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per);
+    else
+        launch((conv_wgrad_stem_f32<KS, 2, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per);
+    return hipGetLastError();
+}
+
 WgradPlan wgrad_plan(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride, int pad) {
     WgradPlan p{};
     const long M = (long)Nb * Ho * Wo;
     const int Ktot = R * S * Cin_p;
     WgTileCfg c;
-    if (pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c)) {
-        p.tile = 1;
+    const bool stem = pick_wgrad_stem(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c);
+    if (stem || pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c)) {
+        p.tile = stem ? 2 : 1;
         p.splits = c.splits;
         p.part_floats = (long)p.splits * Cout * Ktot;
         return p;
@@ -1476,7 +1763,18 @@ hipError_t launch_conv_wgrad(const float* dY, const float* X, float* part, int N
                              int Ho, int Wo, int Cout, int R, int S, int stride, int pad, const WgradPlan& p,
                              hipStream_t st, const float* in_ss) {
     WgArgs a{Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, p.pix_per_split};
-    if (in_ss && !p.tile) return hipErrorInvalidValue;   // folding needs the spatial kernel
+    if (in_ss && p.tile != 1) return hipErrorInvalidValue;   // folding needs the spatial kernel
+    if (p.tile == 2) {
+        WgTileCfg c;
+        if (!pick_wgrad_stem(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c) || c.splits != p.splits)
+            return hipErrorInvalidValue;
+        if (R == 3) {
+            if (stride == 1) return launch_wg_stem<3, 1>(dY, X, part, a, c, st);
+            return launch_wg_stem<3, 2>(dY, X, part, a, c, st);
+        }
+        if (stride == 1) return launch_wg_stem<7, 1>(dY, X, part, a, c, st);
+        return launch_wg_stem<7, 2>(dY, X, part, a, c, st);
+    }
     if (p.tile) {
         WgTileCfg c;
         if (!pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c) || c.splits != p.splits)

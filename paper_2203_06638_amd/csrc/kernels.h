@@ -119,8 +119,8 @@ TileCounts conv_tile_counts(const ConvGeom& g);
 
 // Weight gradient: part[split][Cout][Ktot] = partial sums over pixel ranges
 // of dY[p][cout] * im2col(X)[p][(r,s,c)].  wgrad_plan chooses the kernel:
-// spatial tiles (tile = 1: a split is a run of pixel boxes) or GEMM tiles over
-// ranges of pix_per_split pixels.
+// spatial tiles (tile = 1, or 2 for a stem: a split is a run of pixel boxes) or
+// GEMM tiles over ranges of pix_per_split pixels.
 struct WgradPlan { int tm, tn, splits, pix_per_split; long part_floats; int tile; };
 WgradPlan wgrad_plan(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride, int pad);
 // in_ss (spatial-tile plans only): X is the input of a BN + ReLU whose

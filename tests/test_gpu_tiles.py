@@ -1,0 +1,194 @@
+"""The fp32 spatial tiles at the edges of their boxes (widths that leave part
+of a box empty, boxes over the end of an image, one image, rows longer than a
+box, channel counts in fours), the stem kernels, the stride-2 data gradient on
+odd grids, pooled heads over large maps, the 2x2 max-pool gradient, and the
+threaded copies to the host: against the fp64 oracle with the bars of
+tests/parity.py, or bit for bit where nothing is rounded."""
+import sys
+import threading
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import lppref as R
+from oracle import models as OM
+from paper_2203_06638_amd import lpp
+from paper_2203_06638_amd import models as PM
+from tests import parity as T
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    torch.cuda.init()
+
+
+def dev(img, lab):
+    return (torch.from_numpy(np.ascontiguousarray(img)).cuda(),
+            torch.from_numpy(np.ascontiguousarray(lab, np.int32)).cuda())
+
+
+def grid_inputs(o, seed, n):
+    """Images and first-conv weights on exact grids: the first conv's output,
+    which the ReLU or the pool decides on, is exact in both precisions."""
+    x = T.init_x(o.specs, seed)
+    rec = o.layers[0]
+    nw = rec["cout"] * rec["cin"] * rec["k"] ** 2
+    x[:nw] = synth.grid_values(seed, nw, 2.0 ** -5, 0.5)
+    return x, synth.grid_values(seed + 1, (n,) + o.in_shape, 2.0 ** -6, 4.0), synth.labels(seed, n, o.n_classes)
+
+
+def check_step(o, p, n, seed=11, modes=(lpp.SEQUENTIAL, lpp.ASYNC)):
+    x, img, lab = grid_inputs(o, seed, n)
+    loss, logits, _ = R.forward_backward(o, x, img, lab)
+    g, sc = R.grad_scale(o, x, img, lab)
+    for mode in modes:
+        with lpp.Context(p, K=1, batch=n, mode=mode) as ctx:
+            ctx.set_params(x)
+            i, t = dev(img, lab)
+            torch.cuda.synchronize()
+            ctx.step(0, i, t, 0, 0.0)
+            assert T.relerr(ctx.get_logits(0), logits, T.TAU_LOGITS) < T.TOL_LOGITS
+            worst = T.worst(T.tensor_errors(o, ctx.get_grad(0), g, scale=sc))
+            print(o.in_shape, n, "mode", mode, "worst", worst, file=sys.stderr, flush=True)
+            assert worst[1] < T.TOL_GRAD, worst
+
+
+# cin, c1, k, stride, pad, c2, hw, batch: image -> conv -> ReLU -> conv 3x3 -> pool -> linear
+@pytest.mark.parametrize("case", [
+    (3, 16, 3, 1, 1, 16, 7, 1),       # one image smaller than a box
+    (3, 20, 3, 1, 1, 36, 28, 5),      # channels in fours, boxes over the images' ends
+    (3, 24, 3, 2, 1, 16, 33, 3),      # stem of stride 2, odd size
+    (3, 64, 7, 2, 3, 20, 47, 2),      # 7x7/2 stem, ragged output channels
+    (3, 32, 7, 1, 3, 16, 11, 3),      # 7x7 stem of stride 1
+    (4, 16, 3, 1, 1, 16, 130, 1),     # rows longer than a box, four image channels
+    (3, 16, 3, 1, 1, 64, 20, 3),      # head over 20x20x64: pool and broadcast passes of their own
+    (3, 16, 3, 1, 0, 16, 30, 2),      # unpadded stem
+    (3, 48, 3, 1, 1, 52, 14, 9),
+], ids=lambda c: "x".join(map(str, c)))
+def test_tile_edges(case):
+    cin, c1, k, st, pad, c2, hw, n = case
+    check_step(*T.twin_conv_net(cin, c1, k, st, pad, c2, hw), n)
+
+
+# cin, c0, c1, k, stride, pad, hw, batch: image -> conv 3x3 -> ReLU -> conv -> pool -> linear
+@pytest.mark.parametrize("case", [
+    (3, 16, 36, 3, 2, 1, 17, 3),      # parity-split data gradient, odd grid
+    (3, 20, 24, 1, 2, 0, 15, 4),
+    (3, 16, 16, 3, 2, 1, 28, 37),     # several boxes a workgroup
+    (3, 32, 32, 1, 1, 0, 9, 5),
+    (3, 32, 64, 1, 1, 0, 40, 12),     # 32-channel 1x1 tiles
+    (3, 16, 32, 3, 3, 1, 19, 3),      # stride 3: the gather data gradient
+], ids=lambda c: "x".join(map(str, c)))
+def test_second_conv_edges(case):
+    cin, c0, c1, k, st, pad, hw, n = case
+    check_step(*T.twin_conv2_net(cin, c0, c1, k, st, pad, hw), n)
+
+
+@pytest.mark.parametrize("hw,n,widths", [(13, 5, (16, 20, 32)), (22, 3, (20, 36, 16))])
+def test_folded_batch_norm_on_ragged_boxes(hw, n, widths):
+    """ResNet units whose BN + ReLU folds and backward sums run on ragged
+    boxes: statistics by counted tiles, folded staging, sums in the data
+    gradient's epilogue.  BN shifts +4 and -4 on alternate channels keep every
+    ReLU decision clear of both precisions' disagreement."""
+    o, p = OM.resnet_cifar(1, widths, 10, hw), PM.resnet_cifar(8, widths, 10, hw)
+    o.set_blocks([1] * 5)
+
+    def make(seed):
+        x = T.init_x(o.specs, seed)
+        for name, off, cnt in o.tensors:
+            if name.endswith("bn_beta"):
+                x[off:off + cnt] = np.where(np.arange(cnt) % 2 == 0, 4.0, -4.0)
+        return x.astype(np.float64), T.inputs(seed + 7, n, o.in_shape, 10)[0]
+
+    seed, _ = T.well_posed_seed(o, make, seeds=range(2600, 2680), band=1e-5)
+    x = make(seed)[0].astype(np.float32)
+    img, lab = T.inputs(seed + 7, n, o.in_shape, 10)
+    _, logits, _ = R.forward_backward(o, x, img, lab)
+    g, sc = R.grad_scale(o, x, img, lab)
+    for mode in (lpp.SEQUENTIAL, lpp.ASYNC):
+        with lpp.Context(p, K=1, batch=n, mode=mode) as ctx:
+            ctx.set_params(x)
+            i, t = dev(img, lab)
+            torch.cuda.synchronize()
+            ctx.step(0, i, t, 0, 0.0)
+            assert T.relerr(ctx.get_logits(0), logits, T.TAU_LOGITS) < T.TOL_LOGITS
+            worst = T.worst(T.tensor_errors(o, ctx.get_grad(0), g, scale=sc))
+            print("hw", hw, "mode", mode, "worst", worst, file=sys.stderr, flush=True)
+            assert worst[1] < T.TOL_GRAD, worst
+
+
+@pytest.mark.parametrize("hw", [13, 14])
+def test_maxpool_gradient_blocks(hw):
+    """conv -> max pool 3x3/2 padded by 1 -> conv on odd and even maps: the
+    argmax decisions are taken on identical values (exact grid)."""
+    o = OM.Net("poolnet", 3, hw, hw, 6)
+    a = o.maxpool(o.conv(-1, 3, 16, 3, 1, 1), 3, 2, 1)
+    a = o.gap(o.conv(a, 16, 16, 3, 1, 1))
+    o.next_unit()
+    o.linear(a, 16, 6)
+    o.set_blocks([1, 2])
+    p = PM.Model("poolnet", (3, hw, hw), 6)
+    y = p.maxpool(p.conv(-1, 16, 3), 3, 2, 1)
+    y = p.gap(p.conv(y, 16, 3))
+    p.new_unit()
+    p.linear(y, 6)
+    p.assign_blocks([1, 2])
+    for seed in range(60, 90):      # a seed without tied maxima
+        x, img, _ = grid_inputs(o, seed, 3)
+        if R.kink_margin(o, x, img) > 0:
+            return check_step(o, p, 3, seed=seed)
+    pytest.fail("every seed has a tie")
+
+
+def _wide(n_classes=10):
+    m = PM.Model("wide", (3, 4, 4), n_classes)
+    x = m.conv(-1, 256, 3)
+    m.new_unit()
+    x = m.conv(x, 512, 3)
+    m.new_unit()
+    m.linear(m.gap(m.conv(x, 512, 3)), n_classes)
+    return m.assign_blocks([1, 2, 3])
+
+
+def test_large_copies_to_the_host():
+    """14 MB of parameters (several threads and slots a copy): every entry
+    arrives, a block's gradient is the full one's and zero elsewhere, and
+    copies of two contexts from two threads at once (one of them finds the
+    pinned slots in use) agree."""
+    m = _wide()
+    rng = np.random.default_rng(3)
+    xs = [(rng.standard_normal(m.d) * 0.05).astype(np.float32) for _ in range(2)]
+    img, lab = synth.images(4, 2, 3, 4, 4), synth.labels(4, 2, 10)
+    with lpp.Context(m, K=1, batch=2) as a, lpp.Context(m, K=1, batch=2) as b:
+        for ctx, x in ((a, xs[0]), (b, xs[1])):
+            ctx.set_params(x)
+            assert np.array_equal(ctx.get_params(0), x)
+        i, t = dev(img, lab)
+        torch.cuda.synchronize()
+        a.step(0, i, t, 0, 0.0)
+        full = a.get_grad(0)
+        assert np.any(full)
+        for part in (1, 2, 3):
+            a.step(0, i, t, part, 0.0)
+            got, (lo, hi) = a.get_grad(0), a.block_range(part)
+            assert np.array_equal(got[lo:hi], full[lo:hi])
+            assert not np.any(got[:lo]) and not np.any(got[hi:])
+        bad = []
+
+        def read(ctx, x):
+            for _ in range(20):
+                if not np.array_equal(ctx.get_params(0), x):
+                    bad.append(1)
+
+        th = [threading.Thread(target=read, args=c) for c in ((a, xs[0]), (b, xs[1]))]
+        for h in th:
+            h.start()
+        for h in th:
+            h.join()
+        assert not bad
