@@ -440,7 +440,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 256 ?
 // 10-15% where two of its workgroups fill every compute unit and loses up to
 // 50% where they do not.  With four worker streams at once (fill 128) the
 // larger tiles win although each pass alone is slower: WRN-16-8 +11%,
-// ResNet-18 +5%, ResNet-50 +2% against fill 512 (64 and 96 are no better).
+// ResNet-18 +5%, ResNet-50 +2% against fill 512 (64 and 96 are no better;
+// holding the 256-row tile to 256 or 512 workgroups there, WRN-16-8 -3%, -5%).
+// 128 x 128 tiles of two load steps pay from three quarters of `fill`: 64 x
+// 28x28x128 (392 of them) 33 us with 64 rows, 25 with 128; 128 x 8x8x512 (256)
+// 59 and 69.
 static void pick_bf16(long Mv, int Ncols, int Cs, int fill, int& bm, int& bn) {
     bn = Ncols >= 128 ? 128 : 64;
     const long nt = (Ncols + bn - 1) / bn;
@@ -448,7 +452,7 @@ static void pick_bf16(long Mv, int Ncols, int Cs, int fill, int& bm, int& bn) {
         bm = 256;
         return;
     }
-    bm = ((Mv + 127) / 128) * nt >= fill ? 128 : 64;
+    bm = ((Mv + 127) / 128) * nt >= (Cs % 64 == 0 && bn == 128 ? fill * 3 / 4 : fill) ? 128 : 64;
 }
 
 int conv_bf16_tile_rows(const ConvGeom& g) {
@@ -472,13 +476,20 @@ static hipError_t launch_bf16_pass(const bf16* src, const bf16* B, const float* 
     if (Mmax == 0) return hipSuccess;
     dim3 grid((unsigned)((Mmax + BM - 1) / BM), (unsigned)((g.Ncols + BN - 1) / BN), (unsigned)np);
     const BnSums sm = stats ? *stats : BnSums{};
-    // 32-channel load steps straight into LDS, NS of them in flight; 64 x 128
-    // tiles (a step of 8 MFMAs per wave) take two load steps per buffer and
-    // barrier (measured 7-23% faster on 256- and 512-channel sources)
-    if constexpr (BM == 64 && BN == 128) {
+    // 32-channel load steps straight into LDS, NS of them in flight; tiles of
+    // up to 128 x 128 take two load steps per buffer and barrier where the
+    // source's channels allow: a load step reads half of a pixel's 128-byte
+    // line, and two steps issued together use the whole of it while it is near
+    // (64 x 128 with three buffers: 7-23% faster on 256- and 512-channel
+    // sources; 128 x 128 with two, whose 64 KB leave two workgroups to a
+    // compute unit: 128 x 16x16x256 53 -> 50 us forward, 51 -> 47 data
+    // gradient; three take 96 KB, one workgroup, and 74; 256 x 128 with two
+    // likewise, 57 -> 73)
+    if constexpr (BM <= 128 && BN == 128) {
         if (g.Cs % 64 == 0) {
-            if (stats) launch((conv_bf16_k<BM, BN, true, true, 2, true, 3>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
-            else launch((conv_bf16_k<BM, BN, false, true, 2, true, 3>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
+            constexpr int NS2 = BM == 64 ? 3 : 2;
+            if (stats) launch((conv_bf16_k<BM, BN, true, true, 2, true, NS2>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
+            else launch((conv_bf16_k<BM, BN, false, true, 2, true, NS2>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
             return hipGetLastError();
         }
     }
