@@ -416,33 +416,36 @@ __device__ __forceinline__ f4 buf_load4(__amdgpu_buffer_rsrc_t r, unsigned off, 
 // the workgroup's LDS accesses done, loads from memory left in flight
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Fills the geometry of boxes of `slots` slots, nc to a row, over Nb images of
-// Hper x Wo outputs, each reading `ext` padded rows and columns, `step` apart;
-// box columns are rounded up to a multiple of cq slots.  False when a box
-// stages more than max_batches * 64 input pixels or an index leaves box_div's
-// range.
-static bool box_fill(BoxGeom& t, int Nb, int Hper, int Wo, int ext, int step, int pad_eff, int slots, int nc, int cq,
-                     int max_batches) {
-    const long rows = (long)Nb * Hper;
-    if (nc > Wo || rows >= (1L << 30)) return false;
+// Shapes boxes of `slots` slots, nc to a row, over Nb images of Hper x Wo
+// outputs, each reading `ext` padded rows and columns, `step` apart; box
+// columns are rounded up to a multiple of cq slots.  False when a box stages
+// more than max_batches * 64 input pixels.
+static bool box_shape(BoxGeom& t, int Nb, int Hper, int Wo, int ext, int step, int slots, int nc, int cq,
+                      int max_batches) {
+    if (nc > Wo) return false;
     t.OW = (Wo + nc - 1) / nc;
-    t.OWs = (t.OW + cq - 1) / cq * cq;
+    t.OWs = cq == 1 ? t.OW : (t.OW + cq - 1) / cq * cq;
     if (t.OWs > slots) return false;
     t.nc = (Wo + t.OW - 1) / t.OW;
-    t.OH = (int)std::min<long>(slots / t.OWs, rows);
-    t.rows = (int)rows;
+    t.rows = Nb * Hper;
+    t.OH = std::min(slots / t.OWs, t.rows);
+    // over the ends of as many images as OH rows can reach over
+    const int ends = Hper % t.OH == 0 ? 0 : (t.OH + Hper - 2) / Hper;
+    t.IH = (t.OH - 1) * step + ext + ends * std::max(0, ext - step);
+    t.IW = (t.OWs - 1) * step + ext;
+    return (t.IH * (long)t.IW + 63) / 64 <= max_batches;
+}
+
+// The rest of a shaped box's geometry.  False when an index leaves box_div's
+// range.
+static bool box_fill(BoxGeom& t, int Nb, int Hper, int Wo, int ext, int step, int pad_eff) {
     t.Hper = Hper;
     t.Wo = Wo;
     t.step = step;
     t.Hp = (Hper - 1) * step + ext;
     t.pad_eff = pad_eff;
-    // over the ends of as many images as OH rows can reach over
-    const int ends = Hper % t.OH == 0 ? 0 : (t.OH + Hper - 2) / Hper;
-    t.IH = (t.OH - 1) * step + ext + ends * std::max(0, ext - step);
-    t.IW = (t.OWs - 1) * step + ext;
-    if ((t.IH * (long)t.IW + 63) / 64 > max_batches) return false;
-    const double tiles = (double)((rows + t.OH - 1) / t.OH) * t.nc;
-    if (((double)Nb * t.Hp + t.IH) * t.Hp >= 4294967296.0 || (double)rows * Hper >= 4294967296.0 ||
+    const double tiles = (double)((t.rows + t.OH - 1) / t.OH) * t.nc;
+    if (((double)Nb * t.Hp + t.IH) * t.Hp >= 4294967296.0 || (double)t.rows * Hper >= 4294967296.0 ||
         tiles >= 1073741824.0 || tiles * t.nc >= 4294967296.0)
         return false;
     t.OWs_inv = box_inv(t.OWs);
@@ -457,30 +460,32 @@ static int box_tiles(const BoxGeom& t) { return (t.rows + t.OH - 1) / t.OH * t.n
 // The number of boxes per row: among those within 4% of the fewest boxes, the
 // one that stages the fewest batches of 64 input pixels, then the fewest
 // boxes.  (At 28 columns and 64 slots 16 x 4 boxes fill all slots, 2 x 28 only
-// 56; square boxes stage the smallest halo.)
+// 56; square boxes stage the smallest halo.)  Runs at every launch outside a
+// graph.
 static bool box_pick(BoxGeom& out, int Nb, int Hper, int Wo, int ext, int step, int pad_eff, int slots, int cq,
                      int max_batches) {
+    if ((long)Nb * Hper >= (1L << 30)) return false;
+    BoxGeom t;
+    int nc[32], tiles[32], batches[32], n = 0, last = 0;
     long fewest = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        long best = 0;
-        for (int nc = 1; nc <= 32; ++nc) {
-            BoxGeom t;
-            if (!box_fill(t, Nb, Hper, Wo, ext, step, pad_eff, slots, nc, cq, max_batches)) continue;
-            const long n = box_tiles(t);
-            if (pass == 0) {
-                if (!fewest || n < fewest) fewest = n;
-                continue;
-            }
-            if (n * 25 > fewest * 26) continue;
-            const long score = (long)((t.IH * t.IW + 63) / 64) * (1L << 31) + n;
-            if (!best || score < best) {
-                best = score;
-                out = t;
-            }
-        }
-        if (!fewest) return false;
+    for (int k = 1; k <= 32; ++k) {
+        if ((long)k * slots < Wo || (last && (Wo + k - 1) / k == last)) continue;   // too wide; the last one's box
+        if (!box_shape(t, Nb, Hper, Wo, ext, step, slots, k, cq, max_batches)) continue;
+        const long b = (long)((t.rows + t.OH - 1) / t.OH) * t.nc;
+        if (b >= (1L << 30)) continue;
+        last = t.OW;
+        nc[n] = k;
+        tiles[n] = (int)b;
+        batches[n++] = (t.IH * t.IW + 63) / 64;
+        if (!fewest || b < fewest) fewest = b;
     }
-    return true;
+    int best = -1;
+    for (int i = 0; i < n; ++i)
+        if (tiles[i] * 25L <= fewest * 26 &&
+            (best < 0 || batches[i] < batches[best] || (batches[i] == batches[best] && tiles[i] < tiles[best])))
+            best = i;
+    return best >= 0 && box_shape(out, Nb, Hper, Wo, ext, step, slots, nc[best], cq, max_batches) &&
+           box_fill(out, Nb, Hper, Wo, ext, step, pad_eff);
 }
 
 // Bytes of a tensor of n floats addressable with the kernels' 32-bit offsets

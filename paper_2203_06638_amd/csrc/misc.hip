@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void stats_finalize_k(const float* __restrict_
     if (threadIdx.x < kMergeC && c < C) {
         const double dm = v[0] / (double)M, mu = K + dm;
         double var = v[1] / (double)M - dm * dm;
-        var = var > 0.0 ? var : 0.0;
+        var = var < 0.0 ? 0.0 : var;              // (a NaN stays one)
         const double r = 1.0 / sqrt(var + (double)eps);
         const double sc = (double)gamma[c] * r;
         aux[c] = (float)mu;
