@@ -337,7 +337,14 @@ hipError_t launch_bn_act(int dt, const void* x1, const BnFwd& b1, const void* r,
 // sums to the accumulators.
 // MK: 0 no ReLU; 1 ReLU mask from the stored group output (a.mask); 2 ReLU
 // decision recomputed from the BN input, relu(fma(x1, scale, shift)) > 0 with
-// scale | shift at a.mask_ss (the folded forward's own expression).
+// scale | shift at a.mask_ss (the forward's own expression), as the forward
+// rounds it to T.
+template <class T>
+__device__ __forceinline__ bool relu_passes(float x, float sc, float sh) {
+    float v = __builtin_fmaf(x, sc, sh);
+    if (sizeof(T) == 2) v = from_bf16(to_bf16(v));
+    return v > 0.f;
+}
 template <class T, int MK, bool DUAL, int BT>
 __global__ __launch_bounds__(BT) void bn_bwd_reduce_k(BnBwdArgs a, int R, BnSums out) {
     const T* __restrict__ dy = (const T*)a.dy;
@@ -386,7 +393,7 @@ __global__ __launch_bounds__(BT) void bn_bwd_reduce_k(BnBwdArgs a, int R, BnSums
                     }
                     if (MK == 2) {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) g[j] = __builtin_fmaf(xv[k][j], msc[j], msh[j]) > 0.f ? g[j] : 0.f;
+                        for (int j = 0; j < 4; ++j) g[j] = relu_passes<T>(xv[k][j], msc[j], msh[j]) ? g[j] : 0.f;
                     }
                     s0 += g;
                     s1 += g * ((xv[k] - m1) * r1v);
@@ -445,6 +452,15 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_k(BnBwdArgs a, BnBwdCoef k, 
     const long n4 = a.M * C / 4;
     const long i0 = (long)blockIdx.x * 256 * E + threadIdx.x;
     f4 gv[E], yv[E], x1v[E], x2v[E];
+    const int C4 = C >> 2;
+    // MK == 2: the ReLU's scale and shift; where C4 divides 256 a thread's
+    // quads share their channels
+    const bool same_c = 256 % C4 == 0;
+    f4 msc{}, msh{};
+    if (MK == 2 && same_c) {
+        msc = *(const f4*)(a.mask_ss + (threadIdx.x % C4) * 4);
+        msh = *(const f4*)(a.mask_ss + C + (threadIdx.x % C4) * 4);
+    }
 #pragma unroll
     for (int u = 0; u < E; ++u) {
         const long i = i0 + u * 256;
@@ -495,7 +511,6 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_k(BnBwdArgs a, BnBwdCoef k, 
         }
     }
     __syncthreads();
-    const int C4 = C >> 2;
 #pragma unroll
     for (int u = 0; u < E; ++u) {
         const long i = i0 + u * 256;
@@ -507,9 +522,12 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_k(BnBwdArgs a, BnBwdCoef k, 
             for (int j = 0; j < 4; ++j) g[j] = yv[u][j] > 0.f ? g[j] : 0.f;
         }
         if (MK == 2) {
-            const f4 msc = *(const f4*)(a.mask_ss + c), msh = *(const f4*)(a.mask_ss + C + c);
+            if (!same_c) {
+                msc = *(const f4*)(a.mask_ss + c);
+                msh = *(const f4*)(a.mask_ss + C + c);
+            }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) g[j] = __builtin_fmaf(x1v[u][j], msc[j], msh[j]) > 0.f ? g[j] : 0.f;
+            for (int j = 0; j < 4; ++j) g[j] = relu_passes<T>(x1v[u][j], msc[j], msh[j]) ? g[j] : 0.f;
         }
         if (dx1) {
             const f4 xh = (x1v[u] - *(const f4*)(cf + 3 * C + c)) * *(const f4*)(cf + 4 * C + c);

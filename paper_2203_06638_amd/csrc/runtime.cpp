@@ -1240,9 +1240,9 @@ int run_backward(lpp_ctx* c, Worker& w, int partition) {
             float* ax = c->aux(w, G.a);
             float* ax2 = b2 >= 0 ? c->aux(w, b2) : nullptr;
             const Layer* Y2 = b2 >= 0 ? &M.layers[b2] : nullptr;
-            // plain BN + ReLU (fp32): the ReLU decision is recomputed from the
-            // BN input and its scale and shift instead of read from the output
-            const bool xmask = G.relu >= 0 && G.bn2 < 0 && G.add < 0 && !bf;
+            // plain BN + ReLU: the ReLU decision is recomputed from the BN input
+            // and its scale and shift instead of read from the output
+            const bool xmask = G.relu >= 0 && G.bn2 < 0 && G.add < 0;
             lpp::BnBwdArgs a{dy, G.relu >= 0 && !xmask ? c->act(w, G.out) : nullptr, x0, ax, ax + C,
                              want2 ? c->act(w, Y2->L.in0) : nullptr, want2 ? ax2 : nullptr,
                              want2 ? ax2 + C : nullptr, Min, C, xmask ? ax + 2 * C : nullptr};
@@ -1280,6 +1280,17 @@ int run_backward(lpp_ctx* c, Worker& w, int partition) {
             void* d1 = want1 && pl.din0[G.a] ? dx0 : nullptr;
             void* d2 = want2 && pl.din0[b2] ? c->dact(w, Y2->L.in0) : nullptr;
             void* dr = want_res ? c->dact(w, G.res) : nullptr;
+            // bf16: the apply pass recomputes the mask only where the stored
+            // output, which the consumer's gradient has just read, no longer
+            // lies in the worker's share of the last-level cache (64 x
+            // 112x112x64, 103 MB: 81 us reading it, 67 without; 64 x 56x56x64,
+            // 26 MB: 22 and 27; WRN-16-8's eight workers, 34 and 17 MB: 17.3
+            // and 16.6 on average).  The sums are faster without it at every
+            // size (62 -> 40 us, 10.8 -> 8.5 on 32 x 28x28x128).
+            if (bf && xmask && eb * Min * C < 64e6 * M.conv_fill / 512) {
+                a.mask = c->act(w, G.out);
+                a.mask_ss = nullptr;
+            }
             // (with atomic sums the apply kernel also writes dgamma and dbeta)
             if (d1 || d2 || dr || (k.acc && (gg1 || gb1 || gg2 || gb2))) {
                 const double bytes = ((a.mask ? 2.0 : 1.0) + (d1 ? 3.0 : 0.0) + (d2 ? 3.0 : 0.0) +
