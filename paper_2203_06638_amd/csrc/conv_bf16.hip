@@ -25,9 +25,9 @@
 // (64 bytes) whose four 16-byte chunks are XOR-swizzled by (row / 4) % 4, so
 // both the row-wise stores and the 16-row fragment reads of 16 lanes hit
 // distinct banks.  Sources of 32k channels load their tiles straight into
-// LDS through a pipeline of several buffers (see the DMA notes below); the
-// 8/16-channel stem stages them through registers into two buffers, the next
-// step's loads in flight during the current step's MFMAs.
+// LDS through a pipeline of several buffers (see the DMA notes below), others
+// do on small grids and else stage them through registers into two buffers,
+// the next step's loads in flight during the current step's MFMAs.
 //
 // Weight gradient: dW[cout][(tap, c)] = sum over output pixels p of
 // dY[p][cout] * X[src(p, tap)][c]: a GEMM whose reduction runs over pixels.
@@ -114,7 +114,7 @@ __device__ __forceinline__ void bf_wait_steps(int ahead) {
     else __builtin_amdgcn_s_waitcnt(bf_vmcnt(0));
 }
 
-// DMA (FASTK only): operand tiles go from memory straight into LDS (buffer
+// DMA: operand tiles go from memory straight into LDS (buffer
 // loads with the LDS bit: no register staging, no LDS store instructions;
 // taps in the zero padding and columns past the output read out of the
 // buffer's range, which yields zeros).  Each wave's load instruction fills
@@ -132,7 +132,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 256 ?
                                                    const float* __restrict__ bias, bf16* __restrict__ Y,
                                                    const bf16* __restrict__ res, ConvGeom g, BfPasses pp, int accumulate,
                                                    BnSums sums) {
-    static_assert(!DMA || FASTK, "DMA operand loads need 32-channel load steps");
     static_assert(NS == 2 || DMA, "deeper pipelines use DMA operand loads");
     constexpr int TM = BM / 32, TN = BN / 32;     // 16x16 blocks per wave; waves 2 x 2
     constexpr int AL = BM / 64, BL = BN / 64;     // 16-byte operand loads per thread per K-step
@@ -253,16 +252,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 256 ?
 #pragma unroll
         for (int u = 0; u < BL; ++u) {
             const int n = n0 + rr + 64 * u;
-            b_off[u] = n < g.Ncols ? (unsigned)(n * RS * g.Cs + jj * 8) * 2u : 0x80000000u;
+            b_off[u] = n < g.Ncols ? (unsigned)(n * RS * g.Cs + (FASTK ? jj * 8 : 0)) * 2u : 0x80000000u;
+        }
+        // without FASTK each thread keeps the tap and channel of its own chunk
+        const int dtap = 32 / g.Cs, dch = 32 - dtap * g.Cs;   // a load step further
+        if (!FASTK && ntap) {
+            const int tap = jj / cpt;
+            c0 = (jj - tap * cpt) * 8;
+            tx = tap / ps.ns;
+            ty = tap - tx * ps.ns;
         }
         // one K-step's loads into LDS buffer buf; (tx, ty, c0) advance
         auto issue = [&](int buf, int kk) {
 #pragma unroll
             for (int h = 0; h < KH; ++h) {
-                const bool tok = kk * KH + h < nks;
+                const bool tok = FASTK ? kk * KH + h < nks : tx < ps.nr;
                 const int r = ps.r0 + ps.step * tx, sc = ps.s0 + ps.step * ty;
                 const int dh = (ps.offh + ps.sgn * r) >> ps.shift, dw = (ps.offw + ps.sgn * sc) >> ps.shift;
-                const int aoff = (dh * g.Ws + dw) * g.Cs + c0 + jj * 8;
+                const int aoff = (dh * g.Ws + dw) * g.Cs + c0 + (FASTK ? jj * 8 : 0);
                 const unsigned woff = (unsigned)((r * g.S + sc) * g.Cs + c0) * 2u;
                 bf16* As = lds + buf * STAGE + h * HALF + wave * 16 * P;
 #pragma unroll
@@ -275,11 +282,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 256 ?
                 for (int u = 0; u < BL; ++u)
                     bf_dma16(brs, As + (BM + 64 * u) * P,
                              tok && b_off[u] < 0x80000000u ? b_off[u] + woff : 0x80000000u);
-                c0 += 32;
-                if (c0 == g.Cs) {
-                    c0 = 0;
-                    if (++ty == ps.ns) {
-                        ty = 0;
+                if (FASTK) {
+                    c0 += 32;
+                    if (c0 == g.Cs) {
+                        c0 = 0;
+                        if (++ty == ps.ns) {
+                            ty = 0;
+                            ++tx;
+                        }
+                    }
+                } else {
+                    c0 += dch;
+                    ty += dtap;
+                    if (c0 >= g.Cs) {
+                        c0 -= g.Cs;
+                        ++ty;
+                    }
+                    while (ty >= ps.ns) {
+                        ty -= ps.ns;
                         ++tx;
                     }
                 }
@@ -467,6 +487,9 @@ bool conv_bf16_supported(int mode, const ConvGeom& g) {
     return g.R <= 32 && g.S <= 32 && g.pad < 32;
 }
 
+// n bf16 values lie within the 32-bit offsets of a buffer
+static bool bf_bytes_fit(double n) { return 2.0 * n < 2147483647.0; }
+
 template <int BM, int BN>
 static hipError_t launch_bf16_pass(const bf16* src, const bf16* B, const float* bias, bf16* Y, const bf16* res,
                                    const ConvGeom& g, const BfPasses& ps, int np, bool acc, const BnSums* stats,
@@ -497,6 +520,18 @@ static hipError_t launch_bf16_pass(const bf16* src, const bf16* B, const float* 
         constexpr int NSD = BM == 256 ? 3 : 4;
         if (stats) launch((conv_bf16_k<BM, BN, true, true, 1, true, NSD>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
         else launch((conv_bf16_k<BM, BN, false, true, 1, true, NSD>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
+        // Other channel counts: the pipeline on grids of up to two workgroups
+        // to a compute unit, which leave the latency of register staging
+        // uncovered (16 x 24x24x136: seven convs' steps 2668 -> 2349 us); on
+        // larger grids, where other workgroups cover it, the taps that each
+        // thread then keeps for itself cost 1-3% (24 x 36x36x168, 32 x
+        // 28x28x200, and 128-row tiles)
+    } else if (BM == 64 && (long)grid.x * grid.y * np <= 512 && bf_bytes_fit((double)g.Nb * g.Hs * g.Ws * g.Cs) &&
+               bf_bytes_fit((double)g.Ncols * g.R * g.S * g.Cs)) {
+        if constexpr (BM == 64) {
+            if (stats) launch((conv_bf16_k<BM, BN, true, false, 1, true, 4>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
+            else launch((conv_bf16_k<BM, BN, false, false, 1, true, 4>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
+        }
     } else {
         if (stats) launch((conv_bf16_k<BM, BN, true, false, 1, false>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
         else launch((conv_bf16_k<BM, BN, false, false, 1, false>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);

@@ -192,3 +192,19 @@ def test_large_copies_to_the_host():
         for h in th:
             h.join()
         assert not bad
+
+
+# bf16 sources whose channels are no multiple of 32: on small grids each thread
+# of the load pipeline keeps the tap of its own chunk (the last case's first
+# pass has more than 512 workgroups: staged through registers)
+@pytest.mark.parametrize("case", [
+    (3, 24, 40, 3, 1, 1, 11, 3),
+    (3, 40, 136, 3, 2, 1, 13, 2),     # stride-2 data gradient, two column tiles
+    (8, 136, 72, 1, 1, 0, 9, 3),
+    (3, 48, 16, 7, 2, 3, 17, 2),
+    (24, 72, 200, 3, 1, 1, 6, 2),
+    (3, 24, 40, 3, 1, 1, 58, 12),
+], ids=lambda c: "x".join(map(str, c)))
+def test_bf16_channels_in_eights(case):
+    from tests.test_gpu_bf16 import test_bf16_conv_passes
+    test_bf16_conv_passes(case)
