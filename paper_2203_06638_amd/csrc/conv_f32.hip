@@ -456,6 +456,10 @@ static bool box_fill(BoxGeom& t, int Nb, int Hper, int Wo, int ext, int step, in
     return true;
 }
 static int box_tiles(const BoxGeom& t) { return (t.rows + t.OH - 1) / t.OH * t.nc; }
+// every slot of every box holds a pixel
+static bool box_full(const BoxGeom& t, int slots) {
+    return t.OH * t.OWs == slots && t.OWs == t.OW && t.OW * t.nc == t.Wo && t.rows % t.OH == 0;
+}
 
 // The number of boxes per row: among those within 4% of the fewest boxes, the
 // one that stages the fewest batches of 64 input pixels, then the fewest
@@ -1387,22 +1391,25 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32(const float* __restrict__ 
 // reduction dimension k of v_mfma_f32_16x16x4_f32 is the pixel: lane (li, gi)
 // supplies dY[p][co0 + li] and X[src(p)][c0 + li] for the same four slots
 // p = 16 g + 4 gi + j, consecutive in one box row (OWs % 4 == 0); slots
-// without a pixel hold dY = 0.  Waves are summed in a fixed order and every
-// workgroup writes its own partial, summed in order by the reduce kernel.
+// without a pixel (none where FULL) hold dY = 0.  Waves are summed in a fixed
+// order and every workgroup writes its own partial, summed in order by the
+// reduce kernel.  What a slot without a pixel reads of X belongs to other
+// outputs, and zero times an infinity there is NaN: a workgroup that finds a
+// NaN among its sums forms them once more with zeros for both operands.
+// (Zeros chosen at every MFMA cost up to 9% of a step.)
 // Bound by the staging's latency at ResNet-20's sizes (one box per workgroup)
 // and by the MFMAs where several boxes pipeline.  Held to 168 registers, three
 // workgroups to a compute unit (with two, 16 x 56x56x64 takes 54 us instead of
 // 45, ResNet-20's stages 11.2 instead of 10.8).
 constexpr int kWgBatches = 6;   // staged input quads per thread and box, at most
 
-template <int RS, int NG, int ST>
+template <int RS, int NG, int ST, bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8)))
 void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__ X, float* __restrict__ part, WgArgs a,
                          BoxGeom t, int tiles, int per, const float* __restrict__ in_ss) {
     constexpr bool K1 = RS == 1;
     constexpr int LDW = 20;
     constexpr int JST = (K1 ? 1 : ST) * LDW;   // LDS distance between a lane's four pixels
-    constexpr int TP = NG * 64;
     extern __shared__ float lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int gi = lane >> 4, li = lane & 15, q = tid & 3;
@@ -1528,17 +1535,67 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
     // each wave's RS x 16 x 16 block into its own LDS slice, then the four
     // slices summed in order
     float* red = lds;   // [4][RS][16 co][16 c]
-#pragma unroll
-    for (int k = 0; k < RS; ++k)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) red[((wave * RS + k) * 16 + gi * 4 + i) * 16 + li] = acc[k][i];
-    __syncthreads();
     float* out = part + (long)blockIdx.x * a.Cout * Ktot;
-    for (int e = tid; e < RS * 256; e += 256) {
-        const int k = e >> 8, col = (e >> 4) & 15, c = e & 15;
-        const float v = ((red[e] + red[RS * 256 + e]) + red[2 * RS * 256 + e]) + red[3 * RS * 256 + e];
-        if (co0 + col < a.Cout && c0 + c < a.Cin_p) out[(long)(co0 + col) * Ktot + k * a.Cin_p + c0 + c] = v;
+    auto finish = [&]() {
+#pragma unroll
+        for (int k = 0; k < RS; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) red[((wave * RS + k) * 16 + gi * 4 + i) * 16 + li] = acc[k][i];
+        __syncthreads();
+        bool nan = false;
+        for (int e = tid; e < RS * 256; e += 256) {
+            const int k = e >> 8, col = (e >> 4) & 15, c = e & 15;
+            const float v = ((red[e] + red[RS * 256 + e]) + red[2 * RS * 256 + e]) + red[3 * RS * 256 + e];
+            if (co0 + col < a.Cout && c0 + c < a.Cin_p) out[(long)(co0 + col) * Ktot + k * a.Cin_p + c0 + c] = v;
+            nan |= v != v;
+        }
+        return nan;
+    };
+    const bool nan = finish();
+    if (FULL || !__syncthreads_or(nan)) return;
+    // the same sums in the same order, zeros for both operands at slots without a pixel
+#pragma unroll
+    for (int k = 0; k < RS; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int tile = t0; tile < t1; ++tile) {
+        load(tile);
+        if (in_ss) {
+            // X read through a folded BN + ReLU (padding stays zero)
+#pragma unroll
+            for (int u = 0; u < kWgBatches; ++u)
+                if (u < nxu) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        xv[u][k] = (valid >> u) & 1 ? fmaxf(__builtin_fmaf(xv[u][k], fsc[k], fsh[k]), 0.f) : 0.f;
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < kWgBatches; ++u)
+            if (u < nxu && tid + u * 256 < nx) *(f4*)(Xs + sdst + u * 64 * LDW) = xv[u];
+#pragma unroll
+        for (int u = 0; u < NG; ++u) *(f4*)(Ds + sdst + u * 64 * LDW) = dv[u];
+        __syncthreads();
+#pragma unroll 1
+        for (int g = 0; g < NG; ++g) {
+            const int tr = box_div(tile, t.nc_inv), R0 = tr * t.OH;
+            const int p = (wave * NG + g) * 16 + gi * 4;
+            const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+            const bool ok = oh < min(t.OH, t.rows - R0);
+            const int b0 = ok ? ((box_prow(t, R0 + oh) - box_prow(t, R0)) * t.IW + ow * (K1 ? 1 : ST)) * LDW + li : li;
+            const int left = ok ? min(t.OW, t.Wo - (tile - tr * t.nc) * t.OW) - ow : 0;   // slots that hold a pixel
+#pragma unroll 1
+            for (int j = 0; j < 4; ++j) {
+                const float d = Ds[(p + j) * LDW + li];
+#pragma unroll
+                for (int k = 0; k < RS; ++k) {
+                    const float v = Xs[b0 + toff[k] + j * JST];
+                    acc[k] = mfma16x16x4(d, j < left ? v : 0.f, acc[k]);
+                }
+            }
+        }
+        __syncthreads();
     }
+    finish();
 }
 
 // Boxes of the spatially tiled weight gradient, or false when it does not
@@ -1579,7 +1636,7 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
 // consecutive floats from the pixel of the first tap.  Columns past the filter
 // row are formed and dropped.  (128 x 32x32, 4 -> 16: 10.3 us with a column
 // tile per tap, 7.4 here; 4 -> 96: 36, 19; 7x7/2, 4 -> 64: 97, 82.)
-template <int KS, int NG, int ST>
+template <int KS, int NG, int ST, bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 3 ? 4 : 3, 8)))
 void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__ X,
                                                            float* __restrict__ part, WgArgs a, BoxGeom t, int tiles,
@@ -1659,21 +1716,65 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
     // the four waves' blocks summed in order, KS rows at a time
     float* red = lds;   // [4][NSG][16 co][16]
     float* out = part + (long)blockIdx.x * a.Cout * (KS * KS * 4);
+    auto finish = [&]() {
+        bool nan = false;
 #pragma unroll
-    for (int r = 0; r < KS; ++r) {
+        for (int r = 0; r < KS; ++r) {
 #pragma unroll
-        for (int sg = 0; sg < NSG; ++sg)
+            for (int sg = 0; sg < NSG; ++sg)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                red[((wave * NSG + sg) * 16 + gi * 4 + i) * 16 + li] = acc[r * NSG + sg][i];
+                for (int i = 0; i < 4; ++i)
+                    red[((wave * NSG + sg) * 16 + gi * 4 + i) * 16 + li] = acc[r * NSG + sg][i];
+            __syncthreads();
+            for (int e = tid; e < NSG * 256; e += 256) {
+                const int sg = e >> 8, col = (e >> 4) & 15, cc = e & 15, s = sg * 4 + (cc >> 2);
+                const float v = ((red[e] + red[NSG * 256 + e]) + red[2 * NSG * 256 + e]) + red[3 * NSG * 256 + e];
+                if (s < KS && co0 + col < a.Cout) {
+                    out[(long)(co0 + col) * (KS * KS * 4) + (r * KS + s) * 4 + (cc & 3)] = v;
+                    nan |= v != v;
+                }
+            }
+            __syncthreads();
+        }
+        return nan;
+    };
+    const bool nan = finish();
+    if (FULL || !__syncthreads_or(nan)) return;
+    // the same sums in the same order, zeros for both operands at slots without a pixel
+#pragma unroll
+    for (int k = 0; k < RG; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int tile = t0; tile < t1; ++tile) {
+        load(tile);
+#pragma unroll
+        for (int u = 0; u < kTileBatches; ++u)
+            if (u * 256 < npix && tid + u * 256 < npix) *(f4*)(Xs + (tid + u * 256) * 4) = xv[u];
+        // (the last columns' reads of the last pixels run past the input: finite values, dropped)
+        if (tid < 16) Xs[npix * 4 + tid] = 0.f;
+#pragma unroll
+        for (int u = 0; u < NG; ++u) *(f4*)(Ds + ((tid + u * 256) >> 2) * LDW + q * 4) = dv[u];
         __syncthreads();
-        for (int e = tid; e < NSG * 256; e += 256) {
-            const int sg = e >> 8, col = (e >> 4) & 15, cc = e & 15, s = sg * 4 + (cc >> 2);
-            const float v = ((red[e] + red[NSG * 256 + e]) + red[2 * NSG * 256 + e]) + red[3 * NSG * 256 + e];
-            if (s < KS && co0 + col < a.Cout) out[(long)(co0 + col) * (KS * KS * 4) + (r * KS + s) * 4 + (cc & 3)] = v;
+#pragma unroll 1
+        for (int g = 0; g < NG; ++g) {
+            const int tr = box_div(tile, t.nc_inv), R0 = tr * t.OH;
+            const int p = (wave * NG + g) * 16 + gi * 4;
+            const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
+            const bool ok = oh < min(t.OH, t.rows - R0);
+            const int b0 = ok ? ((box_prow(t, R0 + oh) - box_prow(t, R0)) * t.IW + ow * ST) * 4 + li : li;
+            const int left = ok ? min(t.OW, t.Wo - (tile - tr * t.nc) * t.OW) - ow : 0;   // slots that hold a pixel
+#pragma unroll 1
+            for (int j = 0; j < 4; ++j) {
+                const float d = Ds[(p + j) * LDW + li];
+#pragma unroll
+                for (int k = 0; k < RG; ++k) {
+                    const float v = Xs[b0 + ((k / NSG) * t.IW + (k % NSG) * 4) * 4 + j * JST];
+                    acc[k] = mfma16x16x4(d, j < left ? v : 0.f, acc[k]);
+                }
+            }
         }
         __syncthreads();
     }
+    finish();
 }
 
 // Boxes of a stem's weight gradient: 256 or 128 slots, at most 1024 workgroups.
@@ -1701,15 +1802,26 @@ static bool pick_wgrad_stem(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
     return found;
 }
 
-template <int KS, int ST>
+template <int KS, int ST, bool FULL>
 static hipError_t launch_wg_stem(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
                                  hipStream_t st) {
     dim3 grid((unsigned)c.splits, (unsigned)((a.Cout + 15) / 16));
     if (c.ng == 4)
-        launch((conv_wgrad_stem_f32<KS, 4, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per);
+        launch((conv_wgrad_stem_f32<KS, 4, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per);
     else
-        launch((conv_wgrad_stem_f32<KS, 2, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per);
+        launch((conv_wgrad_stem_f32<KS, 2, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per);
     return hipGetLastError();
+}
+
+template <bool FULL>
+static hipError_t dispatch_wg_stem(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
+                                   hipStream_t st) {
+    if (a.R == 3) {
+        if (a.stride == 1) return launch_wg_stem<3, 1, FULL>(dY, X, part, a, c, st);
+        return launch_wg_stem<3, 2, FULL>(dY, X, part, a, c, st);
+    }
+    if (a.stride == 1) return launch_wg_stem<7, 1, FULL>(dY, X, part, a, c, st);
+    return launch_wg_stem<7, 2, FULL>(dY, X, part, a, c, st);
 }
 
 WgradPlan wgrad_plan(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride, int pad) {
@@ -1751,17 +1863,31 @@ static hipError_t launch_wg(const float* dY, const float* X, float* part, const 
     return hipGetLastError();
 }
 
-template <int RS, int ST>
+template <int RS, int ST, bool FULL>
 static hipError_t launch_wg_tile(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
                                  const float* in_ss, hipStream_t st) {
     dim3 grid((unsigned)c.splits, (unsigned)((a.Cout + 15) / 16), (unsigned)((a.Cin_p + 15) / 16));
     if (c.ng == 4)
-        launch((conv_wgrad_tile_f32<RS, 4, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per, in_ss);
+        launch((conv_wgrad_tile_f32<RS, 4, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+               in_ss);
     else if (c.ng == 2)
-        launch((conv_wgrad_tile_f32<RS, 2, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per, in_ss);
+        launch((conv_wgrad_tile_f32<RS, 2, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+               in_ss);
     else
-        launch((conv_wgrad_tile_f32<RS, 1, ST>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per, in_ss);
+        launch((conv_wgrad_tile_f32<RS, 1, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+               in_ss);
     return hipGetLastError();
+}
+
+template <bool FULL>
+static hipError_t dispatch_wg_tile(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
+                                   const float* in_ss, hipStream_t st) {
+    if (a.R == 1) {
+        if (a.stride == 1) return launch_wg_tile<1, 1, FULL>(dY, X, part, a, c, in_ss, st);
+        return launch_wg_tile<1, 2, FULL>(dY, X, part, a, c, in_ss, st);
+    }
+    if (a.stride == 1) return launch_wg_tile<9, 1, FULL>(dY, X, part, a, c, in_ss, st);
+    return launch_wg_tile<9, 2, FULL>(dY, X, part, a, c, in_ss, st);
 }
 
 hipError_t launch_conv_wgrad(const float* dY, const float* X, float* part, int Nb, int Hi, int Wi, int Cin_p,
@@ -1773,23 +1899,15 @@ hipError_t launch_conv_wgrad(const float* dY, const float* X, float* part, int N
         WgTileCfg c;
         if (!pick_wgrad_stem(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c) || c.splits != p.splits)
             return hipErrorInvalidValue;
-        if (R == 3) {
-            if (stride == 1) return launch_wg_stem<3, 1>(dY, X, part, a, c, st);
-            return launch_wg_stem<3, 2>(dY, X, part, a, c, st);
-        }
-        if (stride == 1) return launch_wg_stem<7, 1>(dY, X, part, a, c, st);
-        return launch_wg_stem<7, 2>(dY, X, part, a, c, st);
+        return box_full(c.t, c.ng * 64) ? dispatch_wg_stem<true>(dY, X, part, a, c, st)
+                                        : dispatch_wg_stem<false>(dY, X, part, a, c, st);
     }
     if (p.tile) {
         WgTileCfg c;
         if (!pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c) || c.splits != p.splits)
             return hipErrorInvalidValue;
-        if (R == 1) {
-            if (stride == 1) return launch_wg_tile<1, 1>(dY, X, part, a, c, in_ss, st);
-            return launch_wg_tile<1, 2>(dY, X, part, a, c, in_ss, st);
-        }
-        if (stride == 1) return launch_wg_tile<9, 1>(dY, X, part, a, c, in_ss, st);
-        return launch_wg_tile<9, 2>(dY, X, part, a, c, in_ss, st);
+        return box_full(c.t, c.ng * 64) ? dispatch_wg_tile<true>(dY, X, part, a, c, in_ss, st)
+                                        : dispatch_wg_tile<false>(dY, X, part, a, c, in_ss, st);
     }
     if (p.tm == 1) return launch_wg<1, 4>(dY, X, part, a, p, st);
     if (p.tm == 2) return launch_wg<2, 4>(dY, X, part, a, p, st);

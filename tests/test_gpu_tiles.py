@@ -208,3 +208,50 @@ def test_large_copies_to_the_host():
 def test_bf16_channels_in_eights(case):
     from tests.test_gpu_bf16 import test_bf16_conv_passes
     test_bf16_conv_passes(case)
+
+
+# cin, c1, k, stride, hw, batch: one infinite pixel in an image's last column
+@pytest.mark.parametrize("case", [
+    (3, 16, 3, 1, 13, 3),
+    (3, 32, 7, 2, 25, 2),
+    (16, 16, 3, 1, 13, 3),
+    (16, 32, 3, 1, 30, 5),
+    (20, 16, 3, 1, 58, 12),
+    (16, 32, 3, 2, 25, 2),
+], ids=lambda c: "x".join(map(str, c)))
+def test_weight_gradient_keeps_an_infinity_in_its_place(case):
+    """An infinite input pixel that every output clips (its weights are
+    negative, a ReLU follows) reaches the weight-gradient entries of its own
+    channel and of the taps that read it, and no other entry: those are bit
+    for bit what a large finite pixel leaves.  Slots of a box that hold no
+    output pixel lie right of the last column and must not read it."""
+    cin, c1, k, st, hw, n = case
+    pad = k // 2
+    o, p = T.twin_conv_net(cin, c1, k, st, pad, 16, hw)
+    x, img, lab = grid_inputs(o, 11, n)
+    w = x[:c1 * cin * k * k].reshape(c1, cin, k, k)
+    w[:, 0] = -np.abs(w[:, 0]) - 0.25
+    row, col = hw // 2, hw - 1
+    taps = np.zeros((k, k), bool)
+    for r in range(k):
+        for s in range(k):
+            h, v = row + pad - r, col + pad - s
+            ho = (hw + 2 * pad - k) // st + 1
+            taps[r, s] = h % st == 0 and v % st == 0 and 0 <= h // st < ho and 0 <= v // st < ho
+    assert taps.any() and not taps.all()
+    grads = []
+    for value in (2.0 ** 20, np.inf):
+        img[n - 1, 0, row, col] = value
+        with lpp.Context(p, K=1, batch=n) as ctx:
+            ctx.set_params(x)
+            i, t = dev(img, lab)
+            torch.cuda.synchronize()
+            ctx.step(0, i, t, 0, 0.0)
+            assert np.all(np.isfinite(ctx.get_logits(0)))
+            grads.append(ctx.get_grad(0))
+    reached = np.zeros((c1, cin, k, k), bool)
+    reached[:, 0] = taps
+    same = np.ones(grads[0].size, bool)
+    same[:reached.size] = ~reached.ravel()
+    assert np.all(np.isfinite(grads[0]))
+    assert np.array_equal(grads[0][same], grads[1][same])
