@@ -1401,7 +1401,15 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32(const float* __restrict__ 
 // and by the MFMAs where several boxes pipeline.  Held to 168 registers, three
 // workgroups to a compute unit (with two, 16 x 56x56x64 takes 54 us instead of
 // 45, ResNet-20's stages 11.2 instead of 10.8).
+// An accumulator takes at most kWgChain MFMAs in a row (ragged boxes:
+// kWgChainRagged); then the workgroup's sums go to fp64 and it starts again, so
+// the error does not grow with the boxes of a workgroup.  Root mean square
+// error of 64 x 32x32, 128 -> 128 channels (43 boxes), relative: 6.6e-8, in one
+// chain 2.2e-7, with a partial for every 16 MFMAs 6.9e-8; 100 x 28x28x64
+// (ragged): 1.2e-7, in one chain 2.0e-7, the GEMM kernel 1.8e-7.  16 x
+// 56x56x64 takes 51.6 us, 48.0 in one chain, 50.6 in chains of 32.
 constexpr int kWgBatches = 6;   // staged input quads per thread and box, at most
+constexpr int kWgChain = 16, kWgChainRagged = 32;
 
 template <int RS, int NG, int ST, bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8)))
@@ -1464,11 +1472,54 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
 #pragma unroll
     for (int k = 0; k < RS; ++k) toff[k] = K1 ? 0 : ((k / 3) * t.IW + k % 3) * LDW;
     f4 acc[RS];
-#pragma unroll
-    for (int k = 0; k < RS; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
-
     const int t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);
     const int sdst = (tid >> 2) * LDW + q * 4;
+    // each wave's RS x 16 x 16 block into its own LDS slice, then the four
+    // slices summed in order
+    float* red = lds;   // [4][RS][16 co][16 c]
+    auto waves = [&]() {
+#pragma unroll
+        for (int k = 0; k < RS; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) red[((wave * RS + k) * 16 + gi * 4 + i) * 16 + li] = acc[k][i];
+        lds_barrier();
+    };
+    auto wave_sum = [&](int k) {
+        const int e = k * 256 + tid;
+        return ((red[e] + red[RS * 256 + e]) + red[2 * RS * 256 + e]) + red[3 * RS * 256 + e];
+    };
+    // runs of kRun boxes leave their sums in fp64, entry tid of every tap in thread tid
+    constexpr int kRun = NG == 4 ? 1 : (FULL ? kWgChain : kWgChainRagged) / (4 * NG);
+    double tot[RS];
+    const bool chained = NG < 4 && t1 - t0 > kRun;
+    auto leave = [&]() {
+        waves();
+#pragma unroll
+        for (int k = 0; k < RS; ++k) {
+            tot[k] += (double)wave_sum(k);
+            acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        lds_barrier();
+    };
+    auto finish = [&]() {
+        waves();
+        float* out = part + (long)blockIdx.x * a.Cout * Ktot;
+        const int co = co0 + (tid >> 4), c = c0 + (tid & 15);
+        bool nan = false;
+#pragma unroll
+        for (int k = 0; k < RS; ++k) {
+            float v = wave_sum(k);
+            if (chained) v = (float)(tot[k] + (double)v);
+            if (co < a.Cout && c < a.Cin_p) out[(long)co * Ktot + k * a.Cin_p + c] = v;
+            nan |= v != v;
+        }
+        return nan;
+    };
+#pragma unroll
+    for (int k = 0; k < RS; ++k) {
+        acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+        tot[k] = 0.0;
+    }
     load(t0);
     for (int tile = t0; tile < t1; ++tile) {
         if (in_ss) {
@@ -1530,32 +1581,17 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
                 for (int k = 0; k < RS; ++k) acc[k] = mfma16x16x4(av[g & 1][j], bv[g & 1][k][j], acc[k]);
         }
         lds_barrier();   // the staged box is dead
+        if (chained && (tile - t0) % kRun == kRun - 1 && tile + 1 < t1) leave();
     }
 
-    // each wave's RS x 16 x 16 block into its own LDS slice, then the four
-    // slices summed in order
-    float* red = lds;   // [4][RS][16 co][16 c]
-    float* out = part + (long)blockIdx.x * a.Cout * Ktot;
-    auto finish = [&]() {
-#pragma unroll
-        for (int k = 0; k < RS; ++k)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) red[((wave * RS + k) * 16 + gi * 4 + i) * 16 + li] = acc[k][i];
-        __syncthreads();
-        bool nan = false;
-        for (int e = tid; e < RS * 256; e += 256) {
-            const int k = e >> 8, col = (e >> 4) & 15, c = e & 15;
-            const float v = ((red[e] + red[RS * 256 + e]) + red[2 * RS * 256 + e]) + red[3 * RS * 256 + e];
-            if (co0 + col < a.Cout && c0 + c < a.Cin_p) out[(long)(co0 + col) * Ktot + k * a.Cin_p + c0 + c] = v;
-            nan |= v != v;
-        }
-        return nan;
-    };
     const bool nan = finish();
     if (FULL || !__syncthreads_or(nan)) return;
     // the same sums in the same order, zeros for both operands at slots without a pixel
 #pragma unroll
-    for (int k = 0; k < RS; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < RS; ++k) {
+        acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+        tot[k] = 0.0;
+    }
 #pragma unroll 1
     for (int tile = t0; tile < t1; ++tile) {
         load(tile);
@@ -1594,6 +1630,7 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
             }
         }
         __syncthreads();
+        if (chained && (tile - t0) % kRun == kRun - 1 && tile + 1 < t1) leave();
     }
     finish();
 }
@@ -1637,7 +1674,7 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
 // row are formed and dropped.  (128 x 32x32, 4 -> 16: 10.3 us with a column
 // tile per tap, 7.4 here; 4 -> 96: 36, 19; 7x7/2, 4 -> 64: 97, 82.)
 template <int KS, int NG, int ST, bool FULL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 3 ? 4 : 3, 8)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 3 && (FULL || NG == 2) ? 4 : 3, 8)))
 void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__ X,
                                                            float* __restrict__ part, WgArgs a, BoxGeom t, int tiles,
                                                            int per) {
@@ -1676,9 +1713,52 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
         }
     };
     f4 acc[RG];
+    const int t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);
+    // the four waves' blocks summed in order, KS rows at a time
+    float* red = lds;   // [4][NSG][16 co][16]
+    auto rows = [&](auto use) {
+#pragma unroll
+        for (int r = 0; r < KS; ++r) {
+#pragma unroll
+            for (int sg = 0; sg < NSG; ++sg)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    red[((wave * NSG + sg) * 16 + gi * 4 + i) * 16 + li] = acc[r * NSG + sg][i];
+            lds_barrier();
+#pragma unroll
+            for (int sg = 0; sg < NSG; ++sg) {
+                const int e = sg * 256 + tid;
+                use(r, sg, ((red[e] + red[NSG * 256 + e]) + red[2 * NSG * 256 + e]) + red[3 * NSG * 256 + e]);
+            }
+            lds_barrier();
+        }
+    };
+    // 3x3: runs of kRun boxes leave their sums in fp64 (7x7: see pick_wgrad_stem)
+    constexpr int kRun = (FULL ? kWgChain : kWgChainRagged) / (4 * NG);
+    double tot[KS == 3 ? RG : 1];
+    const bool chained = KS == 3 && t1 - t0 > kRun;
+    auto leave = [&]() {
+        rows([&](int r, int sg, float v) { tot[KS == 3 ? r * NSG + sg : 0] += (double)v; });
+#pragma unroll
+        for (int k = 0; k < RG; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto finish = [&]() {
+        float* out = part + (long)blockIdx.x * a.Cout * (KS * KS * 4);
+        bool nan = false;
+        rows([&](int r, int sg, float v) {
+            if (chained) v = (float)(tot[KS == 3 ? r * NSG + sg : 0] + (double)v);
+            const int co = co0 + (tid >> 4), s = sg * 4 + ((tid & 15) >> 2);
+            if (s < KS && co < a.Cout) {
+                out[(long)co * (KS * KS * 4) + (r * KS + s) * 4 + (tid & 3)] = v;
+                nan |= v != v;
+            }
+        });
+        return nan;
+    };
 #pragma unroll
     for (int k = 0; k < RG; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
-    const int t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);
+#pragma unroll
+    for (double& v : tot) v = 0.0;
     load(t0);
     for (int tile = t0; tile < t1; ++tile) {
 #pragma unroll
@@ -1712,37 +1792,15 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
             }
         }
         lds_barrier();
+        if (chained && (tile - t0) % kRun == kRun - 1 && tile + 1 < t1) leave();
     }
-    // the four waves' blocks summed in order, KS rows at a time
-    float* red = lds;   // [4][NSG][16 co][16]
-    float* out = part + (long)blockIdx.x * a.Cout * (KS * KS * 4);
-    auto finish = [&]() {
-        bool nan = false;
-#pragma unroll
-        for (int r = 0; r < KS; ++r) {
-#pragma unroll
-            for (int sg = 0; sg < NSG; ++sg)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    red[((wave * NSG + sg) * 16 + gi * 4 + i) * 16 + li] = acc[r * NSG + sg][i];
-            __syncthreads();
-            for (int e = tid; e < NSG * 256; e += 256) {
-                const int sg = e >> 8, col = (e >> 4) & 15, cc = e & 15, s = sg * 4 + (cc >> 2);
-                const float v = ((red[e] + red[NSG * 256 + e]) + red[2 * NSG * 256 + e]) + red[3 * NSG * 256 + e];
-                if (s < KS && co0 + col < a.Cout) {
-                    out[(long)(co0 + col) * (KS * KS * 4) + (r * KS + s) * 4 + (cc & 3)] = v;
-                    nan |= v != v;
-                }
-            }
-            __syncthreads();
-        }
-        return nan;
-    };
     const bool nan = finish();
     if (FULL || !__syncthreads_or(nan)) return;
     // the same sums in the same order, zeros for both operands at slots without a pixel
 #pragma unroll
     for (int k = 0; k < RG; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (double& v : tot) v = 0.0;
 #pragma unroll 1
     for (int tile = t0; tile < t1; ++tile) {
         load(tile);
@@ -1773,11 +1831,14 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
             }
         }
         __syncthreads();
+        if (chained && (tile - t0) % kRun == kRun - 1 && tile + 1 < t1) leave();
     }
     finish();
 }
 
 // Boxes of a stem's weight gradient: 256 or 128 slots, at most 1024 workgroups.
+// (A 7x7 one keeps one chain: 14 sums in fp64 do not fit its registers.  16 x
+// 224x224, 4 -> 64: 49 MFMAs in a row; the GEMM kernel takes 98.)
 static bool pick_wgrad_stem(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride,
                             int pad, WgTileCfg& out) {
     if (Cin_p != 4 || Cout % 4 || R != S || (R != 3 && R != 7) || (stride != 1 && stride != 2)) return false;

@@ -255,3 +255,38 @@ def test_weight_gradient_keeps_an_infinity_in_its_place(case):
     same[:reached.size] = ~reached.ravel()
     assert np.all(np.isfinite(grads[0]))
     assert np.array_equal(grads[0][same], grads[1][same])
+
+
+# cin, cout, k, hw, batch: many boxes to a workgroup (28 and 50: ragged boxes)
+@pytest.mark.parametrize("case", [(128, 128, 3, 32, 64), (64, 64, 3, 28, 100), (4, 64, 3, 64, 64), (4, 64, 3, 50, 90)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_weight_gradient_error_does_not_grow_with_the_tensor(case):
+    """Against 64-bit sums over the pass's own operands.  n additions of
+    random terms in a row round to 2^-24 sqrt(n / 6) of the root of the terms'
+    squares; n is 16, on ragged boxes 32.  What follows in fp32 (four waves,
+    the splits) rounds the sum itself: 2^-24 of it.  A quarter on top."""
+    cin, c1, k, hw, n = case
+    o, p = T.twin_conv_net(cin, c1, k, 1, k // 2, 16, hw)
+    g = torch.Generator("cuda").manual_seed(3)
+    img = torch.randn((n, cin, hw, hw), generator=g, device="cuda")
+    lab = torch.randint(6, (n,), generator=g, device="cuda", dtype=torch.int32)
+    with lpp.Context(p, K=1, batch=n) as ctx:
+        ctx.set_params(T.init_x(o.specs, 5).astype(np.float32))
+        torch.cuda.synchronize()
+        ctx.step(0, img, lab, 0, 0.0)
+        got = ctx.get_grad(0)[:c1 * cin * k * k].reshape(c1, cin, k, k)
+        dy = torch.from_numpy(ctx.get_activation_grad(0, 0, (c1, hw, hw))).cuda().double()
+    d = dy.permute(1, 0, 2, 3).reshape(c1, -1).contiguous()
+    pad = torch.nn.functional.pad(img.double(), (k // 2,) * 4)
+    ref = np.empty(got.shape)
+    sq = np.empty(got.shape)
+    for r in range(k):
+        for s in range(k):
+            v = pad[:, :, r:r + hw, s:s + hw].permute(0, 2, 3, 1).reshape(-1, cin).contiguous()
+            ref[:, :, r, s] = (d @ v).cpu().numpy()
+            sq[:, :, r, s] = (d.square() @ v.square()).cpu().numpy()
+    u, chain = 2.0 ** -24, 16 if hw & (hw - 1) == 0 else 32
+    err = np.sqrt(np.mean((got - ref) ** 2 / sq))
+    bound = 1.25 * u * np.sqrt(chain / 6 + np.mean(ref ** 2 / sq))
+    print(case, "error %.3e, bound %.3e" % (err, bound), file=sys.stderr, flush=True)
+    assert err < bound
