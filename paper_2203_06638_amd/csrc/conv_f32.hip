@@ -1395,26 +1395,29 @@ __global__ __launch_bounds__(256) void conv_wgrad_f32(const float* __restrict__ 
 // order and every workgroup writes its own partial, summed in order by the
 // reduce kernel.  What a slot without a pixel reads of X belongs to other
 // outputs, and zero times an infinity there is NaN: a workgroup that finds a
-// NaN among its sums forms them once more with zeros for both operands.
-// (Zeros chosen at every MFMA cost up to 9% of a step.)
+// NaN among its sums forms them once more with zeros for both operands (zeros
+// chosen at every MFMA cost up to 9% of a step, the look for a NaN 2% of the
+// kernel).
 // Bound by the staging's latency at ResNet-20's sizes (one box per workgroup)
 // and by the MFMAs where several boxes pipeline.  Held to 168 registers, three
 // workgroups to a compute unit (with two, 16 x 56x56x64 takes 54 us instead of
 // 45, ResNet-20's stages 11.2 instead of 10.8).
-// An accumulator takes at most kWgChain MFMAs in a row (ragged boxes:
-// kWgChainRagged); then the workgroup's sums go to fp64 and it starts again, so
-// the error does not grow with the boxes of a workgroup.  Root mean square
-// error of 64 x 32x32, 128 -> 128 channels (43 boxes), relative: 6.6e-8, in one
-// chain 2.2e-7, with a partial for every 16 MFMAs 6.9e-8; 100 x 28x28x64
-// (ragged): 1.2e-7, in one chain 2.0e-7, the GEMM kernel 1.8e-7.  16 x
-// 56x56x64 takes 51.6 us, 48.0 in one chain, 50.6 in chains of 32.
+// An accumulator takes at most 64 MFMAs in a row (wg_run); then the
+// workgroup's sums go to fp64 and it starts again, so the error does not grow
+// with the boxes of a workgroup.
 constexpr int kWgBatches = 6;   // staged input quads per thread and box, at most
-constexpr int kWgChain = 16, kWgChainRagged = 32;
+// Boxes between two such moments: 16 MFMAs where rows are a power of two long,
+// else 64.  Root mean square error, relative, of 64 x 32x32, 128 -> 128
+// channels (43 boxes): 6.6e-8, in one chain 2.2e-7, with a partial for every 16
+// MFMAs 6.9e-8; of 100 x 28x28x64: 1.5e-7, in one chain 2.0e-7, the GEMM kernel
+// (88 in a row) 1.8e-7.  The time follows: 16 x 56x56x64 takes 48.0 us in one
+// chain, 51.6 with 16, 49.8 with 64; 87 x 38x38x44 65.8 and, with 64, 69.6.
+static int wg_run(int ng, int Wo) { return std::max(1, ((Wo & (Wo - 1)) == 0 ? 16 : 64) / (4 * ng)); }
 
 template <int RS, int NG, int ST, bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8)))
 void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__ X, float* __restrict__ part, WgArgs a,
-                         BoxGeom t, int tiles, int per, const float* __restrict__ in_ss) {
+                         BoxGeom t, int tiles, int per, int run, const float* __restrict__ in_ss) {
     constexpr bool K1 = RS == 1;
     constexpr int LDW = 20;
     constexpr int JST = (K1 ? 1 : ST) * LDW;   // LDS distance between a lane's four pixels
@@ -1476,22 +1479,29 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
     const int sdst = (tid >> 2) * LDW + q * 4;
     // each wave's RS x 16 x 16 block into its own LDS slice, then the four
     // slices summed in order
-    float* red = lds;   // [4][RS][16 co][16 c]
+    float* red = lds;   // [4][RS][16 co][16 c], then for each wave whether it met a NaN
+    float all = 0.f;    // a NaN once one was among the sums
     auto waves = [&]() {
 #pragma unroll
         for (int k = 0; k < RS; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) red[((wave * RS + k) * 16 + gi * 4 + i) * 16 + li] = acc[k][i];
+            for (int i = 0; i < 4; ++i) {
+                red[((wave * RS + k) * 16 + gi * 4 + i) * 16 + li] = acc[k][i];
+                if (!FULL) all += acc[k][i];
+            }
+        if (!FULL) {
+            const bool nan = __any(all != all);
+            if (lane == 0) red[4 * RS * 256 + wave] = nan ? 1.f : 0.f;
+        }
         lds_barrier();
     };
     auto wave_sum = [&](int k) {
         const int e = k * 256 + tid;
         return ((red[e] + red[RS * 256 + e]) + red[2 * RS * 256 + e]) + red[3 * RS * 256 + e];
     };
-    // runs of kRun boxes leave their sums in fp64, entry tid of every tap in thread tid
-    constexpr int kRun = NG == 4 ? 1 : (FULL ? kWgChain : kWgChainRagged) / (4 * NG);
+    // runs of `run` boxes leave their sums in fp64, entry tid of every tap in thread tid
     double tot[RS];
-    const bool chained = NG < 4 && t1 - t0 > kRun;
+    const bool chained = NG < 4 && t1 - t0 > run;
     auto leave = [&]() {
         waves();
 #pragma unroll
@@ -1505,15 +1515,12 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
         waves();
         float* out = part + (long)blockIdx.x * a.Cout * Ktot;
         const int co = co0 + (tid >> 4), c = c0 + (tid & 15);
-        bool nan = false;
 #pragma unroll
         for (int k = 0; k < RS; ++k) {
             float v = wave_sum(k);
             if (chained) v = (float)(tot[k] + (double)v);
             if (co < a.Cout && c < a.Cin_p) out[(long)co * Ktot + k * a.Cin_p + c] = v;
-            nan |= v != v;
         }
-        return nan;
     };
 #pragma unroll
     for (int k = 0; k < RS; ++k) {
@@ -1581,11 +1588,14 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
                 for (int k = 0; k < RS; ++k) acc[k] = mfma16x16x4(av[g & 1][j], bv[g & 1][k][j], acc[k]);
         }
         lds_barrier();   // the staged box is dead
-        if (chained && (tile - t0) % kRun == kRun - 1 && tile + 1 < t1) leave();
+        if (chained && (tile + 1 - t0) % run == 0 && tile + 1 < t1) leave();
     }
 
-    const bool nan = finish();
-    if (FULL || !__syncthreads_or(nan)) return;
+    finish();
+    if (FULL) return;
+    const f4 nan = *(const f4*)(red + 4 * RS * 256);
+    if (nan[0] + nan[1] + nan[2] + nan[3] == 0.f) return;
+    __syncthreads();
     // the same sums in the same order, zeros for both operands at slots without a pixel
 #pragma unroll
     for (int k = 0; k < RS; ++k) {
@@ -1630,36 +1640,55 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
             }
         }
         __syncthreads();
-        if (chained && (tile - t0) % kRun == kRun - 1 && tile + 1 < t1) leave();
+        if (chained && (tile + 1 - t0) % run == 0 && tile + 1 < t1) leave();
     }
     finish();
 }
 
 // Boxes of the spatially tiled weight gradient, or false when it does not
-// apply (the GEMM-style kernel takes those passes).  At most 768 workgroups, one
-// round of three to a compute unit: each takes a single box of 256 slots where
-// that gives at least 512 workgroups, else a run of boxes of 128 slots, or of
-// 64 where 128 leave fewer than 512 (measured over 512-1536 workgroups and all
-// three sizes: within 4% of the best of 22 passes).
-struct WgTileCfg { int ng, tiles, per, splits; BoxGeom t; size_t lds; };
+// apply (the GEMM-style kernel takes those passes).  Up to 384 channel blocks:
+// at most 768 workgroups, one round of three to a compute unit; each takes a
+// single box of 256 slots where that gives at least 512 workgroups, else a run
+// of boxes of 128 slots, or of 64 where 128 leave fewer than 512 and 64 give
+// more (measured over 512-1536 workgroups and all three sizes: within 4% of
+// the best of 22 passes).  More blocks do not divide a round: up to four
+// splits, at least 1536 workgroups where they suffice, even out the rounds (16
+// x 14x14: 320 -> 320 channels with one split 110 us, with four 95; 448 -> 448
+// 202, two 177; 768 blocks 152, two 152, three 160).
+// A workgroup reads its 16 output and 16 input channels of every pixel, four
+// times the traffic of the GEMM kernel's 64 x 64 tiles, which counts where taps
+// do not share it.  1x1 passes of 2^28 products and more (3e8 below 32768
+// pixels) take the GEMM kernel: 64 x 32x32, 64 -> 64, 2^28, 37 us and 31 there,
+// 96 -> 96 65 and 44; 32 x 28x28, 320 -> 320, 299 and 93; 96 -> 96, 2.3e8, 25
+// and 33; 16 x 32x32, 64 -> 256, 2.7e8, 28 and 32 (16 channels leave its tiles
+// mostly empty: 100 x 64x64, 16 -> 64, 52 and 68).  So do 3x3 passes of stride 2
+// from 128 blocks on: 32 x 14x14, 128 -> 256, 71 and 67, 320 -> 320 217 and 174;
+// 40 x 20x20, 96 -> 192, 72 blocks, 72 and 77.
+struct WgTileCfg { int ng, tiles, per, splits, run; BoxGeom t; size_t lds; };
 static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride,
                             int pad, WgTileCfg& out) {
     if (Cin_p % 4 || Cout % 4 || R != S || (R != 1 && R != 3) || (stride != 1 && stride != 2)) return false;
     if (Cin_p < 16 && Cout > 32) return false;   // mostly empty MFMA columns: the GEMM kernel is as fast
     if (!buf_fits((double)Nb * Hi * Wi * Cin_p) || !buf_fits((double)Nb * Ho * Wo * Cout)) return false;
     const long blocks = (long)((Cout + 15) / 16) * ((Cin_p + 15) / 16);
+    const double M = (double)Nb * Ho * Wo;
+    if (R == 1 ? Cin_p > 16 && M * Cin_p * Cout >= (M >= 32768 ? 268435456.0 : 3e8) : stride == 2 && blocks >= 128)
+        return false;
+    const long most = blocks <= 384 ? 768 / blocks : std::min<long>(4, (1535 + blocks) / blocks);
     bool found = false;
     for (int ng : {4, 2, 1}) {
         WgTileCfg c;
         if (!box_pick(c.t, Nb, Ho, Wo, R, R == 1 ? 1 : stride, pad, ng * 64, 4, kWgBatches)) continue;
         c.ng = ng;
         c.lds = sizeof(float) *
-                std::max<size_t>(((size_t)c.t.IH * c.t.IW + ng * 64) * 20, (size_t)4 * R * S * 256);
+                std::max<size_t>(((size_t)c.t.IH * c.t.IW + ng * 64) * 20, (size_t)4 * R * S * 256 + 4);
         c.tiles = box_tiles(c.t);
-        const long splits = std::min<long>(c.tiles, std::max<long>(1, 768 / blocks));
+        const long splits = std::min<long>(c.tiles, most);
         c.per = (int)((c.tiles + splits - 1) / splits);
         c.splits = (c.tiles + c.per - 1) / c.per;
+        c.run = wg_run(ng, Wo);
         if (ng == 4 && (c.per > 1 || c.splits * blocks < 512)) continue;
+        if (found && c.splits <= out.splits) break;
         found = true;
         out = c;
         if (c.splits * blocks >= 512) break;
@@ -1677,7 +1706,7 @@ template <int KS, int NG, int ST, bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 3 && (FULL || NG == 2) ? 4 : 3, 8)))
 void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__ X,
                                                            float* __restrict__ part, WgArgs a, BoxGeom t, int tiles,
-                                                           int per) {
+                                                           int per, int run) {
     constexpr int NSG = (KS + 3) / 4, RG = KS * NSG, LDW = 20, JST = ST * 4, TP = NG * 64;
     extern __shared__ float lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1715,8 +1744,15 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
     f4 acc[RG];
     const int t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);
     // the four waves' blocks summed in order, KS rows at a time
-    float* red = lds;   // [4][NSG][16 co][16]
+    float* red = lds;   // [4][NSG][16 co][16], then for each wave whether it met a NaN
+    float all = 0.f;    // a NaN once one was among the sums
     auto rows = [&](auto use) {
+        if (!FULL) {
+#pragma unroll
+            for (int k = 0; k < RG; ++k) all += (acc[k][0] + acc[k][1]) + (acc[k][2] + acc[k][3]);
+            const bool nan = __any(all != all);
+            if (lane == 0) red[4 * NSG * 256 + wave] = nan ? 1.f : 0.f;
+        }
 #pragma unroll
         for (int r = 0; r < KS; ++r) {
 #pragma unroll
@@ -1733,10 +1769,9 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
             lds_barrier();
         }
     };
-    // 3x3: runs of kRun boxes leave their sums in fp64 (7x7: see pick_wgrad_stem)
-    constexpr int kRun = (FULL ? kWgChain : kWgChainRagged) / (4 * NG);
+    // 3x3: runs of `run` boxes leave their sums in fp64 (7x7: see pick_wgrad_stem)
     double tot[KS == 3 ? RG : 1];
-    const bool chained = KS == 3 && t1 - t0 > kRun;
+    const bool chained = KS == 3 && t1 - t0 > run;
     auto leave = [&]() {
         rows([&](int r, int sg, float v) { tot[KS == 3 ? r * NSG + sg : 0] += (double)v; });
 #pragma unroll
@@ -1744,16 +1779,11 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
     };
     auto finish = [&]() {
         float* out = part + (long)blockIdx.x * a.Cout * (KS * KS * 4);
-        bool nan = false;
         rows([&](int r, int sg, float v) {
             if (chained) v = (float)(tot[KS == 3 ? r * NSG + sg : 0] + (double)v);
             const int co = co0 + (tid >> 4), s = sg * 4 + ((tid & 15) >> 2);
-            if (s < KS && co < a.Cout) {
-                out[(long)co * (KS * KS * 4) + (r * KS + s) * 4 + (tid & 3)] = v;
-                nan |= v != v;
-            }
+            if (s < KS && co < a.Cout) out[(long)co * (KS * KS * 4) + (r * KS + s) * 4 + (tid & 3)] = v;
         });
-        return nan;
     };
 #pragma unroll
     for (int k = 0; k < RG; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
@@ -1792,10 +1822,13 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
             }
         }
         lds_barrier();
-        if (chained && (tile - t0) % kRun == kRun - 1 && tile + 1 < t1) leave();
+        if (chained && (tile + 1 - t0) % run == 0 && tile + 1 < t1) leave();
     }
-    const bool nan = finish();
-    if (FULL || !__syncthreads_or(nan)) return;
+    finish();
+    if (FULL) return;
+    const f4 nan = *(const f4*)(red + 4 * NSG * 256);
+    if (nan[0] + nan[1] + nan[2] + nan[3] == 0.f) return;
+    __syncthreads();
     // the same sums in the same order, zeros for both operands at slots without a pixel
 #pragma unroll
     for (int k = 0; k < RG; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
@@ -1831,7 +1864,7 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
             }
         }
         __syncthreads();
-        if (chained && (tile - t0) % kRun == kRun - 1 && tile + 1 < t1) leave();
+        if (chained && (tile + 1 - t0) % run == 0 && tile + 1 < t1) leave();
     }
     finish();
 }
@@ -1851,11 +1884,12 @@ static bool pick_wgrad_stem(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
         c.ng = ng;
         // a column tile reads up to 16 floats past its first tap's pixel
         c.lds = sizeof(float) * std::max<size_t>((size_t)ng * 64 * 20 + ((size_t)c.t.IH * c.t.IW + 4) * 4,
-                                                 (size_t)4 * ((R + 3) / 4) * 256);
+                                                 (size_t)4 * ((R + 3) / 4) * 256 + 4);
         c.tiles = box_tiles(c.t);
         const long splits = std::min<long>(c.tiles, std::max<long>(1, 1024 / blocks));
         c.per = (int)((c.tiles + splits - 1) / splits);
         c.splits = (c.tiles + c.per - 1) / c.per;
+        c.run = wg_run(ng, Wo);
         found = true;
         out = c;
         if (c.splits * blocks >= 512) break;
@@ -1868,9 +1902,11 @@ static hipError_t launch_wg_stem(const float* dY, const float* X, float* part, c
                                  hipStream_t st) {
     dim3 grid((unsigned)c.splits, (unsigned)((a.Cout + 15) / 16));
     if (c.ng == 4)
-        launch((conv_wgrad_stem_f32<KS, 4, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per);
+        launch((conv_wgrad_stem_f32<KS, 4, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+               c.run);
     else
-        launch((conv_wgrad_stem_f32<KS, 2, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per);
+        launch((conv_wgrad_stem_f32<KS, 2, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+               c.run);
     return hipGetLastError();
 }
 
@@ -1905,6 +1941,9 @@ WgradPlan wgrad_plan(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout
     long splits = (512 + tiles - 1) / tiles;
     const long max_splits = (M + 511) / 512;
     if (splits > max_splits) splits = max_splits;
+    // at most 32 MFMAs in a row where rows are a power of two long (as wg_run;
+    // 64 x 32x32, 160 -> 320, 1x1: 129 us instead of 124)
+    if ((Wo & (Wo - 1)) == 0) splits = std::max(splits, max_splits);
     if (splits < 1) splits = 1;
     long pps = (M + splits - 1) / splits;
     pps = (pps + 63) / 64 * 64;
@@ -1930,13 +1969,13 @@ static hipError_t launch_wg_tile(const float* dY, const float* X, float* part, c
     dim3 grid((unsigned)c.splits, (unsigned)((a.Cout + 15) / 16), (unsigned)((a.Cin_p + 15) / 16));
     if (c.ng == 4)
         launch((conv_wgrad_tile_f32<RS, 4, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
-               in_ss);
+               c.run, in_ss);
     else if (c.ng == 2)
         launch((conv_wgrad_tile_f32<RS, 2, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
-               in_ss);
+               c.run, in_ss);
     else
         launch((conv_wgrad_tile_f32<RS, 1, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
-               in_ss);
+               c.run, in_ss);
     return hipGetLastError();
 }
 
