@@ -389,6 +389,7 @@ struct BoxGeom {
     int Hp, step;               // padded rows of one image, rows between output rows
     int IH, IW;                 // staged rows and columns
     int pad_eff;                // input row of padded row hh: hh - pad_eff
+    int far;                    // an activation is larger than 32-bit offsets reach
     unsigned OWs_inv, IW_inv, Hper_inv, Hp_inv, nc_inv;
 };
 
@@ -405,10 +406,19 @@ __device__ __forceinline__ int box_prow(const BoxGeom& t, int R) {
 // Tensors are read through buffer descriptors: a load at kNoLoad lies past
 // every one and returns zero, so the zero padding costs no branch, and (unlike
 // a pointer chosen at run time, a flat address) the loads count apart from the
-// LDS accesses and stay in flight across a barrier and the MFMAs.
+// LDS accesses and stay in flight across a barrier and the MFMAs.  Offsets are
+// of 32 bits: for a larger activation (BoxGeom::far) the descriptor begins at
+// the box's first image or row and reaches at most to kNoLoad.  (The weight
+// gradients, which form it for every box, do so in variants of their own: 50
+// us on 16 x 56x56x64 without, 53 with.)
 constexpr unsigned kNoLoad = 0x80000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const float* p, long n) {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)(n * 4), 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, (int)(n < 0x1fffffffL ? n * 4 : 0x7ffffffcL), 0x00020000);
+}
+// rows first, first + 1, ... of a tensor of `rows` rows of n floats
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const float* p, int first, long n, int rows) {
+    if (first) p += first * n;
+    return buf_rsrc(p, (rows - first) * n);
 }
 __device__ __forceinline__ f4 buf_load4(__amdgpu_buffer_rsrc_t r, unsigned off, int soff) {
     return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
@@ -492,8 +502,15 @@ static bool box_pick(BoxGeom& out, int Nb, int Hper, int Wo, int ext, int step, 
            box_fill(out, Nb, Hper, Wo, ext, step, pad_eff);
 }
 
-// Bytes of a tensor of n floats addressable with the kernels' 32-bit offsets
+// n floats addressable with the kernels' 32-bit offsets
 static bool buf_fits(double n) { return 4.0 * n < 2147483648.0; }
+// so are the images that a box's staged rows may lie in (one more than its
+// output rows reach over: a box ends in the padding of the next), of `image`
+// floats; sets far
+static bool box_fits(BoxGeom& t, int Nb, double image) {
+    t.far = !buf_fits(Nb * image);
+    return buf_fits(((t.OH - 1) / t.Hper + 3) * image);
+}
 
 // Epilogue of a box tile: bias, the output block through LDS, the store (set,
 // add, ReLU) and the batch-norm sums (STATS).
@@ -664,7 +681,9 @@ __global__ __launch_bounds__(256) void conv_tile_f32(const float* __restrict__ s
     if (INBN) bn_fwd_coeffs(inbn, g.Cs, in_co, in_co + kFoldMaxC);
 
     // byte offsets of this thread's quads at channel group 0
-    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(src, (long)g.Nb * g.Hs * g.Ws * g.Cs);
+    const int n1 = t.far ? box_div(P0, t.Hp_inv) : 0;   // the descriptor's first image
+    const long image = (long)g.Hs * g.Ws * g.Cs;
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(src, n1, image, g.Nb);
     const __amdgpu_buffer_rsrc_t wr = buf_rsrc(B, (long)g.Ncols * RS * g.Cs);
     unsigned xo[kTileBatches], wo[NW];
 #pragma unroll
@@ -679,7 +698,7 @@ __global__ __launch_bounds__(256) void conv_tile_f32(const float* __restrict__ s
             const int h = (KS == 1 ? hh * g.stride : hh) - t.pad_eff;
             const int w = (KS == 1 ? (w0 + iw) * g.stride : w0 * g.stride + iw) - t.pad_eff;
             if (ih < t.IH && n < g.Nb && h >= 0 && h < g.Hs && w >= 0 && w < g.Ws)
-                xo[u] = (unsigned)(((n * g.Hs + h) * g.Ws + w) * g.Cs + q * 4) * 4u;
+                xo[u] = (unsigned)((((n - n1) * g.Hs + h) * g.Ws + w) * g.Cs + q * 4) * 4u;
         }
     }
 #pragma unroll
@@ -771,7 +790,7 @@ struct TileCfg { int tm, tn, tiles; BoxGeom t; size_t lds; };
 static bool pick_tile(int mode, const ConvGeom& g, TileCfg& out) {
     if (g.Cs % 4 || g.Cs < 16 || g.Ncols % 4 || g.R != g.S || (g.R != 1 && g.R != 3)) return false;
     if (mode == CONV_DGRAD && g.stride != 1) return false;
-    if (!buf_fits((double)g.Nb * g.Hs * g.Ws * g.Cs) || !buf_fits((double)g.Ncols * g.R * g.R * g.Cs)) return false;
+    if (!buf_fits((double)g.Ncols * g.R * g.R * g.Cs)) return false;
     static const int shapes[][2] = {{2, 2}, {2, 1}, {1, 1}};
     bool found = false;
     for (auto& sh : shapes) {
@@ -779,7 +798,8 @@ static bool pick_tile(int mode, const ConvGeom& g, TileCfg& out) {
         if (tn == 2 && (g.R != 1 || g.Ncols % 32)) continue;
         TileCfg c;
         if (!box_pick(c.t, g.Nb, g.Ho, g.Wo, g.R, g.R == 1 ? 1 : g.stride, mode == CONV_FWD ? g.pad : g.R - 1 - g.pad,
-                      tm * 64, 1, kTileBatches))
+                      tm * 64, 1, kTileBatches) ||
+            !box_fits(c.t, g.Nb, (double)g.Hs * g.Ws * g.Cs))
             continue;
         c.tm = tm;
         c.tn = tn;
@@ -867,7 +887,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const int npix = t.IH * t.IW;
     float* Ws = lds;                                  // [WR][LDW]
     float* Xs = lds + WR * LDW;                       // [npix][4], then a zero quad
-    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(src, (long)g.Nb * g.Hs * g.Ws * 4);
+    const int n1 = t.far ? box_div(P0, t.Hp_inv) : 0;   // the descriptor's first image
+    const long image = (long)g.Hs * g.Ws * 4;
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(src, n1, image, g.Nb);
     const __amdgpu_buffer_rsrc_t wr = buf_rsrc(B, (long)g.Ncols * KS * KS * 4);
     f4 xv[kTileBatches], wv[NW];
 #pragma unroll
@@ -878,7 +900,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             const int pr = P0 + ih;
             const int n = box_div(pr, t.Hp_inv), h = pr - n * t.Hp - t.pad_eff, w = w0 * g.stride + iw - t.pad_eff;
             const bool ok = ih < t.IH && n < g.Nb && h >= 0 && h < g.Hs && w >= 0 && w < g.Ws;
-            xv[u] = buf_load4(xr, ok ? (unsigned)((n * g.Hs + h) * g.Ws + w) * 16u : kNoLoad, 0);
+            xv[u] = buf_load4(xr, ok ? (unsigned)(((n - n1) * g.Hs + h) * g.Ws + w) * 16u : kNoLoad, 0);
         }
 #pragma unroll
     for (int u = 0; u < NW; ++u) {
@@ -937,9 +959,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
 struct StemCfg { int tn, tiles; BoxGeom t; size_t lds; };
 static bool pick_stem(const ConvGeom& g, StemCfg& c) {
     if (g.Cs != 4 || g.Ncols % 4 || g.R != g.S || (g.R != 3 && g.R != 7)) return false;
-    if (!buf_fits((double)g.Nb * g.Hs * g.Ws * 4)) return false;
     // (box_pick counts batches of 64 pixels with a quad group each; here a batch is 256 pixels)
-    if (!box_pick(c.t, g.Nb, g.Ho, g.Wo, g.R, g.stride, g.pad, 128, 1, 4 * kTileBatches)) return false;
+    if (!box_pick(c.t, g.Nb, g.Ho, g.Wo, g.R, g.stride, g.pad, 128, 1, 4 * kTileBatches) ||
+        !box_fits(c.t, g.Nb, (double)g.Hs * g.Ws * 4))
+        return false;
     c.tn = g.Ncols > 16 ? 2 : 1;
     c.tiles = box_tiles(c.t);
     c.lds = sizeof(float) * std::max<size_t>((size_t)c.tn * 16 * g.R * ((g.R + 3) / 4) * 20 +
@@ -998,7 +1021,9 @@ __global__ __launch_bounds__(256) void conv_dgrad_s2_f32(const float* __restrict
     float* Xs = lds;                              // [IH * IW][LDW] dY rows
     float* Ws = lds + t.IH * t.IW * LDW;          // [16][RS][LDW]
 
-    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(dY, (long)g.Nb * g.Hs * g.Ws * g.Cs);
+    const int n1 = t.far ? box_div(P0, t.Hp_inv) : 0;   // the descriptor's first image
+    const long image = (long)g.Hs * g.Ws * g.Cs;
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(dY, n1, image, g.Nb);
     const __amdgpu_buffer_rsrc_t wr = buf_rsrc(B, (long)g.Ncols * RS * g.Cs);
     unsigned xo[kTileBatches], wo[NW];
 #pragma unroll
@@ -1010,7 +1035,7 @@ __global__ __launch_bounds__(256) void conv_dgrad_s2_f32(const float* __restrict
             const int pr = P0 + ih;
             const int n = box_div(pr, t.Hp_inv), h = pr - n * t.Hp, w = w0 + iw;
             if (ih < t.IH && n < g.Nb && h < g.Hs && w < g.Ws)
-                xo[u] = (unsigned)(((n * g.Hs + h) * g.Ws + w) * g.Cs + q * 4) * 4u;
+                xo[u] = (unsigned)((((n - n1) * g.Hs + h) * g.Ws + w) * g.Cs + q * 4) * 4u;
         }
     }
 #pragma unroll
@@ -1109,12 +1134,14 @@ struct S2Cfg { int tm, tiles; BoxGeom t; size_t lds; };
 static bool pick_s2(const ConvGeom& g, S2Cfg& out) {
     if (g.stride != 2 || g.Cs % 4 || g.Ncols % 4) return false;
     if (!((g.R == 3 && g.S == 3 && g.pad == 1) || (g.R == 1 && g.S == 1 && g.pad == 0))) return false;
-    if (!buf_fits((double)g.Nb * g.Hs * g.Ws * g.Cs) || !buf_fits((double)g.Ncols * g.R * g.R * g.Cs)) return false;
+    if (!buf_fits((double)g.Ncols * g.R * g.R * g.Cs)) return false;
     const int ext = g.R == 3 ? 2 : 1;   // dY rows i, i + 1 (3x3) or i
     bool found = false;
     for (int tm : {2, 1}) {
         S2Cfg c;
-        if (!box_pick(c.t, g.Nb, (g.Ho + 1) / 2, (g.Wo + 1) / 2, ext, 1, 0, tm * 64, 1, kTileBatches)) continue;
+        if (!box_pick(c.t, g.Nb, (g.Ho + 1) / 2, (g.Wo + 1) / 2, ext, 1, 0, tm * 64, 1, kTileBatches) ||
+            !box_fits(c.t, g.Nb, (double)g.Hs * g.Ws * g.Cs))
+            continue;
         c.tm = tm;
         c.tiles = box_tiles(c.t);
         c.lds = sizeof(float) * std::max<size_t>(20 * ((size_t)c.t.IH * c.t.IW + (size_t)16 * g.R * g.R),
@@ -1414,7 +1441,7 @@ constexpr int kWgBatches = 6;   // staged input quads per thread and box, at mos
 // chain, 51.6 with 16, 49.8 with 64; 87 x 38x38x44 65.8 and, with 64, 69.6.
 static int wg_run(int ng, int Wo) { return std::max(1, ((Wo & (Wo - 1)) == 0 ? 16 : 64) / (4 * ng)); }
 
-template <int RS, int NG, int ST, bool FULL>
+template <int RS, int NG, int ST, bool FULL, bool FAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8)))
 void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__ X, float* __restrict__ part, WgArgs a,
                          BoxGeom t, int tiles, int per, int run, const float* __restrict__ in_ss) {
@@ -1429,8 +1456,7 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
     const int npix = t.IH * t.IW, nx = npix * 4, nxu = (nx + 255) >> 8;
     float* Xs = lds;                         // [npix][LDW] input rows of the box
     float* Ds = lds + npix * LDW;            // [TP][LDW] dY of the box, 16 channels
-    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(X, (long)a.Nb * a.Hi * a.Wi * a.Cin_p);
-    const __amdgpu_buffer_rsrc_t dr = buf_rsrc(dY, (long)a.Nb * a.Ho * a.Wo * a.Cout);
+    const long image = (long)a.Hi * a.Wi * a.Cin_p, row = (long)a.Wo * a.Cout;
 
     // the fold's scale and shift of this thread's channel quad
     f4 fsc{}, fsh{};
@@ -1444,6 +1470,8 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
         const int tr = box_div(tile, t.nc_inv), tc = tile - tr * t.nc;
         const int R0 = tr * t.OH, w0 = tc * t.OW, P0 = box_prow(t, R0);
         const int ohv = min(t.OH, t.rows - R0), owv = min(t.OW, t.Wo - w0);
+        const int n1 = FAR ? box_div(P0, t.Hp_inv) : 0, R1 = FAR ? R0 : 0;   // the descriptors' first image and row
+        const __amdgpu_buffer_rsrc_t xr = buf_rsrc(X, n1, image, a.Nb), dr = buf_rsrc(dY, R1, row, t.rows);
         valid = 0;
 #pragma unroll
         for (int u = 0; u < kWgBatches; ++u)
@@ -1456,7 +1484,7 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
                 const int w = (K1 ? (w0 + iw) * ST : w0 * ST + iw) - t.pad_eff;
                 unsigned off = kNoLoad;
                 if (ih < t.IH && n < a.Nb && h >= 0 && h < a.Hi && w >= 0 && w < a.Wi && c0 + q * 4 < a.Cin_p) {
-                    off = (unsigned)(((n * a.Hi + h) * a.Wi + w) * a.Cin_p + c0 + q * 4) * 4u;
+                    off = (unsigned)((((n - n1) * a.Hi + h) * a.Wi + w) * a.Cin_p + c0 + q * 4) * 4u;
                     valid |= 1u << u;
                 }
                 xv[u] = buf_load4(xr, off, 0);
@@ -1466,7 +1494,7 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
             const int p = (tid + u * 256) >> 2;
             const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
             const bool ok = oh < ohv && ow < owv && co0 + q * 4 < a.Cout;
-            dv[u] = buf_load4(dr, ok ? (unsigned)(((R0 + oh) * t.Wo + w0 + ow) * a.Cout + co0 + q * 4) * 4u : kNoLoad,
+            dv[u] = buf_load4(dr, ok ? (unsigned)(((R0 - R1 + oh) * t.Wo + w0 + ow) * a.Cout + co0 + q * 4) * 4u : kNoLoad,
                               0);
         }
     };
@@ -1499,34 +1527,44 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
         const int e = k * 256 + tid;
         return ((red[e] + red[RS * 256 + e]) + red[2 * RS * 256 + e]) + red[3 * RS * 256 + e];
     };
-    // runs of `run` boxes leave their sums in fp64, entry tid of every tap in thread tid
-    double tot[RS];
+    // runs of `run` boxes leave their sums in fp64: entry tid of every tap in
+    // thread tid, or (1x1) each lane its own four
+    double tot[K1 ? 4 : RS];
     const bool chained = NG < 4 && t1 - t0 > run;
     auto leave = [&]() {
-        waves();
+        if constexpr (K1) {
 #pragma unroll
-        for (int k = 0; k < RS; ++k) {
-            tot[k] += (double)wave_sum(k);
-            acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < 4; ++i) tot[i] += (double)acc[0][i];
+            acc[0] = f4{0.f, 0.f, 0.f, 0.f};
+        } else {
+            waves();
+#pragma unroll
+            for (int k = 0; k < RS; ++k) {
+                tot[k] += (double)wave_sum(k);
+                acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+            }
+            lds_barrier();
         }
-        lds_barrier();
     };
     auto finish = [&]() {
+        if (K1 && chained) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[0][i] = (float)(tot[i] + (double)acc[0][i]);
+        }
         waves();
         float* out = part + (long)blockIdx.x * a.Cout * Ktot;
         const int co = co0 + (tid >> 4), c = c0 + (tid & 15);
 #pragma unroll
         for (int k = 0; k < RS; ++k) {
             float v = wave_sum(k);
-            if (chained) v = (float)(tot[k] + (double)v);
+            if (!K1 && chained) v = (float)(tot[k] + (double)v);
             if (co < a.Cout && c < a.Cin_p) out[(long)co * Ktot + k * a.Cin_p + c] = v;
         }
     };
 #pragma unroll
-    for (int k = 0; k < RS; ++k) {
-        acc[k] = f4{0.f, 0.f, 0.f, 0.f};
-        tot[k] = 0.0;
-    }
+    for (int k = 0; k < RS; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (double& v : tot) v = 0.0;
     load(t0);
     for (int tile = t0; tile < t1; ++tile) {
         if (in_ss) {
@@ -1598,10 +1636,9 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
     __syncthreads();
     // the same sums in the same order, zeros for both operands at slots without a pixel
 #pragma unroll
-    for (int k = 0; k < RS; ++k) {
-        acc[k] = f4{0.f, 0.f, 0.f, 0.f};
-        tot[k] = 0.0;
-    }
+    for (int k = 0; k < RS; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (double& v : tot) v = 0.0;
 #pragma unroll 1
     for (int tile = t0; tile < t1; ++tile) {
         load(tile);
@@ -1669,7 +1706,6 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
                             int pad, WgTileCfg& out) {
     if (Cin_p % 4 || Cout % 4 || R != S || (R != 1 && R != 3) || (stride != 1 && stride != 2)) return false;
     if (Cin_p < 16 && Cout > 32) return false;   // mostly empty MFMA columns: the GEMM kernel is as fast
-    if (!buf_fits((double)Nb * Hi * Wi * Cin_p) || !buf_fits((double)Nb * Ho * Wo * Cout)) return false;
     const long blocks = (long)((Cout + 15) / 16) * ((Cin_p + 15) / 16);
     const double M = (double)Nb * Ho * Wo;
     if (R == 1 ? Cin_p > 16 && M * Cin_p * Cout >= (M >= 32768 ? 268435456.0 : 3e8) : stride == 2 && blocks >= 128)
@@ -1678,7 +1714,10 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
     bool found = false;
     for (int ng : {4, 2, 1}) {
         WgTileCfg c;
-        if (!box_pick(c.t, Nb, Ho, Wo, R, R == 1 ? 1 : stride, pad, ng * 64, 4, kWgBatches)) continue;
+        if (!box_pick(c.t, Nb, Ho, Wo, R, R == 1 ? 1 : stride, pad, ng * 64, 4, kWgBatches) ||
+            !box_fits(c.t, Nb, (double)Hi * Wi * Cin_p) || !buf_fits((double)c.t.OH * Wo * Cout))
+            continue;
+        c.t.far |= !buf_fits((double)Nb * Ho * Wo * Cout);
         c.ng = ng;
         c.lds = sizeof(float) *
                 std::max<size_t>(((size_t)c.t.IH * c.t.IW + ng * 64) * 20, (size_t)4 * R * S * 256 + 4);
@@ -1702,7 +1741,7 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
 // consecutive floats from the pixel of the first tap.  Columns past the filter
 // row are formed and dropped.  (128 x 32x32, 4 -> 16: 10.3 us with a column
 // tile per tap, 7.4 here; 4 -> 96: 36, 19; 7x7/2, 4 -> 64: 97, 82.)
-template <int KS, int NG, int ST, bool FULL>
+template <int KS, int NG, int ST, bool FULL, bool FAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 3 && (FULL || NG == 2) ? 4 : 3, 8)))
 void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__ X,
                                                            float* __restrict__ part, WgArgs a, BoxGeom t, int tiles,
@@ -1715,13 +1754,14 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
     const int npix = t.IH * t.IW;
     float* Ds = lds;                          // [TP][LDW] dY of the box, 16 channels
     float* Xs = lds + TP * LDW;               // [npix][4] input, 16 floats of slack behind
-    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(X, (long)a.Nb * a.Hi * a.Wi * 4);
-    const __amdgpu_buffer_rsrc_t dr = buf_rsrc(dY, (long)a.Nb * a.Ho * a.Wo * a.Cout);
+    const long image = (long)a.Hi * a.Wi * 4, row = (long)a.Wo * a.Cout;
     f4 xv[kTileBatches], dv[NG];
     auto load = [&](int tile) {
         const int tr = box_div(tile, t.nc_inv), tc = tile - tr * t.nc;
         const int R0 = tr * t.OH, w0 = tc * t.OW, P0 = box_prow(t, R0);
         const int ohv = min(t.OH, t.rows - R0), owv = min(t.OW, t.Wo - w0);
+        const int n1 = FAR ? box_div(P0, t.Hp_inv) : 0, R1 = FAR ? R0 : 0;   // the descriptors' first image and row
+        const __amdgpu_buffer_rsrc_t xr = buf_rsrc(X, n1, image, a.Nb), dr = buf_rsrc(dY, R1, row, t.rows);
 #pragma unroll
         for (int u = 0; u < kTileBatches; ++u)
             if (u * 256 < npix) {
@@ -1730,14 +1770,14 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
                 const int pr = P0 + ih;
                 const int n = box_div(pr, t.Hp_inv), h = pr - n * t.Hp - t.pad_eff, w = w0 * ST + iw - t.pad_eff;
                 const bool ok = ih < t.IH && n < a.Nb && h >= 0 && h < a.Hi && w >= 0 && w < a.Wi;
-                xv[u] = buf_load4(xr, ok ? (unsigned)((n * a.Hi + h) * a.Wi + w) * 16u : kNoLoad, 0);
+                xv[u] = buf_load4(xr, ok ? (unsigned)(((n - n1) * a.Hi + h) * a.Wi + w) * 16u : kNoLoad, 0);
             }
 #pragma unroll
         for (int u = 0; u < NG; ++u) {
             const int p = (tid + u * 256) >> 2;
             const int oh = box_div(p, t.OWs_inv), ow = p - oh * t.OWs;
             const bool ok = oh < ohv && ow < owv && co0 + q * 4 < a.Cout;
-            dv[u] = buf_load4(dr, ok ? (unsigned)(((R0 + oh) * t.Wo + w0 + ow) * a.Cout + co0 + q * 4) * 4u : kNoLoad,
+            dv[u] = buf_load4(dr, ok ? (unsigned)(((R0 - R1 + oh) * t.Wo + w0 + ow) * a.Cout + co0 + q * 4) * 4u : kNoLoad,
                               0);
         }
     };
@@ -1875,12 +1915,14 @@ void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__
 static bool pick_wgrad_stem(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride,
                             int pad, WgTileCfg& out) {
     if (Cin_p != 4 || Cout % 4 || R != S || (R != 3 && R != 7) || (stride != 1 && stride != 2)) return false;
-    if (!buf_fits((double)Nb * Hi * Wi * 4) || !buf_fits((double)Nb * Ho * Wo * Cout)) return false;
     const long blocks = (Cout + 15) / 16;
     bool found = false;
     for (int ng : {4, 2}) {
         WgTileCfg c;
-        if (!box_pick(c.t, Nb, Ho, Wo, R, stride, pad, ng * 64, 4, 4 * kTileBatches)) continue;
+        if (!box_pick(c.t, Nb, Ho, Wo, R, stride, pad, ng * 64, 4, 4 * kTileBatches) ||
+            !box_fits(c.t, Nb, (double)Hi * Wi * 4) || !buf_fits((double)c.t.OH * Wo * Cout))
+            continue;
+        c.t.far |= !buf_fits((double)Nb * Ho * Wo * Cout);
         c.ng = ng;
         // a column tile reads up to 16 floats past its first tap's pixel
         c.lds = sizeof(float) * std::max<size_t>((size_t)ng * 64 * 20 + ((size_t)c.t.IH * c.t.IW + 4) * 4,
@@ -1897,28 +1939,28 @@ static bool pick_wgrad_stem(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
     return found;
 }
 
-template <int KS, int ST, bool FULL>
+template <int KS, int ST, bool FULL, bool FAR>
 static hipError_t launch_wg_stem(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
                                  hipStream_t st) {
     dim3 grid((unsigned)c.splits, (unsigned)((a.Cout + 15) / 16));
     if (c.ng == 4)
-        launch((conv_wgrad_stem_f32<KS, 4, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+        launch((conv_wgrad_stem_f32<KS, 4, ST, FULL, FAR>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
                c.run);
     else
-        launch((conv_wgrad_stem_f32<KS, 2, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+        launch((conv_wgrad_stem_f32<KS, 2, ST, FULL, FAR>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
                c.run);
     return hipGetLastError();
 }
 
-template <bool FULL>
+template <bool FULL, bool FAR>
 static hipError_t dispatch_wg_stem(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
                                    hipStream_t st) {
     if (a.R == 3) {
-        if (a.stride == 1) return launch_wg_stem<3, 1, FULL>(dY, X, part, a, c, st);
-        return launch_wg_stem<3, 2, FULL>(dY, X, part, a, c, st);
+        if (a.stride == 1) return launch_wg_stem<3, 1, FULL, FAR>(dY, X, part, a, c, st);
+        return launch_wg_stem<3, 2, FULL, FAR>(dY, X, part, a, c, st);
     }
-    if (a.stride == 1) return launch_wg_stem<7, 1, FULL>(dY, X, part, a, c, st);
-    return launch_wg_stem<7, 2, FULL>(dY, X, part, a, c, st);
+    if (a.stride == 1) return launch_wg_stem<7, 1, FULL, FAR>(dY, X, part, a, c, st);
+    return launch_wg_stem<7, 2, FULL, FAR>(dY, X, part, a, c, st);
 }
 
 WgradPlan wgrad_plan(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride, int pad) {
@@ -1963,31 +2005,31 @@ static hipError_t launch_wg(const float* dY, const float* X, float* part, const 
     return hipGetLastError();
 }
 
-template <int RS, int ST, bool FULL>
+template <int RS, int ST, bool FULL, bool FAR>
 static hipError_t launch_wg_tile(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
                                  const float* in_ss, hipStream_t st) {
     dim3 grid((unsigned)c.splits, (unsigned)((a.Cout + 15) / 16), (unsigned)((a.Cin_p + 15) / 16));
     if (c.ng == 4)
-        launch((conv_wgrad_tile_f32<RS, 4, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+        launch((conv_wgrad_tile_f32<RS, 4, ST, FULL, FAR>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
                c.run, in_ss);
     else if (c.ng == 2)
-        launch((conv_wgrad_tile_f32<RS, 2, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+        launch((conv_wgrad_tile_f32<RS, 2, ST, FULL, FAR>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
                c.run, in_ss);
     else
-        launch((conv_wgrad_tile_f32<RS, 1, ST, FULL>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
+        launch((conv_wgrad_tile_f32<RS, 1, ST, FULL, FAR>), grid, dim3(256), c.lds, st, dY, X, part, a, c.t, c.tiles, c.per,
                c.run, in_ss);
     return hipGetLastError();
 }
 
-template <bool FULL>
+template <bool FULL, bool FAR>
 static hipError_t dispatch_wg_tile(const float* dY, const float* X, float* part, const WgArgs& a, const WgTileCfg& c,
                                    const float* in_ss, hipStream_t st) {
     if (a.R == 1) {
-        if (a.stride == 1) return launch_wg_tile<1, 1, FULL>(dY, X, part, a, c, in_ss, st);
-        return launch_wg_tile<1, 2, FULL>(dY, X, part, a, c, in_ss, st);
+        if (a.stride == 1) return launch_wg_tile<1, 1, FULL, FAR>(dY, X, part, a, c, in_ss, st);
+        return launch_wg_tile<1, 2, FULL, FAR>(dY, X, part, a, c, in_ss, st);
     }
-    if (a.stride == 1) return launch_wg_tile<9, 1, FULL>(dY, X, part, a, c, in_ss, st);
-    return launch_wg_tile<9, 2, FULL>(dY, X, part, a, c, in_ss, st);
+    if (a.stride == 1) return launch_wg_tile<9, 1, FULL, FAR>(dY, X, part, a, c, in_ss, st);
+    return launch_wg_tile<9, 2, FULL, FAR>(dY, X, part, a, c, in_ss, st);
 }
 
 hipError_t launch_conv_wgrad(const float* dY, const float* X, float* part, int Nb, int Hi, int Wi, int Cin_p,
@@ -1999,15 +2041,17 @@ hipError_t launch_conv_wgrad(const float* dY, const float* X, float* part, int N
         WgTileCfg c;
         if (!pick_wgrad_stem(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c) || c.splits != p.splits)
             return hipErrorInvalidValue;
-        return box_full(c.t, c.ng * 64) ? dispatch_wg_stem<true>(dY, X, part, a, c, st)
-                                        : dispatch_wg_stem<false>(dY, X, part, a, c, st);
+        if (c.t.far) return dispatch_wg_stem<false, true>(dY, X, part, a, c, st);
+        return box_full(c.t, c.ng * 64) ? dispatch_wg_stem<true, false>(dY, X, part, a, c, st)
+                                        : dispatch_wg_stem<false, false>(dY, X, part, a, c, st);
     }
     if (p.tile) {
         WgTileCfg c;
         if (!pick_wgrad_tile(Nb, Hi, Wi, Cin_p, Ho, Wo, Cout, R, S, stride, pad, c) || c.splits != p.splits)
             return hipErrorInvalidValue;
-        return box_full(c.t, c.ng * 64) ? dispatch_wg_tile<true>(dY, X, part, a, c, in_ss, st)
-                                        : dispatch_wg_tile<false>(dY, X, part, a, c, in_ss, st);
+        if (c.t.far) return dispatch_wg_tile<false, true>(dY, X, part, a, c, in_ss, st);
+        return box_full(c.t, c.ng * 64) ? dispatch_wg_tile<true, false>(dY, X, part, a, c, in_ss, st)
+                                        : dispatch_wg_tile<false, false>(dY, X, part, a, c, in_ss, st);
     }
     if (p.tm == 1) return launch_wg<1, 4>(dY, X, part, a, p, st);
     if (p.tm == 2) return launch_wg<2, 4>(dY, X, part, a, p, st);

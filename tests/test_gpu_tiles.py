@@ -262,7 +262,8 @@ def test_weight_gradient_keeps_an_infinity_in_its_place(case):
 
 
 # cin, cout, k, hw, batch: many boxes to a workgroup
-@pytest.mark.parametrize("case", [(128, 128, 3, 32, 64), (64, 64, 3, 28, 100), (4, 64, 3, 64, 64), (4, 64, 3, 50, 90)],
+@pytest.mark.parametrize("case", [(128, 128, 3, 32, 64), (64, 64, 3, 28, 100), (4, 64, 3, 64, 64), (4, 64, 3, 50, 90),
+                                  (64, 64, 1, 32, 60), (64, 64, 1, 28, 80)],
                          ids=lambda c: "x".join(map(str, c)))
 def test_weight_gradient_error_does_not_grow_with_the_tensor(case):
     """Against 64-bit sums over the pass's own operands.  n additions of
@@ -294,3 +295,35 @@ def test_weight_gradient_error_does_not_grow_with_the_tensor(case):
     bound = 1.25 * u * np.sqrt(chain / 6 + np.mean(ref ** 2 / sq))
     print(case, "error %.3e, bound %.3e" % (err, bound), file=sys.stderr, flush=True)
     assert err < bound
+
+
+def _repeated_batch(o, p, small, times, dtype=lpp.FP32):
+    """Logits and gradient of a batch without batch norm, and of the same
+    images `times` times over, whose activations are larger than a buffer
+    descriptor reaches."""
+    g = torch.Generator("cuda").manual_seed(3)
+    img = torch.randn((small,) + o.in_shape, generator=g, device="cuda")
+    lab = torch.randint(o.n_classes, (small,), generator=g, device="cuda", dtype=torch.int32)
+    out = []
+    for k in (1, times):
+        with lpp.Context(p, K=1, batch=small * k, dtype=dtype) as ctx:
+            ctx.set_params(T.init_x(o.specs, 5).astype(np.float32))
+            i, t = img.repeat(k, 1, 1, 1), lab.repeat(k)
+            torch.cuda.synchronize()
+            ctx.step(0, i, t, 0, 0.0)
+            out.append((ctx.get_logits(0), ctx.get_grad(0)))
+        del i, t
+        torch.cuda.empty_cache()
+    return out
+
+
+# over 2 GiB: a stem's output and a 3x3 conv's operands; a stride-2 conv's operands
+@pytest.mark.parametrize("net,times", [
+    (T.twin_conv_net(4, 16, 3, 1, 1, 16, 64), 1125),
+    (T.twin_conv2_net(4, 16, 32, 3, 2, 1, 96), 1000),
+], ids=["stride1", "stride2"])
+def test_tensors_over_2_gib(net, times):
+    (logits, grad), (many, mean) = _repeated_batch(*net, 8, times)
+    assert np.array_equal(many, np.tile(logits, (times, 1)))
+    err = np.linalg.norm(mean.astype(np.float64) - grad) / np.linalg.norm(grad)
+    assert err < 1e-5, err
