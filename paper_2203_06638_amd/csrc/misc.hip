@@ -716,16 +716,14 @@ __global__ void copy_acc_k(const T* __restrict__ s, T* __restrict__ d, long n4, 
         st4(d, i, acc ? ld4(d, i) + ld4(s, i) : ld4(s, i));
 }
 
-// The gradient at a ReLU's output masked in place into the gradient at its
-// input (where the stored output y is zero: the ReLU clipped), and per row
-// tile of stats_rows(M, C) rows the mean over the tile of each masked
-// column, pmean[tile][c] -- a conv bias gradient's partials, summed by
-// sum_from_tiles.  Tiling as stats_partial_k.
-// Row tiles of the masking passes: about 512 of them, of at least 16 rows
+// Row tiles of the masking passes: about 512 of them, of 16 to 512 rows.  A
+// tile's column sums are formed in fp32, the tiles' in fp64: the limit keeps
+// the error from growing with the tensor (802816 rows x 64 in 512 tiles: five
+// times that of tiles of 512 rows).
 int mask_rows(long M, int C) {
     const long gy = ((C >> 2) + 255) / 256;
     long r = (M * gy + 511) / 512;
-    return (int)(r < 16 ? 16 : r);
+    return (int)(r < 16 ? 16 : (r > 512 ? 512 : r));
 }
 int mask_tiles(long M, int C) {
     const int R = mask_rows(M, C);
@@ -759,6 +757,11 @@ __device__ __forceinline__ f4 mask_rows4(const T* g, long gs, const T* y, long y
     return s;
 }
 
+// The gradient at a ReLU's output masked in place into the gradient at its
+// input (where the stored output y is zero: the ReLU clipped), and per row
+// tile of mask_rows(M, C) rows the mean over the tile of each masked column,
+// pmean[tile][c] -- a conv bias gradient's partials, summed by
+// sum_from_tiles_k.
 template <class T>
 __global__ __launch_bounds__(256) void relu_mask_colsum_k(T* dy, const T* __restrict__ y, long M, int C,
                                                           int R, float* __restrict__ pmean) {

@@ -163,3 +163,15 @@ def test_describe_accepts_ragged_shapes():
     m = PM.resnet_imagenet((1, 1), (8, 16), n_classes=5, hw=23, blocks=[1, 1, 2, 2])
     info = lpp.describe(m, 3)
     assert info.d == m.d and info.P == 2
+
+
+def test_masking_tiles_stay_short():
+    """A row tile of the masking passes, whose column sums are formed in fp32,
+    has at most 512 rows however large the tensor; the tiles cover it."""
+    rows, tiles = lpp.lib()._ZN3lpp9mask_rowsEli, lpp.lib()._ZN3lpp10mask_tilesEli
+    for f in (rows, tiles):
+        f.argtypes, f.restype = [lpp.C.c_long, lpp.C.c_int], lpp.C.c_int
+    for m in (1, 15, 16, 8191, 32768, 262144, 262145, 802816, 1577088, 2 ** 31 - 1):
+        for c in (4, 64, 96, 1024, 2048, 4100):
+            assert 16 <= rows(m, c) <= 512
+            assert (tiles(m, c) - 1) * rows(m, c) < m <= tiles(m, c) * rows(m, c)
