@@ -742,6 +742,9 @@ constexpr int kFetchThreads = 4;
 constexpr size_t kFetchPool = 8 << 20;        // bytes, two slots to a thread
 constexpr size_t kFetchMin = 64 << 10;        // smaller copies: hipMemcpy (15 us)
 constexpr size_t kFetchPerThread = 4 << 20;   // bytes that pay for one more thread
+// bytes of a slot with T threads: whole pages, so that every transfer starts on one
+constexpr size_t fetch_slot(int T) { return kFetchPool / (2 * T) & ~size_t(4095); }
+static_assert(fetch_slot(2) % 4096 == 0 && fetch_slot(3) % 4096 == 0 && fetch_slot(kFetchThreads) % 4096 == 0, "");
 struct FetchPool {
     std::mutex use;                           // held while a copy runs
     char* slots = nullptr;
@@ -794,7 +797,7 @@ hipError_t fetch_part(FetchPool& f, int t, int T, hipStream_t st, char* host, co
     lo = std::max(lo, b0);
     hi = std::max(lo, std::min(hi, b1));
     if (lo >= b1) lo = hi = b1;               // nothing of the range here
-    const size_t slot = kFetchPool / (2 * T), n = hi - lo;
+    const size_t slot = fetch_slot(T), n = hi - lo;
     const size_t size = std::min(slot, std::max<size_t>(256 << 10, ((n + 1) / 2 + 4095) & ~size_t(4095)));
     const size_t chunks = (n + size - 1) / size;
     auto len = [&](size_t k) { return std::min(size, n - k * size); };

@@ -150,22 +150,25 @@ def test_maxpool_gradient_blocks(hw):
     pytest.fail("every seed has a tie")
 
 
-def _wide(n_classes=10):
+def _wide(c, n_classes=10):
     m = PM.Model("wide", (3, 4, 4), n_classes)
-    x = m.conv(-1, 256, 3)
+    x = m.conv(-1, c, 3)
     m.new_unit()
-    x = m.conv(x, 512, 3)
+    x = m.conv(x, 2 * c, 3)
     m.new_unit()
-    m.linear(m.gap(m.conv(x, 512, 3)), n_classes)
+    m.linear(m.gap(m.conv(x, 2 * c, 3)), n_classes)
     return m.assign_blocks([1, 2, 3])
 
 
-def test_large_copies_to_the_host():
-    """14 MB of parameters (several threads and slots a copy): every entry
-    arrives, a block's gradient is the full one's and zero elsewhere, and
+@pytest.mark.parametrize("c", [160, 220, 256], ids=["5MB", "10MB", "14MB"])
+def test_large_copies_to_the_host(c):
+    """Parameters of 5, 10 and 14 MB (two, three and four threads, several
+    slots a copy): every entry arrives, a block's gradient is the full one's
+    and zero elsewhere (the last block's begins inside a thread's part), and
     copies of two contexts from two threads at once (one of them finds the
     pinned slots in use) agree."""
-    m = _wide()
+    m = _wide(c)
+    assert (m.d * 4 >> 22) == {160: 1, 220: 2, 256: 3}[c]
     rng = np.random.default_rng(3)
     xs = [(rng.standard_normal(m.d) * 0.05).astype(np.float32) for _ in range(2)]
     img, lab = synth.images(4, 2, 3, 4, 4), synth.labels(4, 2, 10)
@@ -181,7 +184,7 @@ def test_large_copies_to_the_host():
         for part in (1, 2, 3):
             a.step(0, i, t, part, 0.0)
             got, (lo, hi) = a.get_grad(0), a.block_range(part)
-            assert np.array_equal(got[lo:hi], full[lo:hi])
+            assert hi > lo and np.array_equal(got[lo:hi], full[lo:hi])
             assert not np.any(got[:lo]) and not np.any(got[hi:])
         bad = []
 
