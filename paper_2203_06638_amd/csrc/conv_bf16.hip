@@ -499,6 +499,9 @@ static hipError_t launch_bf16_pass(const bf16* src, const bf16* B, const float* 
     if (Mmax == 0) return hipSuccess;
     dim3 grid((unsigned)((Mmax + BM - 1) / BM), (unsigned)((g.Ncols + BN - 1) / BN), (unsigned)np);
     const BnSums sm = stats ? *stats : BnSums{};
+    // the loads into LDS go through buffer descriptors: what lies past one
+    // reads as zero, so larger operands are staged through registers
+    const bool fit = bf_bytes_fit((double)g.Nb * g.Hs * g.Ws * g.Cs) && bf_bytes_fit((double)g.Ncols * g.R * g.S * g.Cs);
     // 32-channel load steps straight into LDS, NS of them in flight; tiles of
     // up to 128 x 128 take two load steps per buffer and barrier where the
     // source's channels allow: a load step reads half of a pixel's 128-byte
@@ -509,14 +512,14 @@ static hipError_t launch_bf16_pass(const bf16* src, const bf16* B, const float* 
     // gradient; three take 96 KB, one workgroup, and 74; 256 x 128 with two
     // likewise, 57 -> 73)
     if constexpr (BM <= 128 && BN == 128) {
-        if (g.Cs % 64 == 0) {
+        if (fit && g.Cs % 64 == 0) {
             constexpr int NS2 = BM == 64 ? 3 : 2;
             if (stats) launch((conv_bf16_k<BM, BN, true, true, 2, true, NS2>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
             else launch((conv_bf16_k<BM, BN, false, true, 2, true, NS2>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
             return hipGetLastError();
         }
     }
-    if (g.Cs % 32 == 0) {
+    if (fit && g.Cs % 32 == 0) {
         constexpr int NSD = BM == 256 ? 3 : 4;
         if (stats) launch((conv_bf16_k<BM, BN, true, true, 1, true, NSD>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
         else launch((conv_bf16_k<BM, BN, false, true, 1, true, NSD>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
@@ -526,8 +529,7 @@ static hipError_t launch_bf16_pass(const bf16* src, const bf16* B, const float* 
         // larger grids, where other workgroups cover it, the taps that each
         // thread then keeps for itself cost 1-3% (24 x 36x36x168, 32 x
         // 28x28x200, and 128-row tiles)
-    } else if (BM == 64 && (long)grid.x * grid.y * np <= 512 && bf_bytes_fit((double)g.Nb * g.Hs * g.Ws * g.Cs) &&
-               bf_bytes_fit((double)g.Ncols * g.R * g.S * g.Cs)) {
+    } else if (fit && BM == 64 && (long)grid.x * grid.y * np <= 512) {
         if constexpr (BM == 64) {
             if (stats) launch((conv_bf16_k<BM, BN, true, false, 1, true, 4>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);
             else launch((conv_bf16_k<BM, BN, false, false, 1, true, 4>), grid, dim3(256), 0, st, src, B, bias, Y, res, g, ps, (int)acc, sm);

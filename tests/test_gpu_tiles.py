@@ -330,3 +330,14 @@ def test_tensors_over_2_gib(net, times):
     assert np.array_equal(many, np.tile(logits, (times, 1)))
     err = np.linalg.norm(mean.astype(np.float64) - grad) / np.linalg.norm(grad)
     assert err < 1e-5, err
+
+
+def test_bf16_tensors_over_2_gib():
+    """The load pipeline of sources of 32k channels reads through a buffer
+    descriptor, which yields zeros past 2 GiB: such a source takes the path
+    through registers."""
+    (logits, grad), (many, mean) = _repeated_batch(*T.twin_conv_net(8, 64, 3, 1, 1, 64, 64), 8, 520, dtype=lpp.BF16)
+    # (one rounding of a stored value may fall the other way: 2^-8 of it, one of 4096 that the pool averages)
+    assert np.max(np.abs(many - np.tile(logits, (520, 1)))) < 1e-5 * np.max(np.abs(logits))
+    err = np.linalg.norm(mean.astype(np.float64) - grad) / np.linalg.norm(grad)
+    assert err < 2e-2, err
