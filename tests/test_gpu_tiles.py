@@ -341,3 +341,64 @@ def test_bf16_tensors_over_2_gib():
     assert np.max(np.abs(many - np.tile(logits, (520, 1)))) < 1e-5 * np.max(np.abs(logits))
     err = np.linalg.norm(mean.astype(np.float64) - grad) / np.linalg.norm(grad)
     assert err < 2e-2, err
+
+
+@pytest.mark.parametrize("hw", [13, 14])
+def test_maxpool_gradient_added_to_another(hw):
+    """A map that a max pool 3x3/2 and, later, a stride-2 conv read: the
+    pool's gradient is added to the conv's.  Argmax decisions on identical
+    values (exact grid)."""
+    o = OM.Net("poolnet", 3, hw, hw, 6)
+    x = o.conv(-1, 3, 16, 3, 1, 1)
+    a = o.maxpool(x, 3, 2, 1)
+    a = o.gap(o.add(a, o.conv(x, 16, 16, 3, 2, 1)))
+    o.next_unit()
+    o.linear(a, 16, 6)
+    o.set_blocks([1, 2])
+    p = PM.Model("poolnet", (3, hw, hw), 6)
+    y = p.conv(-1, 16, 3)
+    z = p.maxpool(y, 3, 2, 1)
+    z = p.gap(p.add(z, p.conv(y, 16, 3, 2)))
+    p.new_unit()
+    p.linear(z, 6)
+    p.assign_blocks([1, 2])
+    for seed in range(60, 90):      # a seed without tied maxima
+        x, img, _ = grid_inputs(o, seed, 3)
+        if R.kink_margin(o, x, img) > 0:
+            return check_step(o, p, 3, seed=seed)
+    pytest.fail("every seed has a tie")
+
+
+@pytest.mark.parametrize("mode", [lpp.SEQUENTIAL, lpp.ASYNC], ids=["sequential", "async"])
+def test_bf16_relu_decision_recomputed(mode):
+    """The BN backward's sums decide the ReLU from the BN input, rounded to
+    bf16 as the stored output: the same decision for every entry, also where
+    outputs lie about half of the smallest bf16 number (scales of 1e-40) and
+    round to zero, and where they are all zero."""
+    n, hw, c = 4, 8, 16
+    m = PM.Model("bn", (8, hw, hw), 6)
+    y = m.maxpool(m.conv(-1, c, 3), 3, 2, 1)
+    r = m.relu(m.bn(y))
+    y = m.conv(r, 16, 3)
+    m.new_unit()
+    m.linear(m.gap(y), 6)
+    m.assign_blocks([1, 2])
+    x = T.init_x(m.specs, 5).astype(np.float32)
+    lo = c * 8 * 9                   # gamma, beta
+    x[lo:lo + 2 * c] = 0
+    x[lo:lo + c] = np.array([1.0, 1e-40, 0.0, -1e-40] * (c // 4), np.float32)
+    x[lo + c] = 0.3
+    g = torch.Generator("cuda").manual_seed(3)
+    img = torch.randn((n, 8, hw, hw), generator=g, device="cuda")
+    lab = torch.randint(6, (n,), generator=g, device="cuda", dtype=torch.int32)
+    with lpp.Context(m, K=1, batch=n, mode=mode, dtype=lpp.BF16) as ctx:
+        ctx.set_params(x)
+        torch.cuda.synchronize()
+        ctx.step(0, img, lab, 0, 0.0)
+        out = ctx.get_activation(0, r, (c, 4, 4))
+        dy = ctx.get_activation_grad(0, r, (c, 4, 4)).astype(np.float64)
+        got = ctx.get_grad(0)[lo + c:lo + 2 * c]
+    assert np.any(out[:, 1] > 0) and np.any(out[:, 1] == 0) and not np.any(out[:, 2])
+    masked = np.where(out > 0, dy, 0.0)
+    # a decision that differs moves its channel's sum by a term, 1/64 of their magnitudes and more
+    assert np.all(np.abs(got - masked.sum((0, 2, 3))) <= 1e-5 * np.abs(dy).sum((0, 2, 3)))
