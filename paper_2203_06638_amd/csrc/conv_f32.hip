@@ -44,28 +44,6 @@ __device__ __forceinline__ f4 mfma16x16x4(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Copies n float4 into LDS: addr(i, src, dst) names element i's source (null:
-// zero) and LDS destination.  Each thread issues NB global loads before their
-// LDS stores, so the load latencies overlap instead of adding up.
-template <int NB, class Addr>
-__device__ __forceinline__ void lds_stage(int n, Addr addr) {
-    for (int base = threadIdx.x; base < n; base += NB * 256) {
-        f4 v[NB];
-        float* d[NB];
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int i = base + u * 256;
-            const float* src = nullptr;
-            d[u] = nullptr;
-            if (i < n) addr(i, src, d[u]);
-            v[u] = src ? *(const f4*)src : f4{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-        for (int u = 0; u < NB; ++u)
-            if (d[u]) *(f4*)d[u] = v[u];
-    }
-}
-
 // Offset of source pixel (n, hs, ws) feeding output pixel (n, p, q) through
 // tap (r, s), or -1 when the tap falls in the zero padding / between strides.
 template <int MODE>

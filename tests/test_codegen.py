@@ -11,10 +11,12 @@ loops carry no such wait, and that the transpose reads issued as inline asm
 (which the compiler does not count) leave their destination registers alone
 until the kernel's own lgkmcnt wait.
 
-The fp32 weight-gradient tile kernel stages its tiles in batches of eight
-loads per thread; with a conditional load and the BN fold right behind each,
-the compiler sent them out one round trip at a time.  The kernel issues a
-batch's loads first; a test checks that every instance still does.
+The fp32 weight-gradient tile kernel stages a box with six loads of the input
+and NG of the output gradient per thread; with a conditional load and the BN
+fold right behind each, the compiler sent them out one round trip at a time.
+The kernel issues all of them first, and like the spatial forward and
+data-gradient kernels it leaves the next box's (or channel group's) loads in
+flight during the MFMAs; tests check that every instance still does.
 """
 import os
 import re
@@ -121,15 +123,41 @@ def test_wgrad_transpose_reads(asm):
         assert waited, name
 
 
-def test_fp32_wgrad_staging_loads_in_flight(tmp_path_factory):
-    fns = functions(compile_asm(tmp_path_factory, "conv_f32"), "_ZN3lpp19conv_wgrad_tile_f32")
+@pytest.fixture(scope="module")
+def asm_f32(tmp_path_factory):
+    return compile_asm(tmp_path_factory, "conv_f32")
+
+
+def memory_order(body):
+    """Loads from memory (G), waits for all of them (V) or some (v), and MFMAs
+    (M) of a kernel in program order."""
+    out = ""
+    for l in body:
+        if l.startswith(("global_load", "flat_load", "buffer_load")):
+            out += "G"
+        elif l.startswith("s_waitcnt") and "vmcnt" in l:
+            out += "V" if "vmcnt(0)" in l else "v"
+        elif l.startswith("v_mfma"):
+            out += "M"
+    return out
+
+
+def test_fp32_wgrad_staging_loads_in_flight(asm_f32):
+    fns = functions(asm_f32, "_ZN3lpp19conv_wgrad_tile_f32")
     assert len(fns) >= 12
     for name, body in fns.items():
-        # loads (G) and full vmcnt waits (V) in program order
-        seq = "".join("G" if l.startswith(("global_load", "flat_load", "buffer_load")) else "V" for l in body
-                      if l.startswith(("global_load", "flat_load", "buffer_load"))
-                      or (l.startswith("s_waitcnt") and "vmcnt(0)" in l))
-        # the first staging batch: eight loads before the first full wait,
-        # and nowhere a run of single loads each followed by one
-        assert seq.find("V") >= 8, (name, seq[:40])
+        seq = memory_order(body)
+        # the fold's scale and shift and the first box's loads before any
+        # wait, and nowhere a run of single loads each followed by a full one
+        ng = int(re.search(r"ILi\d+ELi(\d)E", name).group(1))
+        assert re.search("[vV]", seq).start() >= 2 + 6 + ng, (name, seq[:40])
         assert not re.search(r"(?:G{1,3}V){4,}", seq), (name, seq[:80])
+
+
+@pytest.mark.parametrize("kernel", ["19conv_wgrad_tile_f32", "13conv_tile_f32", "17conv_dgrad_s2_f32"])
+def test_fp32_next_loads_in_flight_during_mfmas(asm_f32, kernel):
+    fns = functions(asm_f32, "_ZN3lpp" + kernel)
+    assert len(fns) >= 4
+    for name, body in fns.items():
+        seq = memory_order(body)
+        assert seq[seq.index("M") - 1] == "G", (name, seq[:80])
