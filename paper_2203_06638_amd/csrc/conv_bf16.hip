@@ -462,9 +462,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 256 ?
 // larger tiles win although each pass alone is slower: WRN-16-8 +11%,
 // ResNet-18 +5%, ResNet-50 +2% against fill 512 (64 and 96 are no better;
 // holding the 256-row tile to 256 or 512 workgroups there, WRN-16-8 -3%, -5%).
-// 128 x 128 tiles of two load steps pay from three quarters of `fill`: 64 x
-// 28x28x128 (392 of them) 33 us with 64 rows, 25 with 128; 128 x 8x8x512 (256)
-// 59 and 69.
+// 128 x 128 tiles of two load steps pay as soon as 64-row tiles no longer fit
+// the chip at two to a compute unit, from 257 of them on: over 16x16 maps of
+// 64 to 512 channels, 1x1 and 3x3, 64 rows take 0.81-0.97 of the time with 224
+// or 256 such tiles, 1.08-1.30 times it with 288, 1.10-1.24 with 384, 1.18-1.31
+// with 448 (256 -> 256 channels, 3x3: 33.8 us and 39.7 with 256, 54.3 and 41.7
+// with 288).  With several streams, from three quarters of `fill`.
 static void pick_bf16(long Mv, int Ncols, int Cs, int fill, int& bm, int& bn) {
     bn = Ncols >= 128 ? 128 : 64;
     const long nt = (Ncols + bn - 1) / bn;
@@ -472,7 +475,8 @@ static void pick_bf16(long Mv, int Ncols, int Cs, int fill, int& bm, int& bn) {
         bm = 256;
         return;
     }
-    bm = ((Mv + 127) / 128) * nt >= (Cs % 64 == 0 && bn == 128 ? fill * 3 / 4 : fill) ? 128 : 64;
+    const long least = Cs % 64 || bn != 128 ? fill : (fill == 512 ? 257 : fill * 3 / 4);
+    bm = ((Mv + 127) / 128) * nt >= least ? 128 : 64;
 }
 
 int conv_bf16_tile_rows(const ConvGeom& g) {
