@@ -331,8 +331,8 @@ TRAFFIC_SOURCES = ["paper_2203_06638_amd/csrc/conv_f32.hip", "paper_2203_06638_a
                    "paper_2203_06638_amd/csrc/bnacc.h"]
 COPY_BYTES = 256 << 20
 # kernel-name prefixes of each timed family (the library's launchers)
-FAMILY_KERNELS = {"conv_fwd": ("void lpp::conv_tile_f32<0,", "void lpp::conv_igemm_f32<0,", "void lpp::conv_lds_f32<0,",
-                               "void lpp::conv_bf16_k<"),
+FAMILY_KERNELS = {"conv_fwd": ("void lpp::conv_tile_f32<0,", "void lpp::conv_stem_f32<", "void lpp::conv_igemm_f32<0,",
+                               "void lpp::conv_lds_f32<0,", "void lpp::conv_bf16_k<"),
                   "sgd_update": ("lpp::sgd_update_k(",),
                   "average": ("void lpp::average_k<",)}
 

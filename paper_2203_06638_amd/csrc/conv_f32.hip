@@ -1718,7 +1718,7 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
 // column tiles: 3x3 three, 7x7 fourteen) read from LDS as they lie, 16
 // consecutive floats from the pixel of the first tap.  Columns past the filter
 // row are formed and dropped.  (128 x 32x32, 4 -> 16: 10.3 us with a column
-// tile per tap, 7.4 here; 4 -> 96: 36, 19; 7x7/2, 4 -> 64: 97, 82.)
+// tile per tap, 7.4 here; 4 -> 96: 36, 22; 7x7/2, 4 -> 64: 97, 80.)
 template <int KS, int NG, int ST, bool FULL, bool FAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KS == 3 && (FULL || NG == 2) ? 4 : 3, 8)))
 void conv_wgrad_stem_f32(const float* __restrict__ dY, const float* __restrict__ X,
