@@ -1,9 +1,11 @@
 """The fp32 spatial tiles at the edges of their boxes (widths that leave part
 of a box empty, boxes over the end of an image, one image, rows longer than a
 box, channel counts in fours), the stem kernels, the stride-2 data gradient on
-odd grids, pooled heads over large maps, the 2x2 max-pool gradient, and the
-threaded copies to the host: against the fp64 oracle with the bars of
-tests/parity.py, or bit for bit where nothing is rounded."""
+odd grids, pooled heads over large maps, the 2x2 max-pool gradient, weight
+gradients over many boxes and channel blocks, infinities, tensors over 2 GiB,
+the bf16 ReLU decision recomputed, and the threaded copies to the host:
+against the fp64 oracle with the bars of tests/parity.py, or bit for bit where
+nothing is rounded."""
 import sys
 import threading
 
