@@ -740,7 +740,7 @@ int sync_all(lpp_ctx* c) {
 // thread's) or made on another device takes hipMemcpy.
 constexpr int kFetchThreads = 4;
 constexpr size_t kFetchPool = 8 << 20;        // bytes, two slots to a thread
-constexpr size_t kFetchMin = 64 << 10;        // smaller copies: hipMemcpy (15 us)
+constexpr size_t kFetchMin = 1 << 20;         // smaller copies: hipMemcpy (0.35 MB 26 us, 43 here; 1.1 MB 72 and 70)
 constexpr size_t kFetchPerThread = 4 << 20;   // bytes that pay for one more thread
 // bytes of a slot with T threads: whole pages, so that every transfer starts on one
 constexpr size_t fetch_slot(int T) { return kFetchPool / (2 * T) & ~size_t(4095); }
