@@ -1677,8 +1677,9 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
 // 96 -> 96 65 and 44; 32 x 28x28, 320 -> 320, 299 and 93; 96 -> 96, 2.3e8, 25
 // and 33; 16 x 32x32, 64 -> 256, 2.7e8, 28 and 32 (16 channels leave its tiles
 // mostly empty: 100 x 64x64, 16 -> 64, 52 and 68).  So do 3x3 passes of stride 2
-// from 128 blocks on: 32 x 14x14, 128 -> 256, 71 and 67, 320 -> 320 217 and 174;
-// 40 x 20x20, 96 -> 192, 72 blocks, 72 and 77.
+// from 128 blocks and 2^27 products (per tap) on: 32 x 14x14, 128 -> 256, 71 and
+// 67, 320 -> 320 217 and 174; 16 x 13x13, 160 -> 320, 1.4e8, 67 and 56; 4 x
+// 13x13, 144 -> 288, 2.8e7, 16 and 21; 40 x 20x20, 96 -> 192, 72 blocks, 72 and 77.
 struct WgTileCfg { int ng, tiles, per, splits, run; BoxGeom t; size_t lds; };
 static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, int Cout, int R, int S, int stride,
                             int pad, WgTileCfg& out) {
@@ -1686,7 +1687,9 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
     if (Cin_p < 16 && Cout > 32) return false;   // mostly empty MFMA columns: the GEMM kernel is as fast
     const long blocks = (long)((Cout + 15) / 16) * ((Cin_p + 15) / 16);
     const double M = (double)Nb * Ho * Wo;
-    if (R == 1 ? Cin_p > 16 && M * Cin_p * Cout >= (M >= 32768 ? 268435456.0 : 3e8) : stride == 2 && blocks >= 128)
+    const double products = M * Cin_p * Cout;
+    if (R == 1 ? Cin_p > 16 && products >= (M >= 32768 ? 268435456.0 : 3e8)
+               : stride == 2 && blocks >= 128 && products >= 134217728.0)
         return false;
     const long most = blocks <= 384 ? 768 / blocks : std::min<long>(4, (1535 + blocks) / blocks);
     bool found = false;

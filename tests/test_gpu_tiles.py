@@ -87,7 +87,8 @@ def test_tile_edges(case):
     (3, 32, 64, 1, 1, 0, 40, 12),     # 32-channel 1x1 tiles
     (3, 16, 32, 3, 3, 1, 19, 3),      # stride 3: the gather data gradient
     (3, 320, 320, 3, 1, 1, 10, 3),    # weight gradient of 400 channel blocks
-    (3, 128, 256, 3, 2, 1, 9, 2),     # weight gradients on the GEMM kernel: stride 2 of many blocks,
+    (3, 128, 256, 3, 2, 1, 9, 2),     # stride 2 of many blocks, few pixels
+    (3, 128, 256, 3, 2, 1, 33, 15),   # weight gradients on the GEMM kernel: more pixels,
     (3, 64, 80, 1, 1, 0, 60, 20),     # large 1x1 passes,
     (3, 64, 64, 1, 1, 0, 32, 64),     # rows of 2^k
 ], ids=lambda c: "x".join(map(str, c)))
