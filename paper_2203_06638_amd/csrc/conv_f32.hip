@@ -1666,7 +1666,10 @@ void conv_wgrad_tile_f32(const float* __restrict__ dY, const float* __restrict__
 // single box of 256 slots where that gives at least 512 workgroups, else a run
 // of boxes of 128 slots, or of 64 where 128 leave fewer than 512 and 64 give
 // more (measured over 512-1536 workgroups and all three sizes: within 4% of
-// the best of 22 passes).  More blocks do not divide a round: up to four
+// the best of 22 passes); 1x1 passes whose boxes are all full take one of 256
+// slots each in up to three rounds (64 x 32x32, 32 -> 32 19.2 us in runs, 14.6
+// so; 64 -> 64 at 32 x 32x32 23.9 and 18.6; ragged ones, 32 x 28x28, 64 -> 64,
+// 17.2 and 18.5).  More blocks do not divide a round: up to four
 // splits, at least 1536 workgroups where they suffice, even out the rounds (16
 // x 14x14: 320 -> 320 channels with one split 110 us, with four 95; 448 -> 448
 // 202, two 177; 768 blocks 152, two 152, three 160).
@@ -1703,7 +1706,8 @@ static bool pick_wgrad_tile(int Nb, int Hi, int Wi, int Cin_p, int Ho, int Wo, i
         c.lds = sizeof(float) *
                 std::max<size_t>(((size_t)c.t.IH * c.t.IW + ng * 64) * 20, (size_t)4 * R * S * 256 + 4);
         c.tiles = box_tiles(c.t);
-        const long splits = std::min<long>(c.tiles, most);
+        const bool each = R == 1 && ng == 4 && c.tiles * blocks <= 2304 && box_full(c.t, 256);
+        const long splits = each ? c.tiles : std::min<long>(c.tiles, most);
         c.per = (int)((c.tiles + splits - 1) / splits);
         c.splits = (c.tiles + c.per - 1) / c.per;
         c.run = wg_run(ng, Wo);

@@ -91,6 +91,8 @@ def test_tile_edges(case):
     (3, 128, 256, 3, 2, 1, 33, 15),   # weight gradients on the GEMM kernel: more pixels,
     (3, 64, 80, 1, 1, 0, 60, 20),     # large 1x1 passes,
     (3, 64, 64, 1, 1, 0, 32, 64),     # rows of 2^k
+    (3, 32, 64, 1, 1, 0, 32, 40),     # 1x1 weight gradients of single full boxes,
+    (3, 32, 64, 1, 1, 0, 32, 80),     # and of runs
 ], ids=lambda c: "x".join(map(str, c)))
 def test_second_conv_edges(case):
     cin, c0, c1, k, st, pad, hw, n = case
